@@ -272,6 +272,12 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     // step (measured + 2 - 4 % at 512 x 512 and 1024 x 1024 with 128 channels; with a single round it only costs,
     // and so it does on a 1x1 call, whose two rounds are memory traffic from start to end: 30 -> 32.5 us)
     a.stagger = (p->cfg == 0 && g->k >= 3 && (long)p->groups * p->bands * p->slabs * p->ksplit >= 1024) ? 1 : 0;
+    // Chunks requested ahead: the 64 x 32 shape on a 3x3 call whose workgroups walk through two chunks or more,
+    // nothing to compute on the way in (Scale+Shift would have to be kept per chunk) and a tile that is one
+    // batch of vectors for the 256 threads (a pixel of a chunk is 2 * kc vectors).  One chunk has nothing to hide.
+    const long pipe_vectors = (long)p->G * p->trows * tw * 2 * p->kc;
+    p->pipe = p->cfg == 3 && g->k == 3 && (p->kc == 4 || p->kc == 8) && a.scale == nullptr && a.act == SIGE_ACT_NONE &&
+              pipe_vectors <= 256L * kPipeVectors && Cin / (p->kc * ks) > p->ksplit;
     a.d_pb = fast_div(p->rows * g->block_w);
     a.d_per = fast_div(p->trows * tw);
     a.d_tw = fast_div(tw);

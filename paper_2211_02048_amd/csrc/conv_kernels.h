@@ -284,6 +284,7 @@ constexpr int ring_depth(int steps, int limit)
     return d;
 }
 
+constexpr int kPipeVectors = 8;   // 16-byte vectors per thread of a chunk that is requested ahead
 constexpr int MAX_G = 256;   // most blocks one workgroup can hold (1x1 blocks in a 256-row patch)
 
 // TM x TN: 32x32 MFMA tiles per wave; WM x WN x WK = 4 (or 8) waves over M, N and K (waves that
@@ -293,7 +294,8 @@ constexpr int MAX_G = 256;   // most blocks one workgroup can hold (1x1 blocks i
 // phase has nothing to overlap its LDS and L2 latencies with.
 // (The body is a device function so that two calls can share one launch, see conv_pair_kernel;
 // bx, by, bz are the workgroup's coordinates inside its own call's grid.)
-template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool MARKED = false>
+// PIPE: the next chunk's pixels are requested while the current chunk is multiplied (see the loop).
+template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool MARKED = false, bool PIPE = false>
 __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const int by, const int bz)
 {
     constexpr int NT = 64 * WM * WN * WK;                     // threads per workgroup
@@ -505,7 +507,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // group and walks over the pixels NT / VPC at a time without dividing.  Each batch of U vectors
     // is loaded before any of them is used (addresses are clamped into the source, so the loads are
     // unconditional and overlap; what lies outside becomes zero afterwards).
-    constexpr int U = TM * TN >= 4 ? 6 : 8;                   // fewer where the accumulators leave fewer registers
+    constexpr int U = TM * TN >= 4 ? 6 : PIPE ? kPipeVectors : 8;   // fewer where the accumulators leave fewer registers
     constexpr int PPI = NT / VPC;                             // pixels covered by one step of the walk
     constexpr int NTS = PPI * VPC;                            // threads that stage (all of them unless VPC is 40 or 80)
     const int sv = tid % VPC;
@@ -643,8 +645,59 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         // network step and every kilobyte of code is fetched first)
         if constexpr (SWAP) stage(ch0);
         start_accumulators();
+        // PIPE.  A workgroup of this shape is bound by round trips: with two or more chunks each cost a
+        // staging round trip (1.7 us from memory) before its 0.9 us of MFMA steps, nothing of the next
+        // chunk in flight meanwhile.  Here the whole tile is one batch of U vectors per thread (the host
+        // checks that it fits), whose source addresses differ from chunk to chunk by a constant: they are
+        // worked out once, and the next chunk's vectors are requested one per step between the weights of
+        // the current chunk (one per step, so that the in-order load counter never makes a weight wait for
+        // a whole tile), waited for only where they go into LDS.
+        // Measured, bf16, weights from memory: 1920 -> 640 channels on 11 8x8 blocks (15 chunks) 46.6 -> 36.7 us,
+        // 960 -> 320 on 25 blocks 40.2 -> 30.1, five chunks a workgroup 20.5 -> 19.1, two chunks 12.5 -> 11.7.
+        const char* src[PIPE ? U : 1];
+        uint4 nextv[PIPE ? U : 1];
+        unsigned inside = 0u;
+        if constexpr (PIPE) {
+            static_assert(!SWAP && U <= STEPS, "one request per step");
+            const char* const base = (fused ? (const char*)a.x : tiles) + (long)ch0 * (KC * KS * S) + sv * 16;
+            const long px_bytes = (long)(fused ? a.x_ld : a.Cin) * S;
+            int q = sq0, g = sg0, r = sr0, x = sx0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int gl = min(g, a.G - 1), rr = min(r, rmax);
+                bool ok = q < npix && r <= rmax && g0 + g < n_eff;
+                int pix;
+                if (!fused) {
+                    pix = (min(g0 + gl, n_eff - 1) * a.th + trow0 + rr) * a.tw + x;
+                } else {
+                    const int iy = org[2 * gl] * a.stride - a.pad + trow0 + rr, ix = org[2 * gl + 1] * a.stride - a.pad + x;
+                    ok = ok && iy >= 0 && iy < a.Hin && ix >= 0 && ix < a.Win;
+                    pix = (min(max(iy, 0), a.Hin - 1) >> a.up) * Ws + (min(max(ix, 0), a.Win - 1) >> a.up);
+                }
+                src[u] = base + pix * px_bytes;
+                nextv[u] = *(const uint4*)src[u];
+                inside |= ok ? 1u << u : 0u;
+                q += PPI;
+                x += step_x;
+                r += step_r;
+                if (x >= a.tw) { x -= a.tw; ++r; }
+                g += step_g;
+                if (r >= a.trows) { r -= a.trows; ++g; }
+            }
+        }
         for (int chunk = ch0; chunk < ch1; ++chunk) {
-            if (!SWAP || chunk != ch0) stage(chunk);
+            long ahead = 0;                                   // bytes to the chunk requested next (the last one again at the end)
+            if constexpr (PIPE) {
+                if (chunk != ch0) __syncthreads();
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (sq0 + u * PPI < npix)
+                        *(uint4*)(lds + (sq0 + u * PPI) * a.ps + sv * 16) = (inside >> u) & 1u ? nextv[u] : make_uint4(0, 0, 0, 0);
+                __syncthreads();
+                ahead = (long)(min(chunk + 1, ch1 - 1) - ch0) * (KC * KS * S);
+            } else {
+                if (!SWAP || chunk != ch0) stage(chunk);
+            }
             // A rows run AD steps ahead of their MFMAs: one step where a step holds four MFMAs or
             // more, two where it holds fewer and would not cover the LDS latency.  In the small shapes
             // a barrier after the loads keeps them in front of this step's MFMAs (the scheduler
@@ -661,6 +714,8 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 multiply(af[st % (AD + 1)], ring[st % D]);
                 const int nx = (st + D) % STEPS;              // the step that takes over this slot
                 fetch(ring[st % D], st + D < STEPS ? chunk : chunk + 1, nx / KW, nx % KW);
+                if constexpr (PIPE)
+                    if (st < U) nextv[st] = *(const uint4*)(src[st] + ahead);
                 // nothing moves across a step boundary: left alone, the scheduler sinks every prefetch
                 // down to its first use to save registers and the ring collapses
                 __builtin_amdgcn_sched_barrier(0);
@@ -825,7 +880,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     }
 }
 
-template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK>
+template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool PIPE = false>
 __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK > 4 ? 1 : 2)) void conv_kernel(ConvArgs a)
 {
     if constexpr (WK == 1 && TM * TN >= 4) {
@@ -839,7 +894,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK > 4 ? 1 : 2)) void
                 for (int i = 0; i < a.stagger; ++i) __builtin_amdgcn_s_sleep(127);
         }
     }
-    conv_body<T, TM, TN, WM, WN, WK, KC, KK>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    conv_body<T, TM, TN, WM, WN, WK, KC, KK, false, PIPE>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Two independent calls in ONE launch: a 3x3 convolution and a 1x1 convolution that both take the
@@ -1244,6 +1299,7 @@ struct ConvPlan {
     int kc;   // K steps per staged channel chunk: 8, 4 or 1; 16 to 40 in the shapes that stage the whole of Cin
     int G, rows, trows, Cc, ps, bands, slabs, groups;
     int ksplit;   // workgroups that share one output patch along K (1 = no split)
+    bool pipe;    // the 64 x 32 shape with chunks requested ahead (see conv_body)
     size_t lds;
 };
 
@@ -1252,10 +1308,10 @@ struct CfgShape { int M, N, WK; };
 constexpr int kNumCfg = 4;    // shapes that compete by score; the last two are chosen by a rule of their own
 static const CfgShape kCfg[kNumCfg + 2] = {{128, 128, 1}, {128, 64, 1}, {64, 64, 1}, {64, 32, 4}, {64, 32, 8}, {32, 32, 8}};
 
-template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK>
+template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool PIPE = false>
 int launch_cfg(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
 {
-    auto kern = conv_kernel<T, TM, TN, WM, WN, WK, KC, KK>;
+    auto kern = conv_kernel<T, TM, TN, WM, WN, WK, KC, KK, PIPE>;
     if (p.lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)p.lds);
@@ -1281,6 +1337,8 @@ int launch_kc(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
         if constexpr (KC <= 8) return launch_cfg<T, 1, 1, 2, 2, 1, KC, KK>(a, p, st);
         break;
     case 3:
+        if constexpr ((KC == 4 || KC == 8) && KK == 9)
+            if (p.pipe) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, true>(a, p, st);
         if constexpr (KC % 4 == 0 && (KC <= 8 || (KC == 20 && KK == 9))) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK>(a, p, st);
         break;
     case 4:

@@ -1215,3 +1215,52 @@ def test_recorded_calls_repeat_the_step():
     calls.calls[0] = (fn, args[:2] + (99,) + args[3:])          # an unknown dtype
     with pytest.raises(api.SigeError):
         calls.run()
+
+
+@pytest.mark.parametrize("dtype,Cin,Cout,H,W,b,stored,kn", [
+    ("bf16", 384, 72, 24, 24, 8, False, {}),                             # three chunks of 128, 10 x 10 tiles
+    ("f16", 256, 40, 37, 50, 16, False, {}),                             # two chunks, row bands, ragged edges and channels
+    ("bf16", 256, 64, 21, 19, 4, False, dict(CONV_KC=4)),    # four blocks per workgroup, chunks of 64
+    ("f16", 640, 64, 16, 16, 8, False, dict(CONV_KC=8, CONV_SPLIT=2)),   # shares of two and three chunks
+    ("f32", 192, 40, 20, 20, 6, False, dict(CONV_KC=8)),
+    ("bf16", 384, 64, 24, 24, 8, True, {}),                              # stored tiles
+])
+def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, stored, kn):
+    """Calls of the 64 x 32 shape that walk through two chunks or more without staged arithmetic request the
+    next chunk ahead.  Scale 1 and shift 0 send the same call down the staging that does not: equal bit for
+    bit (same sums in the same order), and both against the oracle."""
+    rng = np.random.default_rng(Cin + Cout + H)
+    td = DT[dtype]
+    x = torch.from_numpy(rng.standard_normal((H, W, Cin)).astype(np.float32)).to(td)
+    w, bias = inputs.conv_params(rng, Cout, Cin, 3, td)
+    cache = torch.from_numpy(rng.standard_normal((H, W, Cout)).astype(np.float32)).to(td)
+    conv = SigeConv(dev(w), bias, H, W, b, 1, 1)
+    g = conv.g
+    bl = BlockList(g, "cuda").all_active()
+    n = g.grid_blocks
+    pick = np.unique(np.append(rng.permutation(n)[:max(3, n // 3)], n - 1))
+    n = len(pick)
+    blocks = bl.indices[torch.from_numpy(pick).cuda()].clone()
+    bl.indices.fill_(0)
+    bl.indices[:n].copy_(blocks)
+    bl.count.fill_(n)
+    bl.n_host = n
+    one, zero = torch.ones(Cin, device="cuda"), torch.zeros(Cin, device="cuda")
+    ws = Workspace("cuda")
+    with api.knobs(**{**dict(CONV_CFG=3, CONV_SPLIT=1), **kn}):
+        if stored:
+            tiles = torch.from_numpy(rng.standard_normal((n + 1, g.tile_h, g.tile_w, Cin)).astype(np.float32)).to(td)
+            out = torch.full((n + 1, b, b, Cout), 5.0, dtype=td, device="cuda")
+            api.sige_conv(dev(tiles), g, Cin, Cout, conv.packed, conv.bias, bl.count, out, n_blocks=n, max_blocks=n)
+            want = np.stack([oracle.conv2d(f64(tiles[i]), f64(w), f64(bias), 1, 0) for i in range(n)])
+            assert_close(out[:n], want, td, "stored tiles")
+            assert (out[n:] == 5.0).all()
+            return
+        got = []
+        for scale, shift in ((None, None), (one, zero)):
+            y = dev(cache).clone()
+            conv.forward(dev(x), y, bl, ws, scale=scale, shift=shift, fused=True)
+            got.append(y)
+    assert torch.equal(got[0], got[1])
+    want = oracle.select_blocks(oracle.conv2d(f64(x), f64(w), f64(bias), 1, 1), f64(cache), blocks.cpu().numpy(), b, b)
+    assert_close(got[0], want, td, "requested ahead")

@@ -238,7 +238,17 @@ static int pointwise_tiles(const sige_geom* g, const ConvArgs& a, int ks, int nl
     // the smallest patch that still fits one workgroup per compute unit
     if ((rows + 31) / 32 * nt <= 256) return 3;
     if (mt * nt <= 256) return 1;
-    if (mt * ((nt + 1) / 2) <= (kcs >= 64 ? 512 : 256)) return 2;   // a long K: better two rounds here than the tiled kernel's chunks
+    const long patches = mt * ((nt + 1) / 2);
+    if (patches <= (kcs >= 64 ? 512 : 256)) return 2;       // a long K: better two rounds here than the tiled kernel's chunks
+    // Half types, up to eight 64 x 64 patches per compute unit: still this kernel, whose weights and rows are
+    // in flight from the first instruction while the tiled one stages its chunks in turn (bf16, weights from
+    // memory, tiled -> here: 640 rows 320 -> 2560 channels 17.0 -> 9.5 us, 1280 -> 3840 36.5 -> 22.4; 2240 rows
+    // 1280 -> 1280 37.3 -> 22.7, 320 -> 2560 27.4 -> 22.6; beyond 2048 patches even or slower: 1280 rows
+    // 1280 -> 10240 84.9 vs 86.8), unless the tiled kernel's 128 x 128 patches come out as nearly whole rounds of one per compute unit, which then
+    // runs at the rate of its MFMA phase (4096 rows 640 -> 1920: 25.3 vs 31.7 us; 2240 rows 640 -> 5120 even).
+    // fp32 is left where it was: its patches are bound by the MFMAs and gain or lose by 15 % either way.
+    const long big = (rows + 127) / 128 * ((a.Cout + 127) / 128), whole = (big + 255) / 256 * 256;
+    if (ks == 16 && patches <= 2048 && big * 100 < whole * 85) return 2;
     return 0;
 }
 

@@ -1264,3 +1264,31 @@ def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, stored, 
     assert torch.equal(got[0], got[1])
     want = oracle.select_blocks(oracle.conv2d(f64(x), f64(w), f64(bias), 1, 1), f64(cache), blocks.cpu().numpy(), b, b)
     assert_close(got[0], want, td, "requested ahead")
+
+
+@pytest.mark.parametrize("dtype,Cin,Cout,b,n,kernel", [
+    ("bf16", 320, 2560, 8, 10, 1),       # 400 patches of 64 x 64: beyond one per compute unit
+    ("f16", 320, 2536, 5, 27, 1),        # 675 rows and a channel count that end inside a patch
+    ("bf16", 320, 6400, 8, 16, 1),       # 1600 patches; 128 x 128 patches would leave a fifth of the last round idle
+    ("bf16", 320, 8320, 8, 16, 0),       # 2080 patches: more than the rule takes
+    ("f16", 320, 4096, 8, 16, 0),        # 128 x 128 patches in exactly one round of 256: the tiled kernel
+    ("f32", 320, 2560, 8, 10, 0),        # fp32 keeps the tiled kernel
+])
+def test_conv_pointwise_more_patches_than_compute_units(oracle, dtype, Cin, Cout, b, n, kernel):
+    """The rule that sends larger 1x1 calls of the half types to the few-row kernel, and both kernels against
+    the oracle on the same stacked tiles."""
+    rng = np.random.default_rng(Cin + Cout)
+    td = DT[dtype]
+    g = api.geom(64, 64, b, 1, 1, 0)
+    w, bias = inputs.conv_params(rng, Cout, Cin, 1, td)
+    packed = api.sige_pack_weight(dev(w))
+    tiles = torch.from_numpy(rng.standard_normal((n, b, b, Cin)).astype(np.float32)).to(td)
+    cnt = torch.tensor([n], dtype=torch.int32, device="cuda")
+    want = oracle.conv2d(f64(tiles).reshape(n * b, b, Cin), f64(w), f64(bias), 1, 0).reshape(n, b, b, Cout)
+    assert api.sige_conv_plan(td, g, Cin, Cout, n).kernel == kernel
+    for mode in (None, 0, 2):
+        with api.knobs(CONV_POINTWISE=mode):
+            out = torch.full((n + 1, b, b, Cout), 5.0, dtype=td, device="cuda")
+            api.sige_conv(dev(tiles), g, Cin, Cout, packed, dev(bias.float()), cnt, out, n_blocks=n, max_blocks=n)
+            assert_close(out[:n], want, td, f"mode={mode}")
+            assert (out[n:] == 5.0).all()

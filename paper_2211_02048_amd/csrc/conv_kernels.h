@@ -486,7 +486,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // bound, fetching the whole chunk ahead (18 loads per wave) holds up the tile loads behind it by
     // more than it saves later (measured 7.5 vs 7.9 us on a 9-block call with 6 vs 18 slots).
     constexpr int STEPS = KK > 0 ? KK * KW : 1;
-    constexpr int D = KK == 0 ? 1 : ring_depth(STEPS, TN == 1 ? 6 : 8);
+    constexpr int D = KK == 0 ? 1 : ring_depth(STEPS, PIPE ? 9 : TN == 1 ? 6 : 8);
     const int nch = a.Cin / (KC * KS);
     int ch0 = 0, ch1 = nch, rem_unused;                       // this workgroup's chunks
     if (a.ksplit > 1) {
@@ -638,8 +638,11 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     };
 
     if constexpr (KK > 0) {
+        auto fill_ring = [&]() {
 #pragma unroll
-        for (int d = 0; d < D; ++d) fetch(ring[d], ch0, d / KW, d % KW);
+            for (int d = 0; d < D; ++d) fetch(ring[d], ch0, d / KW, d % KW);
+        };
+        if constexpr (!PIPE) fill_ring();
         // (shapes with start values from memory stage the first chunk ahead of the loop, so that those values
         // are dead before the loop begins; the others keep the one staging site - their kernels start cold in a
         // network step and every kilobyte of code is fetched first)
@@ -652,8 +655,12 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         // worked out once, and the next chunk's vectors are requested one per step between the weights of
         // the current chunk (one per step, so that the in-order load counter never makes a weight wait for
         // a whole tile), waited for only where they go into LDS.
-        // Measured, bf16, weights from memory: 1920 -> 640 channels on 11 8x8 blocks (15 chunks) 46.6 -> 36.7 us,
-        // 960 -> 320 on 25 blocks 40.2 -> 30.1, five chunks a workgroup 20.5 -> 19.1, two chunks 12.5 -> 11.7.
+        // The tile is asked for before the first weights, whose ring is nine slots deep here: six left a long
+        // walk waiting for weights (0.8 us a round trip, three of them per chunk of 18 steps), eighteen were
+        // slower again where two workgroups share a compute unit (20.3 -> 22.0 us on 320 workgroups of five chunks).
+        // Measured, weights from memory, before -> now: bf16 1920 -> 640 channels on 11 8x8 blocks (15 chunks)
+        // 46.6 -> 34.2 us, 960 -> 320 on 25 blocks (15 chunks of 64) 40.2 -> 23.6, 1280 -> 1280 on one block (two
+        // chunks a workgroup) 12.5 -> 12.0; f16 256 -> 256 at 64x64 (two chunks) 9.9 -> 9.6.
         const char* src[PIPE ? U : 1];
         uint4 nextv[PIPE ? U : 1];
         unsigned inside = 0u;
@@ -684,6 +691,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 g += step_g;
                 if (r >= a.trows) { r -= a.trows; ++g; }
             }
+            fill_ring();
         }
         for (int chunk = ch0; chunk < ch1; ++chunk) {
             long ahead = 0;                                   // bytes to the chunk requested next (the last one again at the end)

@@ -220,8 +220,8 @@ extern "C" int sige_pack_weight(const void* w_oihw, sige_dtype dt, int32_t Cout,
 // Whether a call goes to pointwise_kernel, and with which patch per workgroup (0 = not; 1: 64 rows
 // x 32 channels, 2: 64 x 64, 3: 32 x 32 where the larger patches would leave most compute units
 // without work): a plain 1x1 (no scale, shift or activation on the way in), an even number of
-// K steps, and few enough rows that its patches do not fill the compute units more than once (then
-// the tiled kernel, which reads every weight once per 128 rows, is the better one).
+// K steps, and not so many rows that the tiled kernel, which reads every weight once per 128 rows,
+// is the better one (the rule at the end, with both sides measured).
 static int pointwise_tiles(const sige_geom* g, const ConvArgs& a, int ks, int nl)
 {
     const int force_v = knob(SIGE_KNOB_CONV_POINTWISE);     // 0 = never, 1 / 2 / 3 = that patch

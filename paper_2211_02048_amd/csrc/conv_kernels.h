@@ -1230,6 +1230,20 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
                 red[(wave * BM + m) * RS + tn * 32 + l32] = acc[tm][tn][r];
             }
     __syncthreads();
+    if (gathered && !to_y) {
+        // A gathered pixel outside the image is a row of zeros, as sige_gather stores it: the sums made from the
+        // clamped pixel that was read in its place do not count.  (Here and not in the K loop: a select there
+        // costs 1 % of every call, a condition in the loop below several.)
+        const int m = tid / W, w = tid % W, r = r0 + m;
+        if (m < BM && r < rows) {
+            int n, p, py, px;
+            divmod(r, a.d_pbfull, n, p);
+            divmod(p, a.d_bw, py, px);
+            if (org[2 * m] + py >= a.Hin || org[2 * m + 1] + px >= a.Win)
+                for (int i = 0; i < BN; ++i) red[(w * BM + m) * RS + i] = 0.0f;
+        }
+        __syncthreads();
+    }
     for (int e = tid; e < BM * (BN / N); e += 64 * W) {
         const int m = e / (BN / N), nn = (e - m * (BN / N)) * N;
         const int r = r0 + m, o = blockIdx.x * BN + nn;

@@ -1292,3 +1292,36 @@ def test_conv_pointwise_more_patches_than_compute_units(oracle, dtype, Cin, Cout
             api.sige_conv(dev(tiles), g, Cin, Cout, packed, dev(bias.float()), cnt, out, n_blocks=n, max_blocks=n)
             assert_close(out[:n], want, td, f"mode={mode}")
             assert (out[n:] == 5.0).all()
+
+
+@pytest.mark.parametrize("dtype,Cin,Cout,b,kernel_shape", [
+    ("f16", 320, 64, 8, 3),         # 32 x 32 patches
+    ("bf16", 640, 256, 16, 1),      # 64 x 32
+    ("f32", 320, 640, 6, 2),        # 64 x 64
+    ("f16", 320, 4224, 8, 2),       # 64 x 64, more patches than compute units
+])
+def test_few_row_kernel_tiles_of_ragged_blocks(oracle, dtype, Cin, Cout, b, kernel_shape):
+    """Gathered 1x1 calls that keep their tiles: a block's pixels outside the image are rows of zeros, as in the
+    tiles that sige_gather stores, so the fused call and gather + sige_conv agree bit for bit everywhere."""
+    rng = np.random.default_rng(Cin + Cout)
+    td = DT[dtype]
+    H, W = 21, 45
+    x = torch.from_numpy(rng.standard_normal((H, W, Cin)).astype(np.float32)).to(td)
+    w, bias = inputs.conv_params(rng, Cout, Cin, 1, td)
+    conv = SigeConv(dev(w), bias, H, W, b, 1, 0)
+    bl = BlockList(conv.g, "cuda").all_active()
+    n = bl.n_host
+    plan = api.sige_conv_plan(td, conv.g, Cin, Cout, n)
+    assert (plan.kernel, plan.shape) == (1, kernel_shape)
+    ws = Workspace("cuda")
+    got = conv.forward(dev(x), None, bl, ws, scatter=False, fused=True, tag="fused").view(n, b, b, Cout)
+    three = conv.forward(dev(x), None, bl, ws, scatter=False, fused=False, tag="three").view(n, b, b, Cout)
+    assert torch.equal(got, three)
+    outside = [(i, py, px) for i, (y0, x0) in enumerate(bl.indices.tolist()) for py in range(b) for px in range(b)
+               if y0 + py >= H or x0 + px >= W]
+    assert outside
+    i, py, px = (torch.tensor(v) for v in zip(*outside))
+    assert_close(got[i, py, px], np.broadcast_to(f64(bias), (len(outside), Cout)), td, "outside the image: the bias")
+    want = oracle.conv2d(f64(x), f64(w), f64(bias), 1, 0)
+    y0, x0 = bl.indices[0].tolist()
+    assert_close(got[0], want[:b, :b], td, "first block")

@@ -217,42 +217,56 @@ extern "C" int sige_pack_weight(const void* w_oihw, sige_dtype dt, int32_t Cout,
                             : launch_pack<bf16>(w_oihw, Cout, Cin, k, n, packed, st);
 }
 
-// Whether a call goes to pointwise_kernel, and with which patch per workgroup (0 = not; 1: 64 rows
-// x 32 channels, 2: 64 x 64, 3: 32 x 32 where the larger patches would leave most compute units
-// without work): a plain 1x1 (no scale, shift or activation on the way in), an even number of
-// K steps, and not so many rows that the tiled kernel, which reads every weight once per 128 rows,
-// is the better one (the rule at the end, with both sides measured).
+// Whether a call can go to pointwise_kernel at all: a plain 1x1 (no scale, shift or activation on the way in), an
+// even number of K steps, twenty of them or more (a short K is the tiled kernel's: one staged chunk).
+static bool pointwise_fits(const sige_geom* g, const ConvArgs& a, int ks, int nl)
+{
+    if (g->k != 1 || g->stride != 1 || g->pad != 0 || a.up != 0 || a.scale != nullptr || a.act != SIGE_ACT_NONE)
+        return false;
+    const int kcs = a.Cin / ks;
+    const long rows = (long)nl * g->block_h * g->block_w;
+    return kcs % 2 == 0 && (kcs >= 20 || knob(SIGE_KNOB_CONV_POINTWISE) >= 0) && (rows + 31) / 32 <= 65535;
+}
+
+// Whether a call goes to pointwise_kernel whatever runs beside it, and with which patch per workgroup (0 = not;
+// 1: 64 rows x 32 channels, 2: 64 x 64, 3: 32 x 32 where the larger patches would leave most compute units
+// without work): few enough rows that its patches do not fill the compute units more than once.
 static int pointwise_tiles(const sige_geom* g, const ConvArgs& a, int ks, int nl)
 {
     const int force_v = knob(SIGE_KNOB_CONV_POINTWISE);     // 0 = never, 1 / 2 / 3 = that patch
-    const bool force = force_v >= 0;
-    if (force && force_v == 0) return 0;
-    if (g->k != 1 || g->stride != 1 || g->pad != 0 || a.up != 0 || a.scale != nullptr || a.act != SIGE_ACT_NONE)
-        return 0;
+    if (force_v == 0 || !pointwise_fits(g, a, ks, nl)) return 0;
+    if (force_v > 0) return std::min(force_v, 3);
     const int kcs = a.Cin / ks;
-    if (kcs % 2 || (kcs < 20 && !force)) return 0;          // a short K is the tiled kernel's (one staged chunk)
     const long rows = (long)nl * g->block_h * g->block_w;
     const long mt = (rows + 63) / 64, nt = (a.Cout + 31) / 32;
-    if ((rows + 31) / 32 > 65535) return 0;
-    if (force) return std::min(std::max(force_v, 1), 3);
     // the smallest patch that still fits one workgroup per compute unit
     if ((rows + 31) / 32 * nt <= 256) return 3;
     if (mt * nt <= 256) return 1;
-    const long patches = mt * ((nt + 1) / 2);
-    if (patches <= (kcs >= 64 ? 512 : 256)) return 2;       // a long K: better two rounds here than the tiled kernel's chunks
-    // Half types, up to eight 64 x 64 patches per compute unit: still this kernel, whose weights and rows are
-    // in flight from the first instruction while the tiled one stages its chunks in turn (bf16, weights from
-    // memory, tiled -> here: 640 rows 320 -> 2560 channels 17.0 -> 9.5 us, 1280 -> 3840 36.5 -> 22.4; 2240 rows
-    // 1280 -> 1280 37.3 -> 22.7, 320 -> 2560 27.4 -> 22.6; beyond 2048 patches even or slower: 1280 rows
-    // 1280 -> 10240 84.9 vs 86.8), unless the tiled kernel's 128 x 128 patches come out as nearly whole rounds of one per compute unit, which then
-    // runs at the rate of its MFMA phase (4096 rows 640 -> 1920: 25.3 vs 31.7 us; 2240 rows 640 -> 5120 even).
-    // fp32 is left where it was: its patches are bound by the MFMAs and gain or lose by 15 % either way.
-    const long big = (rows + 127) / 128 * ((a.Cout + 127) / 128), whole = (big + 255) / 256 * 256;
-    if (ks == 16 && patches <= 2048 && big * 100 < whole * 85) return 2;
+    if (mt * ((nt + 1) / 2) <= (kcs >= 64 ? 512 : 256)) return 2;   // a long K: better two rounds here than the tiled kernel's chunks
     return 0;
 }
 
-// Shared by sige_conv, sige_conv_scatter and sige_fused_conv: plan and fill the arguments ...
+// The same question for calls of the half types with more 64 x 64 patches than compute units, up to eight of them
+// per compute unit: launched by itself such a call still goes to the few-row kernel, whose weights and rows
+// are in flight from the first instruction while the tiled one stages its chunks in turn (bf16, weights from
+// memory, tiled -> here: 640 rows 320 -> 2560 channels 17.0 -> 9.5 us, 1280 -> 3840 36.5 -> 22.4; 2240 rows
+// 1280 -> 1280 37.3 -> 22.7, 320 -> 2560 27.4 -> 22.6; beyond 2048 patches even or slower: 1280 rows
+// 1280 -> 10240 84.9 vs 86.8), unless the tiled kernel's 128 x 128 patches come out as nearly whole rounds of one per compute unit, which then
+// runs at the rate of its MFMA phase (4096 rows 640 -> 1920: 25.3 vs 31.7 us; 2240 rows 640 -> 5120 even).
+// fp32 is left where it was: its patches are bound by the MFMAs and gain or lose by 15 % either way.
+// A pair of calls asks first whether its tiled plans share a launch (shared_beats_few_rows).
+static bool few_rows_alone(const sige_geom* g, const ConvArgs& a, int ks, int nl)
+{
+    if (knob(SIGE_KNOB_CONV_POINTWISE) >= 0 || !pointwise_fits(g, a, ks, nl) || ks != 16) return false;
+    const long rows = (long)nl * g->block_h * g->block_w;
+    const long patches = (rows + 63) / 64 * ((a.Cout + 63) / 64);
+    const long big = (rows + 127) / 128 * ((a.Cout + 127) / 128), whole = (big + 255) / 256 * 256;
+    return patches <= 2048 && big * 100 < whole * 85;
+}
+
+// Shared by sige_conv, sige_conv_scatter and sige_fused_conv: plan and fill the arguments.  *pointwise: the call
+// goes to the few-row kernel, with that patch; otherwise p is its tiled plan, and p->few_rows_alone says that
+// launched by itself it goes to the few-row kernel all the same (64 x 64 patches) ...
 static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int th, int tw, int Cin, int Cout,
                         int max_blocks, int n_blocks, int nl, ConvArgs& a, void* workspace, size_t workspace_bytes,
                         ConvPlan* p, int* pointwise)
@@ -265,9 +279,15 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     *pointwise = pointwise_tiles(g, a, ks, nl);
     if (*pointwise) return SIGE_OK;
     const bool ws_ok = workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-    SIGE_REQUIRE(plan_conv(g, th, tw, Cin, Cout, dtype_size(dt), ks, nl, ws_ok && !a.glu ? workspace_bytes / sizeof(float) : 0,
-                           a.scale != nullptr || a.act != SIGE_ACT_NONE, p),
-                 SIGE_ERR_UNSUPPORTED, "%s: no kernel shape fits block %dx%d, k %d, stride %d, Cin %d", who,
+    const bool planned = plan_conv(g, th, tw, Cin, Cout, dtype_size(dt), ks, nl,
+                                   ws_ok && !a.glu ? workspace_bytes / sizeof(float) : 0,
+                                   a.scale != nullptr || a.act != SIGE_ACT_NONE, p);
+    p->few_rows_alone = few_rows_alone(g, a, ks, nl);
+    if (!planned && p->few_rows_alone) {                    // a block too wide for every tiled shape
+        *pointwise = 2;
+        return SIGE_OK;
+    }
+    SIGE_REQUIRE(planned, SIGE_ERR_UNSUPPORTED, "%s: no kernel shape fits block %dx%d, k %d, stride %d, Cin %d", who,
                  g->block_h, g->block_w, g->k, g->stride, Cin);
     SIGE_REQUIRE(p->groups <= 65535 && p->bands * p->ksplit <= 65535, SIGE_ERR_UNSUPPORTED,
                  "%s: too many blocks per launch", who);
@@ -296,12 +316,53 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     return SIGE_OK;
 }
 
+// A pair that could share a launch, but whose 1x1 call is one that launched by itself goes to the few-row kernel:
+// whether the shared launch is the faster one.  Against it stand two launches of which the 3x3 one, when it stages no
+// arithmetic, requests its chunks ahead (the shared kernel does not) and the 1x1 one streams its K.  The shared
+// launch numbers its tiles per XCD, so what it costs follows the fullest XCD: `rounded` workgroups, as if all were
+// as full.  310 pairs of 320 to 1280 channels on 4x4 to 16x16 blocks, weights from memory, two launches -> shared:
+//   arithmetic staged (Scale+Shift, activation), up to 1664: 640 -> 320 + 320 on 64 8x8 blocks 57.7 -> 46.2 us, 320 -> 320 + 320
+//     40.2 -> 33.8, 960 -> 320 + 320 109 -> 94, 512 -> 160 + 288 32.2 -> 24.8, marked 640 -> 320 + 320 65.6 -> 52.8; beyond, even or
+//     slower: 704 -> 544 + 544 on 51 blocks (1904) 88.2 -> 97.4.  Chunks of four K steps feed a wide shortcut badly:
+//     832 -> 320 + 768 on 9 16x16 blocks 58.2 -> 73.0.
+//   nothing staged, chunks of eight K steps, up to six of them and 1472 workgroups: 512 -> 256 + 256 on 20 16x16 blocks 35.8 -> 31.0,
+//     640 -> 320 + 320 on 64 8x8 41.9 -> 37.6; beyond: 960 -> 320 + 320 (15 chunks of four) 59.1 -> 73.5, 640 -> 512 + 512 on 44
+//     (1536) 43.0 -> 46.9; 320 -> 320 + 320 (five chunks of four) even.
+constexpr long kSharedStaged = 1664, kSharedPlain = 1472;
+static bool shared_beats_few_rows(const ConvArgs& a0, const ConvPlan& p0, const ConvPlan& p1, int ks)
+{
+    const long t0 = (long)p0.groups * p0.bands, t1 = (long)p1.groups * p1.bands;
+    const long rounded = (t0 + 7) / 8 * 8 * p0.slabs + (t1 + 7) / 8 * 8 * p1.slabs;
+    if (a0.scale != nullptr || a0.act != SIGE_ACT_NONE)
+        return rounded <= kSharedStaged && (p0.kc == 8 || 2 * t1 * p1.slabs <= 3 * t0 * p0.slabs);
+    return p0.kc == 8 && a0.Cin / (p0.kc * ks) <= 6 && rounded <= kSharedPlain;
+}
+
+// The order of sums that the few-row kernel has to keep for a call it takes from that tiled plan (see
+// pointwise_kernel): the plan's own where some pair with the call shares its launch.  With chunks of four that
+// order costs up to 6 %, so calls too large for it (three fifths of the workgroups above, by the rule on wide
+// shortcuts) keep the free one.
+static int order_of_sums(const ConvPlan& p)
+{
+    if (p.cfg != 3 || p.ksplit != 1 || knob(SIGE_KNOB_CONV_POINTWISE_W4) == 0) return 0;     // (its kernels have four waves)
+    if (p.kc == 4) return 5L * p.groups * p.bands * p.slabs <= 3 * kSharedStaged ? 4 : 0;
+    return p.kc == 8 ? 8 : 0;
+}
+
 // ... and launch.
 static int launch_prepared(sige_dtype dt, const ConvArgs& a, const ConvPlan& p, int pointwise, int nl, hipStream_t st)
 {
+    // (it may also be the second of a pair that shares its launch, with the tiled shape: the outputs have the same
+    // bits either way, and as separate gather, convolution and scatter)
+    int order = 0;
+    if (!pointwise && p.few_rows_alone) {
+        pointwise = 2;
+        order = order_of_sums(p);
+    }
     if (pointwise)
-        return dt == SIGE_F32 ? launch_pointwise<float>(a, nl, pointwise, st)
-               : dt == SIGE_F16 ? launch_pointwise<f16>(a, nl, pointwise, st) : launch_pointwise<bf16>(a, nl, pointwise, st);
+        return dt == SIGE_F32 ? launch_pointwise<float>(a, nl, pointwise, 0, st)
+               : dt == SIGE_F16 ? launch_pointwise<f16>(a, nl, pointwise, order, st)
+                                : launch_pointwise<bf16>(a, nl, pointwise, order, st);
     int rc = dt == SIGE_F32 ? launch_conv<float>(a, p, st)
              : dt == SIGE_F16 ? launch_conv<f16>(a, p, st) : launch_conv<bf16>(a, p, st);
     if (rc || p.ksplit == 1) return rc;
@@ -313,7 +374,7 @@ static int run_conv(const char* who, sige_dtype dt, const sige_geom* g, int th, 
                     int max_blocks, int n_blocks, int nl, ConvArgs& a, void* workspace, size_t workspace_bytes,
                     void* stream)
 {
-    ConvPlan p;
+    ConvPlan p = {};
     int pointwise = 0;
     if (int rc = prepare_conv(who, dt, g, th, tw, Cin, Cout, max_blocks, n_blocks, nl, a, workspace, workspace_bytes,
                               &p, &pointwise))
@@ -354,13 +415,14 @@ extern "C" int sige_conv_plan(sige_dtype dt, const sige_geom* g, int32_t Cin, in
     ConvArgs a = {};
     a.up = up;
     a.act = staged_math ? SIGE_ACT_SILU : SIGE_ACT_NONE;
-    ConvPlan p;
+    ConvPlan p = {};
     int pointwise = 0;
     // any 16-byte aligned non-null address stands for the workspace: nothing is dereferenced here
     void* ws = workspace_bytes ? reinterpret_cast<void*>(uintptr_t(16)) : nullptr;
     if (int rc = prepare_conv(who, dt, g, th, tw, Cin, Cout, n_blocks, n_blocks, n_blocks, a, ws, workspace_bytes, &p, &pointwise))
         return rc;
     *info = sige_conv_plan_info{};
+    if (!pointwise && p.few_rows_alone) pointwise = 2;
     if (pointwise) {
         const long rows = (long)n_blocks * g->block_h * g->block_w;
         const int BM = pointwise == 3 ? 32 : 64, BN = pointwise == 2 ? 64 : 32;
@@ -557,7 +619,7 @@ static int fused_pair(const char* who, const sige_fused_conv_call* first, const 
     SIGE_REQUIRE(first && second, SIGE_ERR_INVALID_ARG, "%s: two calls are required", who);
     const sige_fused_conv_call* c[2] = {first, second};
     ConvArgs a[2];
-    ConvPlan p[2];
+    ConvPlan p[2] = {};
     int th[2], tw[2], nl[2], pw[2] = {0, 0};
     long nb[2] = {0, 0};
     if (marks != nullptr) {
@@ -599,7 +661,8 @@ static int fused_pair(const char* who, const sige_fused_conv_call* first, const 
     const long pair_max = pair_knob >= 0 ? pair_knob : (1L << 30);
     const bool together = nl[0] > 0 && nl[1] > 0 && wgs_both <= pair_max && !pw[0] && !pw[1] && c[0]->dt == c[1]->dt && a[0].k == 3 &&
                           a[1].k == 1 && p[0].cfg == 3 && p[1].cfg == 3 && p[0].ksplit == 1 && p[1].ksplit == 1 &&
-                          p[0].kc == p[1].kc && (p[0].kc == 8 || p[0].kc == 4);
+                          p[0].kc == p[1].kc && (p[0].kc == 8 || p[0].kc == 4) &&
+                          (!p[1].few_rows_alone || shared_beats_few_rows(a[0], p[0], p[1], c[0]->dt == SIGE_F32 ? 8 : 16));
     bool scan = false;
     if (marks != nullptr) {
         // the one-launch kernel builds the lists itself when a workgroup can scan a whole block grid

@@ -1039,13 +1039,20 @@ __global__ __launch_bounds__(256) void conv_reduce_kernel(ConvArgs a, long n_run
 // covers 16 rows, one request per row).  That is not the MFMA operand layout, so each pair of steps
 // passes through a buffer in LDS that belongs to the wave alone: written as loaded, read back as
 // operands, no workgroup barrier involved.
-template <typename T, int W, int P, int TM, int TN>
+//
+// ORDER: in which order K is summed.  0: a run of neighbouring steps per wave.  8 or 4: as the tiled kernel's 64 x 32
+// shape sums chunks of that many K steps (wave w takes steps 2w and 2w + 1, or step w, of every chunk, the bias goes
+// into the first wave's sum), so that a call has the same bits launched by itself, here, as inside a shared
+// launch (conv_pair_kernel).  With 8 a wave still loads what it multiplies.  With 4 that would be half rows, two
+// requests for 64 bytes (15 - 30 % slower): the waves load 64 bytes of a row each, as with 8, into one buffer, and take
+// their steps from there, one barrier per pair of chunks.
+template <typename T, int W, int P, int TM, int TN, int ORDER = 0>
 __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvArgs a)
 {
     constexpr int KS = Mma<T>::KSTEP, S = (int)sizeof(T), N = Vec16<T>::N;
     constexpr int BM = 32 * TM, BN = 32 * TN, RS = BN + 4;
     constexpr int NI = BM / 16;                               // load instructions per pair of K steps: 16 rows each
-    constexpr int AROW = 80;                                  // bytes per row in the wave's buffer: 64 + pad
+    constexpr int AROW = ORDER == 4 ? 272 : 80;               // bytes per row in the wave's buffer: 64 + pad; in the common one 4 * 64 + pad
     constexpr int ABUF = BM * AROW;                           // one pair of K steps of the patch rows
     static_assert(2 * KS * S == 64, "two K steps of one row are 64 bytes");
     extern __shared__ uint4 lds4[];
@@ -1065,7 +1072,15 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
     const bool gathered = a.x != nullptr;                     // rows come from x at the blocks' pixels
     const bool have_org = a.indices != nullptr;               // needed by the gather and by the scatter epilogue
     const int kcs = a.Cin / KS, np = kcs / 2;                 // K steps, pairs of K steps
-    const int q0 = wave * np / W, q1 = (wave + 1) * np / W;   // this wave's pairs
+    // this wave's pairs of steps: q0 .. q1 - 1, or (ORDER) every fourth one, the first of them number `wave`; pair q of
+    // the rows is what the wave loads, pair q of the weights what it multiplies (the same unless ORDER is 4, where an
+    // odd number of chunks leaves the last pair without its second step)
+    static_assert(ORDER == 0 || (W == 4 && TM == 2 && (ORDER == 8 || ORDER == 4)), "the order of the shape whose four waves split K");
+    const int q0 = ORDER ? 0 : wave * np / W, q1 = ORDER == 8 ? np / 4 : ORDER == 4 ? (np + 3) / 4 : (wave + 1) * np / W;
+    auto row_pair = [&](int q) { return ORDER ? 4 * q + wave : q; };
+    auto row_live = [&](int q) { return ORDER == 4 ? 4 * q + wave < np : q < q1; };
+    auto w_step = [&](int q) { return ORDER == 4 ? 8 * q + wave : 2 * row_pair(q); };
+    auto w_second = [&](int q) { return ORDER == 4 ? (8 * q + 4 < kcs ? 4 * 64 : 0) : q < q1 ? 64 : 0; };
     const int ntn_total = (a.Cout + 31) / 32;
 
     // The weight fragments do not depend on the block list: their first loads go out before it is
@@ -1080,9 +1095,9 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
     auto fetch_b = [&](int st, int q) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
-            const u32x4* src = q < q1 ? wp[tn] + (long)(2 * q) * 64 : idle;
+            const u32x4* src = q < q1 ? wp[tn] + (long)w_step(q) * 64 : idle;
             rb[st][tn][0] = src[0];
-            rb[st][tn][1] = src[q < q1 ? 64 : 0];
+            rb[st][tn][1] = src[w_second(q)];
         }
     };
 #pragma unroll
@@ -1141,7 +1156,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
     auto fetch_a = [&](int st, int q) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            ra[st][i] = *(q < q1 ? (const u32x4*)(rp[i] + (long)q * 64) : idle);
+            ra[st][i] = *(row_live(q) ? (const u32x4*)(rp[i] + (long)row_pair(q) * 64) : idle);
     };
 #pragma unroll
     for (int st = 0; st < P; ++st) fetch_a(st, q0 + st);
@@ -1185,25 +1200,28 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[tm][tn][r] = 0.0f;
 
-    char* const abuf = lds + wave * (2 * ABUF);               // two buffers, used in turn
-    const int a_wr = (lane >> 2) * AROW + (lane & 3) * 16;    // + 16 * i rows
-    const int a_rd = l32 * AROW + half * 16;                  // + 32 * tm rows, + 32 bytes per step
+    char* const abuf = lds + (ORDER == 4 ? 0 : wave * (2 * ABUF));   // two buffers, used in turn
+    const int a_wr = (lane >> 2) * AROW + (lane & 3) * 16 + (ORDER == 4 ? wave * 64 : 0);     // + 16 * i rows
+    const int a_rd = l32 * AROW + half * 16 + (ORDER == 4 ? wave * 32 : 0);   // + 32 * tm rows, + A2 to the second step
+    constexpr int A2 = ORDER == 4 ? 128 : 32;
     for (int q = q0; q < q1; q += P) {
 #pragma unroll
         for (int st = 0; st < P; ++st) {
             {
                 // no branch in the loop body: a stage past the wave's share multiplies zero rows, and the
                 // number of loads in flight at every wait is known at compile time
-                const bool live = q + st < q1;
+                const bool live = row_live(q + st);
                 const u32x4 zero = {0u, 0u, 0u, 0u};
-                char* const buf = abuf + (st & 1) * ABUF;
+                char* const buf = abuf + ((ORDER == 4 ? q + st : st) & 1) * ABUF;
 #pragma unroll
                 for (int i = 0; i < NI; ++i) *(u32x4*)(buf + 16 * i * AROW + a_wr) = live ? ra[st][i] : zero;
-                __builtin_amdgcn_wave_barrier();
+                // (a buffer is written again two stages later, behind the next stage's barrier and so behind all reads)
+                if constexpr (ORDER == 4) __syncthreads();
+                else __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm) {
                     const uint4 f0 = *(const uint4*)(buf + 32 * tm * AROW + a_rd);
-                    const uint4 f1 = *(const uint4*)(buf + 32 * tm * AROW + a_rd + 32);
+                    const uint4 f1 = *(const uint4*)(buf + 32 * tm * AROW + a_rd + A2);
 #pragma unroll
                     for (int tn = 0; tn < TN; ++tn) {
                         const u32x4 b0 = rb[st][tn][0], b1 = rb[st][tn][1];
@@ -1301,6 +1319,10 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
             for (int i = 0; i < N; ++i) bv[i] = 0.0f;
             load_bias<N>(a, o, bv);
         }
+        if constexpr (ORDER != 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] = bv[i];
+        }
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const float4* src = (const float4*)(red + (w * BM + m) * RS + nn);
@@ -1310,8 +1332,10 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
                 v[4 * i] += q.x; v[4 * i + 1] += q.y; v[4 * i + 2] += q.z; v[4 * i + 3] += q.w;
             }
         }
+        if constexpr (ORDER == 0) {
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] += bv[i];
+            for (int i = 0; i < N; ++i) v[i] += bv[i];
+        }
         emit_run<T>(a, to_y, vec_ok, t, pix, o, v, ap, early_ok, early_t, early_f);
     }
 }
@@ -1322,6 +1346,7 @@ struct ConvPlan {
     int G, rows, trows, Cc, ps, bands, slabs, groups;
     int ksplit;   // workgroups that share one output patch along K (1 = no split)
     bool pipe;    // the 64 x 32 shape with chunks requested ahead (see conv_body)
+    bool few_rows_alone;   // a 1x1 call: launched by itself it goes to pointwise_kernel, 64 x 64 patches (see conv.hip)
     size_t lds;
 };
 
@@ -1399,10 +1424,10 @@ int launch_conv(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
 }
 
 
-template <typename T, int W, int P, int TM, int TN>
+template <typename T, int W, int P, int TM, int TN, int ORDER = 0>
 int launch_pointwise_as(const ConvArgs& a, int nl, hipStream_t st)
 {
-    auto kern = pointwise_kernel<T, W, P, TM, TN>;
+    auto kern = pointwise_kernel<T, W, P, TM, TN, ORDER>;
     constexpr int BM = 32 * TM;
     const size_t lds = std::max((size_t)W * BM * (32 * TN + 4) * sizeof(float), (size_t)W * 2 * BM * 80);
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1414,9 +1439,14 @@ int launch_pointwise_as(const ConvArgs& a, int nl, hipStream_t st)
     return SIGE_OK;
 }
 
+// order: 64 x 64 patches of a half type, summed as the tiled kernel's 64 x 32 shape sums chunks of that many K steps
 template <typename T>
-int launch_pointwise(const ConvArgs& a, int nl, int tiles, hipStream_t st)
+int launch_pointwise(const ConvArgs& a, int nl, int tiles, int order, hipStream_t st)
 {
+    if constexpr (sizeof(T) == 2) {
+        if (order == 8) return launch_pointwise_as<T, 4, 3, 2, 2, 8>(a, nl, st);
+        if (order == 4) return launch_pointwise_as<T, 4, 3, 2, 2, 4>(a, nl, st);
+    }
     if (tiles == 3) return launch_pointwise_as<T, 8, 6, 1, 1>(a, nl, st);
     if (tiles == 2) {
         // more 64 x 64 patches than compute units: four waves per workgroup, so that two workgroups
@@ -1477,7 +1507,7 @@ int launch_pack(const void* w_oihw, int Cout, int Cin, int k, long n, void* pack
 // The launchers one translation unit per storage type instantiates.
 #define SIGE_CONV_LAUNCHERS(KW, T)                                                                              \
     KW template int launch_conv<T>(const ConvArgs&, const ConvPlan&, hipStream_t);                              \
-    KW template int launch_pointwise<T>(const ConvArgs&, int, int, hipStream_t);                                \
+    KW template int launch_pointwise<T>(const ConvArgs&, int, int, int, hipStream_t);                           \
     KW template int launch_reduce<T>(const ConvArgs&, int, hipStream_t);                                        \
     KW template int launch_pair<T>(const ConvArgs&, const ConvPlan&, const ConvArgs&, const ConvPlan&, bool, \
                                    hipStream_t);                                                            \

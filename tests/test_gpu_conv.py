@@ -2,6 +2,8 @@
 element.  Masks, block lists and pure copies bit-exact; floating results within
 1e-4 (fp32) / 1e-2 (fp16, bf16) of the oracle, relative to max(|ref|, rms(ref))."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -1000,6 +1002,96 @@ def test_fused_conv_pair(oracle, dtype, Cin, C3, C1, res, b, n):
     c1.Cin = Cin + 1                        # argument errors of either call are reported
     with pytest.raises(api.SigeError):
         api.sige_fused_conv_pair(c3, c1)
+
+
+def kernel_launches(fn):
+    """How many kernels a call enqueues: the nodes of a graph it is captured into."""
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        fn()
+    n = ctypes.c_size_t(0)
+    rc = ctypes.CDLL(api.LIB_PATH).hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n))
+    assert rc == 0
+    return n.value
+
+
+@pytest.mark.parametrize("dtype,Cin,C3,C1,b,n,staged,launches", [
+    ("bf16", 384, 1056, 2112, 8, 8, True, 1),     # 264 patches of 64 x 64 in the shortcut, chunks of eight K steps
+    ("f16", 384, 1056, 2112, 8, 8, False, 1),
+    ("f16", 320, 1408, 2112, 8, 8, True, 1),      # five chunks of four K steps
+    ("bf16", 320, 1408, 2112, 8, 8, False, 2),    # nothing staged and chunks of four: two launches are faster
+    ("bf16", 320, 1056, 2112, 8, 8, True, 2),     # a shortcut twice as wide as the 3x3 call, chunks of four
+    ("f16", 384, 1504, 1504, 16, 4, False, 2),    # 1504 workgroups: beyond the rule for calls that stage nothing
+    ("f16", 384, 1504, 1504, 16, 4, True, 1),     # ... within it for calls that do
+    ("bf16", 384, 1696, 1696, 5, 31, True, 2),    # 1696 counted per XCD: beyond both; two ragged blocks per workgroup
+])
+def test_fused_conv_pair_wide_shortcut(oracle, dtype, Cin, C3, C1, b, n, staged, launches):
+    """Pairs whose 1x1 call has more 64 x 64 patches than compute units, so that launched by itself it goes to
+    the few-row kernel: they share one launch (and, marked, build their lists in it) where that is the faster
+    way, and the outputs have the bits of the two separate calls either way."""
+    rng = np.random.default_rng(Cin + C3 + C1 + n)
+    td = DT[dtype]
+    res = 60
+    x = torch.from_numpy(rng.standard_normal((res, res, Cin)).astype(np.float32)).to(td)
+    w3, b3 = inputs.conv_params(rng, C3, Cin, 3, td)
+    w1, b1 = inputs.conv_params(rng, C1, Cin, 1, td)
+    scale = torch.from_numpy(rng.uniform(0.5, 1.5, Cin).astype(np.float32)) if staged else None
+    shift = torch.from_numpy(rng.uniform(-0.5, 0.5, Cin).astype(np.float32)) if staged else None
+    kw = dict(scale=dev(scale), shift=dev(shift), act=api.ACT_SILU) if staged else {}
+    conv3, conv1 = SigeConv(dev(w3), b3, res, res, b, 1, 1), SigeConv(dev(w1), b1, res, res, b, 1, 0)
+    every = BlockList(conv3.g, "cuda").all_active().indices
+    pick = np.sort(np.append(rng.permutation(len(every) - 1)[:n - 1], len(every) - 1))     # the ragged last block among them
+    idx = every[torch.from_numpy(pick).cuda()]
+    lists = [BlockList(c.g, "cuda", max_blocks=n) for c in (conv3, conv1)]
+    for bl in lists:
+        bl.indices.copy_(idx)
+        bl.count.fill_(n)
+        bl.n_host = n
+    ws = Workspace("cuda")
+    xd = dev(x)
+    assert api.sige_conv_plan(td, conv1.g, Cin, C1, n).kernel == 1
+    ya = torch.zeros((res, res, C3), dtype=td, device="cuda")
+    conv3.forward(xd, ya, lists[0], ws, fused=True, **kw)
+    tb = conv1.forward(xd, None, lists[1], ws, scatter=False, tag="alone", fused=True).clone()
+    y3 = torch.zeros_like(ya)
+    c3, _ = conv3.fused_call(xd, y3, lists[0], ws, tag="p3", **kw)
+    c1, t1 = conv1.fused_call(xd, None, lists[1], ws, scatter=False, tag="p1")
+    t1.fill_(7.0)
+    assert kernel_launches(lambda: api.sige_fused_conv_pair(c3, c1)) == launches
+    api.sige_fused_conv_pair(c3, c1)
+    torch.cuda.synchronize()
+    assert torch.equal(y3, ya) and torch.equal(t1, tb), "pair differs from the two calls"
+    # the same pair on marked lists: the one launch builds the lists, otherwise the compaction pass runs first
+    # (8x8 blocks and larger: one marked pixel inside a block then activates that block alone)
+    if b >= 8:
+        mask = torch.zeros((res, res), dtype=torch.uint8, device="cuda")
+        for yy, xx in idx.tolist():
+            mask[yy + 2, xx + 2] = 1
+        got = [BlockList(c.g, "cuda", max_blocks=n) for c in (conv3, conv1)]
+        BlockList.mark_together(got, mask_in=mask)
+        y3m = torch.zeros_like(ya)
+        m3, _ = conv3.fused_call(xd, y3m, got[0], ws, tag="p3", **kw)
+        m1, t1m = conv1.fused_call(xd, None, got[1], ws, scatter=False, tag="m1")
+        t1m.fill_(7.0)
+        descs = [bl.desc() for bl in got]
+        assert kernel_launches(lambda: api.sige_fused_conv_pair_marked(m3, m1, descs)) == (1 if launches == 1 else 3)
+        api.sige_fused_conv_pair_marked(m3, m1, descs)
+        torch.cuda.synchronize()
+        for bl in got:
+            assert int(bl.count.item()) == n and torch.equal(bl.indices, idx)
+        assert torch.equal(y3m, ya) and torch.equal(t1m, tb), "marked pair"
+    # first and last block against the oracle
+    pad = np.zeros((res + 2, res + 2, Cin))
+    pad[1:-1, 1:-1] = oracle.scale_shift_act(f64(x), f64(scale), f64(shift), oracle.ACT_SILU) if staged else f64(x)
+    if staged:
+        pad = round_to(pad, td)                # the activated tile is stored in td on its way to the matrix cores
+    for i in (0, n - 1):
+        yy, xx = idx[i].tolist()
+        hh, ww = min(b, res - yy), min(b, res - xx)
+        want = oracle.conv2d(pad[yy:yy + hh + 2, xx:xx + ww + 2].copy(), f64(w3), f64(b3), 1, 0)
+        assert_close(y3[yy:yy + hh, xx:xx + ww], want, td, f"3x3, block {i}")
+        want = oracle.conv2d(f64(x)[yy:yy + hh, xx:xx + ww].copy(), f64(w1), f64(b1), 1, 0)
+        assert_close(t1.view(n, b, b, C1)[i, :hh, :ww], want, td, f"1x1, block {i}")
 
 
 @pytest.mark.parametrize("dtype,Cin,C3,C1,res,b,frac", [

@@ -251,17 +251,33 @@ static int pointwise_tiles(const sige_geom* g, const ConvArgs& a, int ks, int nl
 // are in flight from the first instruction while the tiled one stages its chunks in turn (bf16, weights from
 // memory, tiled -> here: 640 rows 320 -> 2560 channels 17.0 -> 9.5 us, 1280 -> 3840 36.5 -> 22.4; 2240 rows
 // 1280 -> 1280 37.3 -> 22.7, 320 -> 2560 27.4 -> 22.6; beyond 2048 patches even or slower: 1280 rows
-// 1280 -> 10240 84.9 vs 86.8), unless the tiled kernel's 128 x 128 patches come out as nearly whole rounds of one per compute unit, which then
-// runs at the rate of its MFMA phase (4096 rows 640 -> 1920: 25.3 vs 31.7 us; 2240 rows 640 -> 5120 even).
+// 1280 -> 10240 84.9 vs 86.8), unless the plan p that the tiled kernel would use is one it runs well.  200 calls of
+// 512 to 100000 rows and 32 to 5000 channels, tiles to tiles / gathered and scattered with a residual and a copy:
+//   chunks of one or three K steps: never (480 -> 80 on 8448 rows 1.4 / 1.2 times the few-row time, 608 -> 176 on 42880 4.2 / 2.4),
+//     except 128 x 128 patches with chunks of three in a whole round (1056 -> 2176 on 3776 rows even);
+//   128 x 128 in nearly whole rounds of two workgroups per compute unit: always (640 -> 1920 on 4096 rows 25.3 vs 31.7 us);
+//   128 x 64 in such rounds: with up to ten chunks (320 -> 320 on 11008 rows 15.7 / 20.1 vs 15.7 / 23.2, 768 -> 176 on 39360 45.4 /
+//     53.4 vs 44.2 / 59.9; 832 -> 720 on 4544, 13 chunks of four, 1.14 times);  64 x 64: up to seven (512 -> 128 on 16384 12.1 / 14.5
+//     vs 12.5 / 16.4; a round and a half of 1280 -> 640 on 4096 36.1 / 37.4 vs 24.3 / 30.1);
+//   64 x 32: where less than 0.7 of this kernel's 64 channels is used, few chunks and up to two rounds (512 -> 32 on 19520
+//     rows 9.3 / 10.4 vs 11.2 / 14.0, 320 -> 32 on 21568 11.9 / 10.2 vs 11.2 / 11.8; 960 -> 32 on 20480 22.3 / 23.7 vs 15.9 / 18.1,
+//     640 -> 48 on 16448 1.6 / 1.4 times).
 // fp32 is left where it was: its patches are bound by the MFMAs and gain or lose by 15 % either way.
 // A pair of calls asks first whether its tiled plans share a launch (shared_beats_few_rows).
-static bool few_rows_alone(const sige_geom* g, const ConvArgs& a, int ks, int nl)
+static bool few_rows_alone(const sige_geom* g, const ConvArgs& a, int ks, int nl, const ConvPlan* p)
 {
     if (knob(SIGE_KNOB_CONV_POINTWISE) >= 0 || !pointwise_fits(g, a, ks, nl) || ks != 16) return false;
-    const long rows = (long)nl * g->block_h * g->block_w;
-    const long patches = (rows + 63) / 64 * ((a.Cout + 63) / 64);
-    const long big = (rows + 127) / 128 * ((a.Cout + 127) / 128), whole = (big + 255) / 256 * 256;
-    return patches <= 2048 && big * 100 < whole * 85;
+    const long rows = (long)nl * g->block_h * g->block_w, nt2 = (a.Cout + 63) / 64;
+    if ((rows + 63) / 64 * nt2 > 2048) return false;
+    if (p == nullptr) return true;                          // a block too wide for every tiled shape
+    const long w = (long)p->groups * p->bands * p->slabs, whole = (w + 511) / 512 * 512;
+    const bool full = w * 100 >= whole * 79;
+    const int nch = a.Cin / (p->kc * ks);
+    if (p->kc == 1) return true;
+    if (p->cfg == 0) return !full;
+    if (p->kc < 4) return true;
+    if (p->cfg == 3) return a.Cout * 10L >= nt2 * 64 * 7 || nch > 5 || w > 1024;
+    return !full || nch > (p->cfg == 1 ? 10 : 7);
 }
 
 // Shared by sige_conv, sige_conv_scatter and sige_fused_conv: plan and fill the arguments.  *pointwise: the call
@@ -282,8 +298,8 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     const bool planned = plan_conv(g, th, tw, Cin, Cout, dtype_size(dt), ks, nl,
                                    ws_ok && !a.glu ? workspace_bytes / sizeof(float) : 0,
                                    a.scale != nullptr || a.act != SIGE_ACT_NONE, p);
-    p->few_rows_alone = few_rows_alone(g, a, ks, nl);
-    if (!planned && p->few_rows_alone) {                    // a block too wide for every tiled shape
+    p->few_rows_alone = few_rows_alone(g, a, ks, nl, planned ? p : nullptr);
+    if (!planned && p->few_rows_alone) {
         *pointwise = 2;
         return SIGE_OK;
     }

@@ -259,6 +259,32 @@ def test_conv_plans_respect_the_lds_of_a_compute_unit(L):
         api.sige_conv_plan(f16, g3, 128, 128, 0)
 
 
+@pytest.mark.parametrize("Cin,Cout,rows,few", [
+    # (Cin, Cout, rows in 8x8 blocks, the few-row kernel?) with more 64 x 64 patches than compute units, half types
+    (320, 32, 21568, False), (640, 32, 40960, False), (384, 32, 19200, False), (512, 32, 19520, False),   # half of its 64 channels used
+    (512, 80, 18560, False),
+    (960, 32, 20480, True), (320, 32, 102400, True), (640, 48, 16448, True), (640, 96, 51200, True),
+    (320, 160, 16384, True), (640, 160, 16384, True),      # 128 x 128 patches would fill a round; the plan is 64 x 32
+    (512, 128, 16384, False), (896, 304, 6464, False),     # 64 x 64 in one whole round, four and seven chunks
+    (1280, 640, 4096, True), (640, 320, 8192, True),       # ... in one and a quarter
+    (320, 320, 11008, False), (640, 720, 8640, False), (768, 176, 39360, False), (1280, 160, 41216, False),   # 128 x 64, whole rounds
+    (832, 720, 4544, True), (320, 320, 16384, True),       # 13 chunks; a round and a quarter
+    (640, 1920, 4096, False), (320, 256, 32768, False),    # 128 x 128
+    (608, 32, 58304, True), (736, 288, 10176, True), (480, 80, 8448, True),     # chunks of one or three K steps
+])
+def test_few_row_rule_follows_the_tiled_plan(L, Cin, Cout, rows, few):
+    """Which 1x1 calls beyond one 64 x 64 patch per compute unit go to the few-row kernel: decided from the plan
+    that the tiled kernel would use (the side measured faster for each of these)."""
+    import torch
+    g = api.geom(512, 512, 8, 1, 1, 0)
+    for td in (torch.float16, torch.bfloat16):
+        p = api.sige_conv_plan(td, g, Cin, Cout, rows // 64, workspace_bytes=1 << 30)
+        assert p.kernel == int(few), (Cin, Cout, rows, p)
+    # a block wider than every tiled shape's patch has the few-row kernel only
+    wide = api.geom(8, 512, (8, 512), 1, 1, 0)
+    assert api.sige_conv_plan(torch.float16, wide, 320, 320, 2).kernel == 1
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(api, "_lib", None)
     monkeypatch.setattr(api, "LIB_PATH", str(tmp_path / "missing.so"))

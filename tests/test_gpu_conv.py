@@ -1417,3 +1417,63 @@ def test_few_row_kernel_tiles_of_ragged_blocks(oracle, dtype, Cin, Cout, b, kern
     want = oracle.conv2d(f64(x), f64(w), f64(bias), 1, 0)
     y0, x0 = bl.indices[0].tolist()
     assert_close(got[0], want[:b, :b], td, "first block")
+
+
+@pytest.mark.parametrize("dtype,Cin,Cout,b,n", [
+    ("bf16", 384, 2112, 8, 8),      # sums in the order of chunks of eight K steps
+    ("f16", 320, 2112, 8, 8),       # ... of four, an odd number of chunks
+    ("f16", 352, 2080, 5, 22),      # in its own order; ragged rows and channels
+])
+def test_few_row_kernel_forms_beyond_the_compute_units(oracle, dtype, Cin, Cout, b, n):
+    """1x1 calls with more 64 x 64 patches than compute units in every form that reaches the few-row kernel - gathered
+    and scattered with a residual and an activated copy, tiles scattered, gated GELU - against the oracle, and the
+    fused call against the three in sequence bit for bit."""
+    rng = np.random.default_rng(Cin + Cout)
+    td = DT[dtype]
+    H, W = 43, 46                            # no multiple of the blocks
+    x = torch.from_numpy(rng.standard_normal((H, W, Cin + 32)).astype(np.float32)).to(td)
+    w, bias = inputs.conv_params(rng, Cout, Cin, 1, td)
+    conv = SigeConv(dev(w), bias, H, W, b, 1, 0)
+    g = conv.g
+    every = BlockList(g, "cuda").all_active().indices
+    pick = np.sort(np.append(rng.permutation(len(every) - 1)[:n - 1], len(every) - 1))
+    bl = BlockList(g, "cuda", max_blocks=n)
+    bl.indices.copy_(every[torch.from_numpy(pick).cuda()])
+    bl.count.fill_(n)
+    bl.n_host = n
+    blocks = bl.indices.cpu().numpy()
+    assert api.sige_conv_plan(td, g, Cin, Cout, n).kernel == 1
+    assert api.sige_conv_plan(td, g, Cin, Cout, n).shape == 2 and -(-n * b * b // 64) * -(-Cout // 64) > 256
+    cache = torch.from_numpy(rng.standard_normal((H, W, Cout)).astype(np.float32)).to(td)
+    resid = torch.from_numpy(rng.standard_normal((H, W, Cout)).astype(np.float32)).to(td)
+    sc, sh = (torch.from_numpy(rng.uniform(0.5, 1.5, Cout).astype(np.float32)) for _ in range(2))
+    xd = dev(x)[:, :, 16:16 + Cin]           # a channel slice of a wider tensor
+    xs = f64(x)[:, :, 16:16 + Cin].copy()
+    dense = oracle.conv2d(xs, f64(w), f64(bias), 1, 0)
+    ws = Workspace("cuda")
+    # gathered and scattered, with a residual and an activated copy
+    y, copy = dev(cache).clone(), torch.full((H, W, Cout), 3.0, dtype=td, device="cuda")
+    scd, shd = dev(sc), dev(sh)
+    conv.forward(xd, y, bl, ws, fused=True, residual=dev(resid),
+                 act_outs=api.act_out_array([(copy, scd, shd, api.ACT_SILU)]))
+    assert_close(y, oracle.select_blocks(dense + f64(resid), f64(cache), blocks, b, b), td, "gathered and scattered")
+    want = oracle.scale_shift_act(f64(y), f64(sc), f64(sh), oracle.ACT_SILU)
+    assert_close(copy, oracle.select_blocks(want, np.full((H, W, Cout), 3.0), blocks, b, b), td, "activated copy")
+    # the fused call, the three calls and tiles scattered by the convolution: the same bits
+    y1, y3, y2 = (dev(cache).clone() for _ in range(3))
+    conv.forward(xd, y1, bl, ws, fused=True)
+    conv.forward(xd, y3, bl, ws, fused=False)
+    tiles = torch.zeros((n, b, b, Cin), dtype=td, device="cuda")
+    api.sige_gather(xd, g, bl.indices, bl.count, tiles, n_blocks=n, C=Cin, max_blocks=n)
+    api.sige_conv_scatter(tiles, g, bl.indices, bl.count, Cin, Cout, conv.packed, conv.bias, y2, n_blocks=n, max_blocks=n)
+    assert torch.equal(y1, y3) and torch.equal(y1, y2)
+    assert_close(y1, oracle.select_blocks(dense, f64(cache), blocks, b, b), td, "scattered")
+    # gated GELU: values and gates from one convolution, Cout / 2 channels out
+    if Cout % 16 == 0:
+        rows = api.geglu_rows(Cout // 2)
+        packed, gb = api.sige_pack_weight(dev(w[rows])), dev(bias[rows].float())
+        out = torch.full((n + 1, b, b, Cout // 2), 5.0, dtype=td, device="cuda")
+        api.sige_conv_geglu(tiles, g, Cin, Cout // 2, packed, gb, bl.count, out, n_blocks=n, max_blocks=n)
+        full = oracle.conv2d(f64(tiles).reshape(n * b, b, Cin), f64(w), f64(bias), 1, 0).reshape(n, b, b, Cout)
+        assert_close(out[:n], oracle.geglu(full.reshape(-1, Cout)).reshape(n, b, b, Cout // 2), td, "gated GELU")
+        assert (out[n:] == 5.0).all()

@@ -318,12 +318,17 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     // step (measured + 2 - 4 % at 512 x 512 and 1024 x 1024 with 128 channels; with a single round it only costs,
     // and so it does on a 1x1 call, whose two rounds are memory traffic from start to end: 30 -> 32.5 us)
     a.stagger = (p->cfg == 0 && g->k >= 3 && (long)p->groups * p->bands * p->slabs * p->ksplit >= 1024) ? 1 : 0;
-    // Chunks requested ahead: the 64 x 32 shape on a 3x3 call whose workgroups walk through two chunks or more,
-    // nothing to compute on the way in (Scale+Shift would have to be kept per chunk) and a tile that is one
-    // batch of vectors for the 256 threads (a pixel of a chunk is 2 * kc vectors).  One chunk has nothing to hide.
+    // Chunks requested ahead: the 64 x 32 shape on a 3x3 call some of whose workgroups walk through two chunks or
+    // more, nothing to compute on the way in (Scale+Shift would have to be kept per chunk) and a tile that is one
+    // batch of vectors for the 256 threads (a pixel of a chunk is 2 * kc vectors).  Where every workgroup has one
+    // chunk there is nothing to hide; shares of one and two still gain (bf16 960 -> 640 on one 8x8 block, 15 chunks in
+    // ten shares: 14.5 -> 13.9 us).
     const long pipe_vectors = (long)p->G * p->trows * tw * 2 * p->kc;
     p->pipe = p->cfg == 3 && g->k == 3 && (p->kc == 4 || p->kc == 8) && a.scale == nullptr && a.act == SIGE_ACT_NONE &&
               pipe_vectors <= 256L * kPipeVectors && Cin / (p->kc * ks) > p->ksplit;
+    const int ahead = knob(SIGE_KNOB_CONV_AHEAD);           // 0 = never, 1 = refuse what cannot
+    SIGE_REQUIRE(ahead < 1 || p->pipe, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
+    p->pipe = p->pipe && ahead != 0;
     a.d_pb = fast_div(p->rows * g->block_w);
     a.d_per = fast_div(p->trows * tw);
     a.d_tw = fast_div(tw);

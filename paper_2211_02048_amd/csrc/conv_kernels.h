@@ -648,7 +648,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         // network step and every kilobyte of code is fetched first)
         if constexpr (SWAP) stage(ch0);
         start_accumulators();
-        // PIPE.  A workgroup of this shape is bound by round trips: with two or more chunks each cost a
+        // PIPE.  A workgroup of this shape is bound by round trips: of two or more chunks each cost a
         // staging round trip (1.7 us from memory) before its 0.9 us of MFMA steps, nothing of the next
         // chunk in flight meanwhile.  Here the whole tile is one batch of U vectors per thread (the host
         // checks that it fits), whose source addresses differ from chunk to chunk by a constant: they are
@@ -659,8 +659,8 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         // walk waiting for weights (0.8 us a round trip, three of them per chunk of 18 steps), eighteen were
         // slower again where two workgroups share a compute unit (20.3 -> 22.0 us on 320 workgroups of five chunks).
         // Measured, weights from memory, before -> now: bf16 1920 -> 640 channels on 11 8x8 blocks (15 chunks)
-        // 46.6 -> 34.2 us, 960 -> 320 on 25 blocks (15 chunks of 64) 40.2 -> 23.6, 1280 -> 1280 on one block (two
-        // chunks a workgroup) 12.5 -> 12.0; f16 256 -> 256 at 64x64 (two chunks) 9.9 -> 9.6.
+        // 46.6 -> 34.2 us, 960 -> 320 on 25 blocks (15 chunks of 64) 40.2 -> 23.6, 1280 -> 1280 on one block (five shares of
+        // two chunks, with the second kernel) even; f16 256 -> 256 at 64x64 (two chunks) 9.9 -> 9.6.
         const char* src[PIPE ? U : 1];
         uint4 nextv[PIPE ? U : 1];
         unsigned inside = 0u;
@@ -694,7 +694,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
             fill_ring();
         }
         for (int chunk = ch0; chunk < ch1; ++chunk) {
-            long ahead = 0;                                   // bytes to the chunk requested next (the last one again at the end)
+            long ahead = 0;                                   // bytes to the chunk requested next (the last one again at the end: no branch between the steps)
             if constexpr (PIPE) {
                 if (chunk != ch0) __syncthreads();
 #pragma unroll

@@ -1309,25 +1309,32 @@ def test_recorded_calls_repeat_the_step():
         calls.run()
 
 
-@pytest.mark.parametrize("dtype,Cin,Cout,H,W,b,stored,kn", [
-    ("bf16", 384, 72, 24, 24, 8, False, {}),                             # three chunks of 128, 10 x 10 tiles
-    ("f16", 256, 40, 37, 50, 16, False, {}),                             # two chunks, row bands, ragged edges and channels
-    ("bf16", 256, 64, 21, 19, 4, False, dict(CONV_KC=4)),    # four blocks per workgroup, chunks of 64
-    ("f16", 640, 64, 16, 16, 8, False, dict(CONV_KC=8, CONV_SPLIT=2)),   # shares of two and three chunks
-    ("f32", 192, 40, 20, 20, 6, False, dict(CONV_KC=8)),
-    ("bf16", 384, 64, 24, 24, 8, True, {}),                              # stored tiles
+@pytest.mark.parametrize("dtype,Cin,Cout,H,W,b,form,kn", [
+    ("bf16", 384, 72, 24, 24, 8, "", {}),                                # three chunks of 128, 10 x 10 tiles
+    ("f16", 256, 40, 37, 50, 16, "", {}),                                # two chunks, row bands, ragged edges and channels
+    ("bf16", 256, 64, 21, 19, 4, "", dict(CONV_KC=4)),       # four blocks per workgroup, chunks of 64
+    ("f16", 640, 64, 16, 16, 8, "", dict(CONV_KC=8, CONV_SPLIT=2)),      # shares of two and three chunks
+    ("bf16", 960, 64, 16, 16, 8, "", dict(CONV_KC=4, CONV_SPLIT=10)),    # shares of one and two
+    ("f32", 192, 40, 20, 20, 6, "", dict(CONV_KC=8)),
+    ("bf16", 384, 64, 24, 24, 8, "stored", {}),                          # stored tiles
+    ("f16", 256, 48, 22, 26, 8, "up", {}),                               # up-sampled source
+    ("bf16", 192, 48, 27, 29, 6, "stride 2", dict(CONV_KC=4)),           # 13 x 13 tiles, ragged
+    ("f16", 256, 64, 22, 26, 8, "copies", {}),                           # residual and an activated copy in the epilogue
 ])
-def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, stored, kn):
+def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, form, kn):
     """Calls of the 64 x 32 shape that walk through two chunks or more without staged arithmetic request the
-    next chunk ahead.  Scale 1 and shift 0 send the same call down the staging that does not: equal bit for
-    bit (same sums in the same order), and both against the oracle."""
+    next chunk ahead (CONV_AHEAD=1 refuses a call that does not).  The same call without that, and sent down
+    the staging with arithmetic by scale 1 and shift 0: equal bit for bit (same sums in the same order), and
+    against the oracle."""
     rng = np.random.default_rng(Cin + Cout + H)
     td = DT[dtype]
-    x = torch.from_numpy(rng.standard_normal((H, W, Cin)).astype(np.float32)).to(td)
+    up, stride = int(form == "up"), 2 if form == "stride 2" else 1
+    x = torch.from_numpy(rng.standard_normal((H >> up, W >> up, Cin)).astype(np.float32)).to(td)
     w, bias = inputs.conv_params(rng, Cout, Cin, 3, td)
-    cache = torch.from_numpy(rng.standard_normal((H, W, Cout)).astype(np.float32)).to(td)
-    conv = SigeConv(dev(w), bias, H, W, b, 1, 1)
+    conv = SigeConv(dev(w), bias, H, W, b, stride, 1, up=up)
     g = conv.g
+    Ho, Wo = g.H_out, g.W_out
+    cache = torch.from_numpy(rng.standard_normal((Ho, Wo, Cout)).astype(np.float32)).to(td)
     bl = BlockList(g, "cuda").all_active()
     n = g.grid_blocks
     pick = np.unique(np.append(rng.permutation(n)[:max(3, n // 3)], n - 1))
@@ -1339,23 +1346,42 @@ def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, stored, 
     bl.n_host = n
     one, zero = torch.ones(Cin, device="cuda"), torch.zeros(Cin, device="cuda")
     ws = Workspace("cuda")
-    with api.knobs(**{**dict(CONV_CFG=3, CONV_SPLIT=1), **kn}):
-        if stored:
-            tiles = torch.from_numpy(rng.standard_normal((n + 1, g.tile_h, g.tile_w, Cin)).astype(np.float32)).to(td)
+    kn = {**dict(CONV_CFG=3, CONV_SPLIT=1), **kn}
+    if form == "stored":
+        tiles = torch.from_numpy(rng.standard_normal((n + 1, g.tile_h, g.tile_w, Cin)).astype(np.float32)).to(td)
+        outs = []
+        for ahead in (1, 0):
             out = torch.full((n + 1, b, b, Cout), 5.0, dtype=td, device="cuda")
-            api.sige_conv(dev(tiles), g, Cin, Cout, conv.packed, conv.bias, bl.count, out, n_blocks=n, max_blocks=n)
-            want = np.stack([oracle.conv2d(f64(tiles[i]), f64(w), f64(bias), 1, 0) for i in range(n)])
-            assert_close(out[:n], want, td, "stored tiles")
-            assert (out[n:] == 5.0).all()
-            return
-        got = []
-        for scale, shift in ((None, None), (one, zero)):
-            y = dev(cache).clone()
-            conv.forward(dev(x), y, bl, ws, scale=scale, shift=shift, fused=True)
-            got.append(y)
-    assert torch.equal(got[0], got[1])
-    want = oracle.select_blocks(oracle.conv2d(f64(x), f64(w), f64(bias), 1, 1), f64(cache), blocks.cpu().numpy(), b, b)
-    assert_close(got[0], want, td, "requested ahead")
+            with api.knobs(CONV_AHEAD=ahead, **kn):
+                api.sige_conv(dev(tiles), g, Cin, Cout, conv.packed, conv.bias, bl.count, out, n_blocks=n, max_blocks=n)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1])
+        want = np.stack([oracle.conv2d(f64(tiles[i]), f64(w), f64(bias), 1, 0) for i in range(n)])
+        assert_close(outs[0][:n], want, td, "stored tiles")
+        assert (outs[0][n:] == 5.0).all()
+        return
+    resid = torch.from_numpy(rng.standard_normal((Ho, Wo, Cout)).astype(np.float32)).to(td) if form == "copies" else None
+    rd = None if resid is None else dev(resid)
+    asc, ash = torch.full((Cout,), 0.75, device="cuda"), torch.full((Cout,), -0.25, device="cuda")
+    got = []
+    for ahead, scale, shift in ((1, None, None), (0, None, None), (None, one, zero)):
+        y = dev(cache).clone()
+        copy = torch.full((Ho, Wo, Cout), 3.0, dtype=td, device="cuda")
+        aos = api.act_out_array([(copy, asc, ash, api.ACT_SILU)]) if form == "copies" else None
+        with api.knobs(CONV_AHEAD=ahead, **kn):
+            conv.forward(dev(x), y, bl, ws, scale=scale, shift=shift, fused=True, residual=rd, act_outs=aos)
+        got.append((y, copy))
+    for y, copy in got[1:]:
+        assert torch.equal(got[0][0], y) and torch.equal(got[0][1], copy)
+    with api.knobs(CONV_AHEAD=1, **kn), pytest.raises(api.SigeError):
+        conv.forward(dev(x), got[2][0], bl, ws, scale=one, shift=zero, fused=True)      # staged arithmetic: refused
+    xin = f64(x).repeat(2, axis=0).repeat(2, axis=1) if up else f64(x)
+    want = oracle.conv2d(xin, f64(w), f64(bias), stride, 1) + (f64(resid) if resid is not None else 0)
+    want = oracle.select_blocks(want, f64(cache), blocks.cpu().numpy(), b, b)
+    assert_close(got[0][0], want, td, "requested ahead")
+    if form == "copies":
+        act = oracle.scale_shift_act(f64(got[0][0]), np.full(Cout, 0.75), np.full(Cout, -0.25), oracle.ACT_SILU)
+        assert_close(got[0][1], oracle.select_blocks(act, np.full((Ho, Wo, Cout), 3.0), blocks.cpu().numpy(), b, b), td, "copy")
 
 
 @pytest.mark.parametrize("dtype,Cin,Cout,b,n,kernel", [

@@ -21,6 +21,9 @@ from . import api, inputs
 from .layers import BlockList, SigeConv, Workspace
 
 
+WHOLE_IMAGE_BLOCK = 4096      # the largest block the library takes: wider images are copied in blocks
+
+
 def _next_pow2(n: int) -> int:
     p = 1
     while p < n:
@@ -158,7 +161,7 @@ class SigeUNet:
         one kernel and one trip through memory per copy instead of a gather and a scatter (the dense
         pass of the 256x256 pixel-space network: 2.86 -> 2.31 ms, 55 of 299 launches fewer)."""
         H, C = x.shape[0], x.shape[2]
-        whole = H <= 4096                          # the largest block the library takes
+        whole = H <= WHOLE_IMAGE_BLOCK
         b = H if whole else min(self.block, H)
         bl = self._lists(H, 1, 1, b)[0]
         n = bl.n_host

@@ -253,6 +253,25 @@ def test_gather_strided_source_and_upsample(oracle):
     assert np.array_equal(f64(tiles), want)
 
 
+@pytest.mark.parametrize("dtype,C,H", [("f16", 128, 256), ("bf16", 320, 64), ("f16", 48, 100), ("f32", 24, 130)])
+def test_gather_of_the_whole_image(oracle, dtype, C, H):
+    """A block as large as the image: its tile has the image's own layout (how the dense pass writes its
+    activated copies), with Scale+Shift and SiLU, from a channel slice of a wider tensor."""
+    rng = np.random.default_rng(C + H)
+    td = DT[dtype]
+    x = torch.from_numpy(rng.standard_normal((H, H, C + 16)).astype(np.float32)).to(td)
+    scale = torch.from_numpy(rng.uniform(0.5, 1.5, C).astype(np.float32))
+    shift = torch.from_numpy(rng.uniform(-0.5, 0.5, C).astype(np.float32))
+    g = api.geom(H, H, H, 1, 1, 0)
+    bl = BlockList(g, "cuda").all_active()
+    assert bl.n_host == 1
+    out = torch.full((H, H, C), float("nan"), dtype=td, device="cuda")
+    api.sige_gather(dev(x)[:, :, 8:8 + C], g, bl.indices, bl.count, out, n_blocks=1, scale=dev(scale), shift=dev(shift),
+                    act=api.ACT_SILU, C=C, max_blocks=1)
+    want = oracle.scale_shift_act(f64(x)[:, :, 8:8 + C].copy(), f64(scale), f64(shift), oracle.ACT_SILU)
+    assert_close(out, want, td, "whole image")
+
+
 @pytest.mark.parametrize("dtype,C,H,W,b", [("f32", 64, 64, 64, 6), ("f16", 128, 70, 90, 16),
                                            ("bf16", 256, 33, 31, 4), ("f16", 8, 19, 23, 5)])
 def test_scatter_bit_exact_and_untouched_outside(oracle, dtype, C, H, W, b):

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from helpers import f64, round_to
-from paper_2211_02048_amd import api, inputs
+from paper_2211_02048_amd import api, inputs, unet
 from paper_2211_02048_amd.unet import SigeUNet
 
 pytestmark = pytest.mark.gpu
@@ -134,7 +134,7 @@ def test_unet_full_size_every_layer_teacher_forced(area):
     rep_e.assert_clean(min_checked=80)
 
 
-def test_unet_precompute_and_sparse_step(setup):
+def test_unet_precompute_and_sparse_step(setup, monkeypatch):
     s = setup
     net, td = s["net"], inputs.DTYPES[s["dtype"]]
     # SECOND check, on the free-running chain (the per-layer bar is held by the teacher-forced test
@@ -214,8 +214,12 @@ def test_unet_precompute_and_sparse_step(setup):
         x = net.view(L["op"]["x"])
         keep = L["pre"].clone()
         act = api.ACT_SILU if (L["op"]["kind"] == "conv" and L["op"]["act"]) else api.ACT_NONE
-        net._fill_copy(L, x, L["scale"], L["shift"], act)
-        assert torch.equal(L["pre"], keep), ("activated copy", n)
+        for limit in (unet.WHOLE_IMAGE_BLOCK, 1):        # one gather of the whole image; blocks (images wider than a block may be)
+            monkeypatch.setattr(unet, "WHOLE_IMAGE_BLOCK", limit)
+            L["pre"].fill_(float("nan"))
+            net._fill_copy(L, x, L["scale"], L["shift"], act)
+            assert torch.equal(L["pre"], keep), ("activated copy", n, limit)
+            monkeypatch.undo()
         n_copies += 1
     assert n_copies >= 20
 

@@ -1136,6 +1136,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
         org[2 * (16 * wave + (lane >> 2)) + 1] = xx;
     }
     const char* __restrict__ rp[NI];
+    bool outside = false;                                     // one of this lane's rows is a pixel outside the image
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int r = min(rr[i], rows - 1);
@@ -1149,6 +1150,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
             const int y0 = r == rr[i] ? oy[i] : a.indices[2 * n];
             const int x0 = r == rr[i] ? ox[i] : a.indices[2 * n + 1];
             pixel = (long)min(y0 + py, a.Hin - 1) * a.Win + min(x0 + px, a.Win - 1);
+            outside = outside || y0 + py >= a.Hin || x0 + px >= a.Win;
             ld = a.x_ld;
         }
         rp[i] = (gathered ? (const char*)a.x : (const char*)a.tiles) + pixel * ld * S + (lane & 3) * 16;
@@ -1160,6 +1162,9 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
     };
 #pragma unroll
     for (int st = 0; st < P; ++st) fetch_a(st, q0 + st);
+
+    // (every wave has looked at all rows of the patch: the answer is the workgroup's)
+    const bool clear_outside = gathered && a.y == nullptr && __ballot(outside) != 0ull;
 
     // What the epilogue needs for this thread's first run of output channels and does not depend on
     // the sums - bias and residuals - is fetched now and arrives during the K loop (the origin of the
@@ -1248,10 +1253,11 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
                 red[(wave * BM + m) * RS + tn * 32 + l32] = acc[tm][tn][r];
             }
     __syncthreads();
-    if (gathered && !to_y) {
+    if (clear_outside) {
         // A gathered pixel outside the image is a row of zeros, as sige_gather stores it: the sums made from the
         // clamped pixel that was read in its place do not count.  (Here and not in the K loop: a select there
-        // costs 1 % of every call, a condition in the loop below several.)
+        // costs 1 % of every call, a condition in the loop below several; and only where a row does lie outside:
+        // the barrier and the divisions cost the pixel-space denoiser's step 6 us.)
         const int m = tid / W, w = tid % W, r = r0 + m;
         if (m < BM && r < rows) {
             int n, p, py, px;

@@ -251,14 +251,16 @@ static int pointwise_tiles(const sige_geom* g, const ConvArgs& a, int ks, int nl
 // are in flight from the first instruction while the tiled one stages its chunks in turn (bf16, weights from
 // memory, tiled -> here: 640 rows 320 -> 2560 channels 17.0 -> 9.5 us, 1280 -> 3840 36.5 -> 22.4; 2240 rows
 // 1280 -> 1280 37.3 -> 22.7, 320 -> 2560 27.4 -> 22.6; beyond 2048 patches even or slower: 1280 rows
-// 1280 -> 10240 84.9 vs 86.8), unless the plan p that the tiled kernel would use is one it runs well.  200 calls of
-// 512 to 100000 rows and 32 to 5000 channels, tiles to tiles / gathered and scattered with a residual and a copy:
+// 1280 -> 10240 84.9 vs 86.8), unless the plan p that the tiled kernel would use is one it runs well.  270 calls of
+// 128 to 100000 rows and 32 to 10000 channels, tiles to tiles / gathered and scattered with a residual and a copy (a
+// round is two workgroups per compute unit; nearly whole: 0.79 of it is work, counted in this kernel's patches):
 //   chunks of one or three K steps: never (480 -> 80 on 8448 rows 1.4 / 1.2 times the few-row time, 608 -> 176 on 42880 4.2 / 2.4),
 //     except 128 x 128 patches with chunks of three in a whole round (1056 -> 2176 on 3776 rows even);
-//   128 x 128 in nearly whole rounds of two workgroups per compute unit: always (640 -> 1920 on 4096 rows 25.3 vs 31.7 us);
-//   128 x 64 in such rounds: with up to ten chunks (320 -> 320 on 11008 rows 15.7 / 20.1 vs 15.7 / 23.2, 768 -> 176 on 39360 45.4 /
-//     53.4 vs 44.2 / 59.9; 832 -> 720 on 4544, 13 chunks of four, 1.14 times);  64 x 64: up to seven (512 -> 128 on 16384 12.1 / 14.5
-//     vs 12.5 / 16.4; a round and a half of 1280 -> 640 on 4096 36.1 / 37.4 vs 24.3 / 30.1);
+//   128 x 128 in nearly whole rounds: always (640 -> 1920 on 4096 rows 25.3 vs 31.7 us, 640 -> 6080 on 1280 0.65 times);
+//   128 x 64 in a nearly whole round: up to ten chunks of eight K steps or seven of four (320 -> 320 on 11008 rows 15.7 / 20.1 vs
+//     15.7 / 23.2; 832 -> 720 on 4544, 13 chunks of four, 1.14 times); in two: up to six or five (768 -> 176 on 39360 45.4 /
+//     53.4 vs 44.2 / 59.9; 1280 -> 2800 on 2560, ten chunks, 1.12 times; in one and a half 768 -> 6112 on 960 1.3 times);
+//   64 x 64: up to four chunks (512 -> 128 on 16384 12.1 / 14.5 vs 12.5 / 16.4; 640 -> 2 x 2560 gated on 384 16.0 vs 12.7);
 //   64 x 32: where less than 0.7 of this kernel's 64 channels is used, few chunks and up to two rounds (512 -> 32 on 19520
 //     rows 9.3 / 10.4 vs 11.2 / 14.0, 320 -> 32 on 21568 11.9 / 10.2 vs 11.2 / 11.8; 960 -> 32 on 20480 22.3 / 23.7 vs 15.9 / 18.1,
 //     640 -> 48 on 16448 1.6 / 1.4 times).
@@ -271,13 +273,14 @@ static bool few_rows_alone(const sige_geom* g, const ConvArgs& a, int ks, int nl
     if ((rows + 63) / 64 * nt2 > 2048) return false;
     if (p == nullptr) return true;                          // a block too wide for every tiled shape
     const long w = (long)p->groups * p->bands * p->slabs, whole = (w + 511) / 512 * 512;
-    const bool full = w * 100 >= whole * 79;
+    const bool full = rows * nt2 * 64 * 100 >= 79 * whole * kCfg[p->cfg].M * kCfg[p->cfg].N;
     const int nch = a.Cin / (p->kc * ks);
     if (p->kc == 1) return true;
     if (p->cfg == 0) return !full;
     if (p->kc < 4) return true;
     if (p->cfg == 3) return a.Cout * 10L >= nt2 * 64 * 7 || nch > 5 || w > 1024;
-    return !full || nch > (p->cfg == 1 ? 10 : 7);
+    if (p->cfg == 2) return !full || nch > 4;
+    return !full || nch > (whole == 512 ? (p->kc == 8 ? 10 : 7) : (p->kc == 8 ? 6 : 5));
 }
 
 // Shared by sige_conv, sige_conv_scatter and sige_fused_conv: plan and fill the arguments.  *pointwise: the call
@@ -363,8 +366,9 @@ static bool shared_beats_few_rows(const ConvArgs& a0, const ConvPlan& p0, const 
 // pointwise_kernel): the plan's own where some pair with the call shares its launch.  With chunks of four that
 // order costs up to 6 %, so calls too large for it (three fifths of the workgroups above, by the rule on wide
 // shortcuts) keep the free one.
-static int order_of_sums(const ConvPlan& p)
+static int order_of_sums(const ConvArgs& a, const ConvPlan& p)
 {
+    if (a.glu) return 0;                                    // never part of a pair
     if (p.cfg != 3 || p.ksplit != 1 || knob(SIGE_KNOB_CONV_POINTWISE_W4) == 0) return 0;     // (its kernels have four waves)
     if (p.kc == 4) return 5L * p.groups * p.bands * p.slabs <= 3 * kSharedStaged ? 4 : 0;
     return p.kc == 8 ? 8 : 0;
@@ -378,7 +382,7 @@ static int launch_prepared(sige_dtype dt, const ConvArgs& a, const ConvPlan& p, 
     int order = 0;
     if (!pointwise && p.few_rows_alone) {
         pointwise = 2;
-        order = order_of_sums(p);
+        order = order_of_sums(a, p);
     }
     if (pointwise)
         return dt == SIGE_F32 ? launch_pointwise<float>(a, nl, pointwise, 0, st)

@@ -265,9 +265,10 @@ def test_conv_plans_respect_the_lds_of_a_compute_unit(L):
     (512, 80, 18560, False),
     (960, 32, 20480, True), (320, 32, 102400, True), (640, 48, 16448, True), (640, 96, 51200, True),
     (320, 160, 16384, True), (640, 160, 16384, True),      # 128 x 128 patches would fill a round; the plan is 64 x 32
-    (512, 128, 16384, False), (896, 304, 6464, False),     # 64 x 64 in one whole round, four and seven chunks
+    (512, 128, 16384, False), (896, 304, 6464, True), (640, 5120, 384, True),     # 64 x 64 in one whole round; four, seven and five chunks
     (1280, 640, 4096, True), (640, 320, 8192, True),       # ... in one and a quarter
-    (320, 320, 11008, False), (640, 720, 8640, False), (768, 176, 39360, False), (1280, 160, 41216, False),   # 128 x 64, whole rounds
+    (320, 320, 11008, False), (640, 720, 8640, False), (768, 176, 39360, False), (768, 144, 42368, False),   # 128 x 64, whole rounds
+    (1280, 1984, 1984, False), (1280, 160, 41216, True), (1152, 9200, 320, True),   # ten chunks in one round and in two; patches that stick out
     (832, 720, 4544, True), (320, 320, 16384, True),       # 13 chunks; a round and a quarter
     (640, 1920, 4096, False), (320, 256, 32768, False),    # 128 x 128
     (608, 32, 58304, True), (736, 288, 10176, True), (480, 80, 8448, True),     # chunks of one or three K steps

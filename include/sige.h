@@ -224,7 +224,8 @@ size_t sige_conv_workspace_bytes(sige_dtype dt, const sige_geom* g, int32_t Cin,
  * know which code path they cover and for tuning.  n_blocks = the number of blocks the launch is
  * sized for; staged_math != 0 when Scale+Shift or an activation is applied on the way into LDS;
  * up as in sige_fused_conv; workspace_bytes as the call would get (0 = none).
- *   kernel             0 = tiled implicit GEMM, 1 = the 1x1 kernel for few rows
+ *   kernel             0 = tiled implicit GEMM, 1 = the 1x1 kernel that streams K (built for few rows; the half
+ *                      types take it up to 2048 patches of 64x64)
  *   shape              tiled: 0 = 128x128, 1 = 128x64, 2 = 64x64, 3 = 64x32 with four waves splitting K,
  *                      4 = 64x32 and 5 = 32x32 with eight waves splitting K; few rows: 1 = 64x32, 2 = 64x64,
  *                      3 = 32x32

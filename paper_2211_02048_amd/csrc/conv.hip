@@ -14,7 +14,7 @@
 // scatter into the epilogue (sige_conv_scatter: the scatter only); with a workspace, calls
 // with few workgroups and a long K are cut along K and finished by conv_reduce_kernel, or
 // - without staged arithmetic and up to two chunks - take a shape whose four or eight waves split K
-// with the whole of Cin (or half) staged at once.  1x1 calls with few rows have a kernel of their
+// with the whole of Cin (or half) staged at once.  1x1 calls with a long K and not too many rows have a kernel of their
 // own further down (pointwise_kernel); two independent fused calls can share one launch
 // (conv_pair_kernel, sige_fused_conv_pair).
 // The epilogue can also write activated copies of the output for the layers that
@@ -678,7 +678,8 @@ static int fused_pair(const char* who, const sige_fused_conv_call* first, const 
     hipStream_t st = (hipStream_t)stream;
     // one launch when both take the 64 x 32 shape whose four waves split K, unsplit over workgroups,
     // with the same chunk: a 3x3 call first, a 1x1 call second (measured a gain up to the 1440
-    // workgroups at which calls still take that shape: 23.3 vs 25.2 us; 11.4 vs 16.3 us at 560)
+    // workgroups at which calls still take that shape: 23.3 vs 25.2 us; 11.4 vs 16.3 us at 560), unless the 1x1 call
+    // by itself goes to the few-row kernel and the two are the faster way (shared_beats_few_rows)
     const long wgs_both = nl[0] > 0 && nl[1] > 0 && !pw[0] && !pw[1]
                               ? (long)p[0].groups * p[0].bands * p[0].slabs + (long)p[1].groups * p[1].bands * p[1].slabs
                               : 0;

@@ -1028,6 +1028,7 @@ __global__ __launch_bounds__(256) void conv_reduce_kernel(ConvArgs a, long n_run
 }
 
 // ---- 1x1 convolutions with few rows ------------------------------------------------------------
+// (built for a few hundred rows; the half types take it up to 2048 patches of 64 x 64, see few_rows_alone in conv.hip)
 // A 1x1, stride-1 convolution on the stacked pixels of the active blocks is a matrix product with
 // few rows (M = active pixels) and a long K; no input pixel is used by two taps, so a tile staged
 // for the whole workgroup buys nothing.  One workgroup owns 64 rows x 32*TN output channels and its

@@ -1045,7 +1045,7 @@ __global__ __launch_bounds__(256) void conv_reduce_kernel(ConvArgs a, long n_run
 // shape sums chunks of that many K steps (wave w takes steps 2w and 2w + 1, or step w, of every chunk, the bias goes
 // into the first wave's sum), so that a call has the same bits launched by itself, here, as inside a shared
 // launch (conv_pair_kernel).  With 8 a wave still loads what it multiplies.  With 4 that would be half rows, two
-// requests for 64 bytes (15 - 30 % slower): the waves load 64 bytes of a row each, as with 8, into one buffer, and take
+// requests for 64 bytes (2 - 12 % slower): the waves load 64 bytes of a row each, as with 8, into one buffer, and take
 // their steps from there, one barrier per pair of chunks.
 template <typename T, int W, int P, int TM, int TN, int ORDER = 0>
 __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvArgs a)

@@ -227,7 +227,7 @@ size_t sige_conv_workspace_bytes(sige_dtype dt, const sige_geom* g, int32_t Cin,
  *   kernel             0 = tiled implicit GEMM, 1 = the 1x1 kernel that streams K (built for few rows; the half
  *                      types take it up to 2048 patches of 64x64)
  *   shape              tiled: 0 = 128x128, 1 = 128x64, 2 = 64x64, 3 = 64x32 with four waves splitting K,
- *                      4 = 64x32 and 5 = 32x32 with eight waves splitting K; few rows: 1 = 64x32, 2 = 64x64,
+ *                      4 = 64x32, 5 = 32x32 and 6 = 32x16 with eight waves splitting K; few rows: 1 = 64x32, 2 = 64x64,
  *                      3 = 32x32
  *   patch_m, patch_n   output rows (pixels) x channels per workgroup
  *   k_steps_per_chunk  MFMA K steps per staged channel chunk (tiled kernel)
@@ -461,7 +461,7 @@ int sige_version(void);
  *                      3 = 64x32 with four waves splitting K; with CONV_KC >= 16 also 4 (eight waves)
  *   CONV_KC            K steps per staged channel chunk (1, 3, 4, 8; 16, 20, 32, 40 = whole-Cin shapes)
  *   CONV_SPLIT         number of workgroups that share an output patch along K (needs a workspace)
- *   CONV_HALF          most workgroups up to which the eight-wave shape takes 32-row patches
+ *   CONV_HALF          most workgroups up to which the eight-wave shape takes 32-row patches (128)
  *   CONV_SPLIT_WGS     workgroups a K split over workgroups aims for
  *   CONV_POINTWISE     the few-row 1x1 kernel: 0 = never, 1 = 64x32, 2 = 64x64, 3 = 32x32 patches
  *   CONV_POINTWISE_W4  its four-wave variant for 64x64 patches: 0 = never, 1 = always
@@ -472,8 +472,8 @@ int sige_version(void);
  *   CONV_DIRECT        0: the shapes whose waves do not split K send their accumulators through LDS
  *                      instead of straight from the registers
  *   CONV_LDS_PAD       bytes between the staged pixels' channel runs in LDS (a multiple of 16)
- *   CONV_AHEAD         chunks of the 64x32 shape requested ahead: 0 = never, 1 = a tiled call that cannot ends in
- *                      SIGE_ERR_UNSUPPORTED                                                             */
+ *   CONV_AHEAD         requests ahead in the shapes whose waves split K (the next chunk, or the only one at once): 0 = never,
+ *                      1 = a tiled call that cannot request its next chunk ahead ends in SIGE_ERR_UNSUPPORTED                                                             */
 typedef enum {
     SIGE_KNOB_CONV_CFG = 0, SIGE_KNOB_CONV_KC = 1, SIGE_KNOB_CONV_SPLIT = 2, SIGE_KNOB_CONV_HALF = 3,
     SIGE_KNOB_CONV_SPLIT_WGS = 4, SIGE_KNOB_CONV_POINTWISE = 5, SIGE_KNOB_CONV_POINTWISE_W4 = 6,

@@ -136,10 +136,11 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
             if (lds <= (c[0] == 4 ? 150u : 75u) * 1024u) { q.cfg = c[0]; q.kc = c[1]; q.lds = lds; break; }
         }
         long wgs4 = (long)q.groups * q.bands * q.slabs;
-        // at most 64 workgroups (a 512-channel layer at 8 x 8 has 16): patches of 32 rows instead of
-        // 64, so that twice as many compute units stream the weight and share the MFMAs
+        // at most 128 workgroups (a 512-channel layer at 8 x 8 has 16): patches of 32 rows instead of 64, so that twice as
+        // many compute units stream the weight and share the MFMAs (640 -> 640 on six 8x8 blocks 13.1 -> 11.4 us, 512 -> 256
+        // on four 16x16 blocks 12.1 -> 10.1)
         const int half_knob = knob(SIGE_KNOB_CONV_HALF);     // most workgroups for which rows are halved
-        const long half_max = half_knob >= 0 ? half_knob : 64;
+        const long half_max = half_knob >= 0 ? half_knob : 128;
         if (q.kc && q.cfg == 4 && wgs4 <= half_max && pbfull >= 64 && g->block_w <= 32) {
             q.cfg = 5;
             q.G = 1;
@@ -149,6 +150,15 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
             q.groups = nblocks;
             q.lds = lds_bytes(5, (long)q.trows * tw, q.kc);
             wgs4 = (long)q.groups * q.bands * q.slabs;
+            // still at most 128 of them, half types: 16 output channels each (see NARROW in conv_kernels.h; 512 -> 512 at
+            // 16 x 16 9.7 -> 7.7 us, at 8 x 8 10.1 -> 7.9), whose workgroups request everything ahead
+            if (s == 2 && wgs4 <= 128 && q.kc % 16 == 0 && !force_whole && knob(SIGE_KNOB_CONV_AHEAD) != 0 &&
+                (long)q.trows * tw <= (long)once_vectors(q.kc, 1) * (512 / (2 * q.kc))) {
+                q.cfg = 6;
+                q.slabs = (Cout + 15) / 16;
+                q.lds = lds_bytes(6, (long)q.trows * tw, q.kc);
+                wgs4 = (long)q.groups * q.bands * q.slabs;
+            }
         }
         if (q.kc && (wgs4 <= 256 || force_whole)) {
             q.Cc = q.kc * kstep;
@@ -327,11 +337,18 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     // chunk there is nothing to hide; shares of one and two still gain (bf16 960 -> 640 on one 8x8 block, 15 chunks in
     // ten shares: 14.5 -> 13.9 us).
     const long pipe_vectors = (long)p->G * p->trows * tw * 2 * p->kc;
-    p->pipe = p->cfg == 3 && g->k == 3 && (p->kc == 4 || p->kc == 8) && a.scale == nullptr && a.act == SIGE_ACT_NONE &&
-              pipe_vectors <= 256L * kPipeVectors && Cin / (p->kc * ks) > p->ksplit;
+    const int nch = Cin / (p->kc * ks);
+    const bool can_ahead = nch > p->ksplit && (p->cfg == 6 || (p->cfg == 3 && g->k == 3 && (p->kc == 4 || p->kc == 8) &&
+                                                               a.scale == nullptr && a.act == SIGE_ACT_NONE &&
+                                                               pipe_vectors <= 256L * kPipeVectors));
     const int ahead = knob(SIGE_KNOB_CONV_AHEAD);           // 0 = never, 1 = refuse what cannot
-    SIGE_REQUIRE(ahead < 1 || p->pipe, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
-    p->pipe = p->pipe && ahead != 0;
+    SIGE_REQUIRE(ahead < 1 || can_ahead, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
+    // One chunk per workgroup (the whole of Cin staged at once, or as many shares as chunks): requested in one go where
+    // the tile is one batch of vectors for the threads that stage (2 * kc vectors per pixel, whole pixels per step).
+    const int threads = kCfg[p->cfg].WK == 8 ? 512 : 256;
+    const bool can_once = kCfg[p->cfg].WK > 1 && (g->k == 3 || g->k == 1) && nch == p->ksplit &&
+                          (long)p->G * p->trows * tw <= (long)once_vectors(p->kc, p->cfg >= 5 ? 1 : 2) * (threads / (2 * p->kc));
+    p->mode = can_ahead && ahead != 0 ? kAhead : can_once && ahead != 0 ? kOnce : kPlain;
     a.d_pb = fast_div(p->rows * g->block_w);
     a.d_per = fast_div(p->trows * tw);
     a.d_tw = fast_div(tw);

@@ -47,6 +47,27 @@ template <> struct Mma<float> {
     }
 };
 
+// NARROW shapes: 16 x 16 tiles, one fragment of each operand advances K by two K steps; lane l holds row (or channel)
+// l % 16 and the (l / 16)-th quarter of the 32 channels, which is half (l / 16) % 2 of the (l / 32)-th K step in the
+// packed weight's terms: the fragment of 16 channels is four runs of 256 bytes of it.
+template <typename T> struct Mma16;
+template <> struct Mma16<f16> {
+    static __device__ __forceinline__ void run(const uint4& a, const uint4& b, f32x4& c)
+    {
+        union { uint4 u; f16x8 v; } x, y;
+        x.u = a; y.u = b;
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x.v, y.v, c, 0, 0, 0);
+    }
+};
+template <> struct Mma16<bf16> {
+    static __device__ __forceinline__ void run(const uint4& a, const uint4& b, f32x4& c)
+    {
+        union { uint4 u; bf16x8 v; } x, y;
+        x.u = a; y.u = b;
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v, y.v, c, 0, 0, 0);
+    }
+};
+
 struct ConvArgs {
     const void* tiles;
     const void* w;
@@ -284,7 +305,18 @@ constexpr int ring_depth(int steps, int limit)
     return d;
 }
 
+// How a workgroup of the shapes whose waves split K comes by its chunks (see the K loop in conv_body):
+// kPlain  a chunk is requested, staged and multiplied before the next one is asked for
+// kAhead  the next chunk's pixels are requested while the current chunk is multiplied
+// kOnce   the workgroup has one chunk: its tile and its first weights are requested together, nothing is fetched twice
+enum ChunkMode { kPlain = 0, kAhead = 1, kOnce = 2 };
 constexpr int kPipeVectors = 8;   // 16-byte vectors per thread of a chunk that is requested ahead
+// ... and of a chunk that is requested at once: the tile of a 16 x 16 or 8 x 8 block's band with a halo of one, by the K steps of
+// the chunk and the 32-row tiles of the patch (a fixed number: under a condition, uniform or not, the compiler waits for each)
+constexpr int once_vectors(int kc, int tm)
+{
+    return kc == 40 ? (tm == 1 ? 10 : 18) : kc == 32 ? (tm == 1 ? 9 : 14) : kc == 20 ? 18 : kc == 16 ? (tm == 1 ? 5 : 7) : kc == 8 ? 7 : 4;
+}
 constexpr int MAX_G = 256;   // most blocks one workgroup can hold (1x1 blocks in a 256-row patch)
 
 // TM x TN: 32x32 MFMA tiles per wave; WM x WN x WK = 4 (or 8) waves over M, N and K (waves that
@@ -294,16 +326,23 @@ constexpr int MAX_G = 256;   // most blocks one workgroup can hold (1x1 blocks i
 // phase has nothing to overlap its LDS and L2 latencies with.
 // (The body is a device function so that two calls can share one launch, see conv_pair_kernel;
 // bx, by, bz are the workgroup's coordinates inside its own call's grid.)
-// PIPE: the next chunk's pixels are requested while the current chunk is multiplied (see the loop).
-template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool MARKED = false, bool PIPE = false>
+// NARROW: 16 x 16 instead of 32 x 32 tiles, a patch of 32 rows x 16 channels whose eight waves split K.  A layer with few rows
+// is weights through few compute units (9 * Cin * 2 bytes per output channel at 64 bytes per clock): half the channels per
+// workgroup halve that and leave the tile, the smaller part, as it is.
+template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool MARKED = false, int MODE = kPlain,
+          bool NARROW = false>
 __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const int by, const int bz)
 {
     constexpr int NT = 64 * WM * WN * WK;                     // threads per workgroup
     static_assert(NT == 256 || NT == 512, "four or eight waves per workgroup");
     static_assert(KC % WK == 0, "waves that split K take whole K steps");
+    constexpr bool PIPE = MODE == kAhead, ONCE = MODE == kOnce;
+    static_assert(!ONCE || (WK > 1 && KK > 0), "one chunk at once: the shapes whose waves split K");
     constexpr int KS = Mma<T>::KSTEP;
     constexpr int S = (int)sizeof(T);
-    constexpr int KW = KC / WK;                               // K steps per wave and tap
+    static_assert(!NARROW || (TM == 2 && TN == 1 && WM * WN == 1 && MODE != kPlain && S == 2 && KC % (2 * WK) == 0), "32 x 16 patches");
+    constexpr int TILE = NARROW ? 16 : 32, GW = NARROW ? 2 : 1;   // rows and channels of an MFMA tile, K steps it takes
+    constexpr int KW = KC / WK / GW;                          // MFMA steps per wave and tap
     extern __shared__ uint4 lds4[];
     char* lds = reinterpret_cast<char*>(lds4);
     // the arguments, fetched in two goes instead of group by group before each first use
@@ -405,21 +444,22 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     const int wk = wave % WK, wmn = wave / WK;
     const int wm = wmn / WN, wn = wmn - wm * WN;
     const int half = lane >> 5, l32 = lane & 31;
+    const int lt = lane % TILE, quarter = lane / TILE;        // row (or channel) and K share of this lane in an MFMA tile
     const int trow0 = band_row0 * a.stride;                   // first staged tile row
 
     // LDS byte offset of this lane's A row for each of its M tiles (clamped to a valid pixel)
     int a_base[TM];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
-        const int m = (wm * TM + tm) * 32 + l32;
+        const int m = (wm * TM + tm) * TILE + lt;
         int g, p, py, px;
         divmod(m, a.d_pb, g, p);
         divmod(p, a.d_bw, py, px);
         if (g >= a.G || py >= band_rows) { g = 0; py = 0; px = 0; }
-        a_base[tm] = ((g * a.trows + py * a.stride) * a.tw + px * a.stride) * a.ps + half * 16 +
-                     wk * KW * (KS * S);
+        a_base[tm] = ((g * a.trows + py * a.stride) * a.tw + px * a.stride) * a.ps + quarter * 16 +
+                     wk * KW * (GW * KS * S);
     }
-    const int nt0 = (bx * WN + wn) * TN;                      // first 32-wide Cout tile of this wave
+    const int nt0 = (bx * WN + wn) * TN;                      // first Cout tile of this wave (TILE channels wide)
     const int kk = a.k * a.k, kcs = a.Cin / KS;
     const int ntn_total = (a.Cout + 31) / 32;
 
@@ -434,17 +474,18 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // The start values are only requested here (four-float vectors where the run is whole) and go into
     // the accumulators after the first chunk is staged: taken at once they would make every workgroup
     // wait for a round trip to memory before it has asked for its weights and its tile.
-    f32x16 acc[TM][TN];
-    f32x16 acc_init[TN];
+    using Acc = std::conditional_t<NARROW, f32x4, f32x16>;
+    Acc acc[TM][TN];
+    Acc acc_init[TN];
     float bias_v[TN];
     const bool bias4 = aligned16_dev(a.bias);
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
-        const int o = (nt0 + tn) * 32 + l32;
+        const int o = (nt0 + tn) * TILE + lt;
         bias_v[tn] = (!SWAP && a.bias && o < a.Cout && wk == 0 && a.partial == nullptr) ? a.bias[o] : 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc_init[tn][r] = 0.0f;
-        if (SWAP && a.bias != nullptr && a.partial == nullptr) {
+        for (int r = 0; r < (NARROW ? 4 : 16); ++r) acc_init[tn][r] = 0.0f;
+        if constexpr (SWAP) if (a.bias != nullptr && a.partial == nullptr) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int ob = (nt0 + tn) * 32 + 8 * g + 4 * half;
@@ -470,8 +511,9 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     const uint4* __restrict__ wp[TN];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
-        const int nt = min(nt0 + tn, ntn_total - 1);
-        wp[tn] = (const uint4*)a.w + ((long)nt * kk * kcs + wk * KW) * 64 + lane;
+        const int nt = min((nt0 + tn) / (32 / TILE), ntn_total - 1);
+        const int frag = NARROW ? (lane >> 5) * 64 + ((lane >> 4) & 1) * 32 + (nt0 & 1) * 16 + lt : lane;
+        wp[tn] = (const uint4*)a.w + ((long)nt * kk * kcs + wk * KW * GW) * 64 + frag;
     }
     const char* __restrict__ tiles = (const char*)a.tiles;
     const int npix = a.G * a.trows * a.tw;
@@ -486,7 +528,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // bound, fetching the whole chunk ahead (18 loads per wave) holds up the tile loads behind it by
     // more than it saves later (measured 7.5 vs 7.9 us on a 9-block call with 6 vs 18 slots).
     constexpr int STEPS = KK > 0 ? KK * KW : 1;
-    constexpr int D = KK == 0 ? 1 : ring_depth(STEPS, PIPE ? 9 : TN == 1 ? 6 : 8);
+    constexpr int D = KK == 0 ? 1 : ring_depth(STEPS, ONCE ? 18 : PIPE ? 9 : TN == 1 ? 6 : 8);
     const int nch = a.Cin / (KC * KS);
     int ch0 = 0, ch1 = nch, rem_unused;                       // this workgroup's chunks
     if (a.ksplit > 1) {
@@ -496,9 +538,15 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     const int ntaps = KK ? KK : kk;
     uint4 ring[D][TN];
     auto fetch = [&](uint4 (&slot)[TN], int chunk, int tp, int kc) {
-        chunk = min(chunk, nch - 1);
+        if constexpr (PIPE) {
+            // past this workgroup's last chunk every lane reads the same 16 bytes: one request, and the loads in flight stay a fixed number
+            const uint4* src = chunk < ch1 ? wp[0] + ((long)tp * kcs + chunk * KC + kc * GW) * 64 : (const uint4*)a.w;
+            slot[0] = *src;
+        } else {
+            chunk = min(chunk, nch - 1);
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) slot[tn] = wp[tn][((long)tp * kcs + chunk * KC + kc) * 64];
+            for (int tn = 0; tn < TN; ++tn) slot[tn] = wp[tn][((long)tp * kcs + chunk * KC + kc * GW) * 64];
+        }
     };
     const bool fused = a.x != nullptr;
     const bool fuse_math = fused && (a.scale != nullptr || a.act != SIGE_ACT_NONE);
@@ -507,7 +555,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // group and walks over the pixels NT / VPC at a time without dividing.  Each batch of U vectors
     // is loaded before any of them is used (addresses are clamped into the source, so the loads are
     // unconditional and overlap; what lies outside becomes zero afterwards).
-    constexpr int U = TM * TN >= 4 ? 6 : PIPE ? kPipeVectors : 8;   // fewer where the accumulators leave fewer registers
+    constexpr int U = TM * TN >= 4 ? 6 : NARROW ? once_vectors(KC, 1) : PIPE ? kPipeVectors : 8;   // fewer where the accumulators leave fewer registers
     constexpr int PPI = NT / VPC;                             // pixels covered by one step of the walk
     constexpr int NTS = PPI * VPC;                            // threads that stage (all of them unless VPC is 40 or 80)
     const int sv = tid % VPC;
@@ -623,7 +671,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     auto load_a = [&](uint4 (&af)[TM], int tp, int kc) {
         const int kdim = KK == 9 ? 3 : (KK == 1 ? 1 : a.k);      // known at compile time for the unrolled sizes
         const int ky = tp / kdim, kx = tp - ky * kdim;
-        const int off = (ky * a.tw + kx) * a.ps + kc * (KS * S);
+        const int off = (ky * a.tw + kx) * a.ps + kc * (GW * KS * S);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) af[tm] = *(const uint4*)(lds + a_base[tm] + off);
     };
@@ -632,17 +680,21 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-                if constexpr (SWAP) Mma<T>::run(b[tn], af[tm], acc[tm][tn]);
+                if constexpr (NARROW) Mma16<T>::run(af[tm], b[tn], acc[tm][tn]);
+                else if constexpr (SWAP) Mma<T>::run(b[tn], af[tm], acc[tm][tn]);
                 else Mma<T>::run(af[tm], b[tn], acc[tm][tn]);
             }
     };
 
     if constexpr (KK > 0) {
-        auto fill_ring = [&]() {
+        auto fill_ring = [&](const int d0, const int d1) {
 #pragma unroll
-            for (int d = 0; d < D; ++d) fetch(ring[d], ch0, d / KW, d % KW);
+            for (int d = d0; d < d1; ++d) {
+                fetch(ring[d], ch0, d / KW, d % KW);
+                if constexpr (MODE != kPlain) __builtin_amdgcn_sched_barrier(0);   // in the order of the steps: loads return in issue order
+            }
         };
-        if constexpr (!PIPE) fill_ring();
+        if constexpr (MODE == kPlain) fill_ring(0, D);
         // (shapes with start values from memory stage the first chunk ahead of the loop, so that those values
         // are dead before the loop begins; the others keep the one staging site - their kernels start cold in a
         // network step and every kilobyte of code is fetched first)
@@ -691,10 +743,99 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 g += step_g;
                 if (r >= a.trows) { r -= a.trows; ++g; }
             }
-            fill_ring();
+            fill_ring(0, D);
         }
-        for (int chunk = ch0; chunk < ch1; ++chunk) {
-            long ahead = 0;                                   // bytes to the chunk requested next (the last one again at the end: no branch between the steps)
+        // ONCE.  What bounds a one-chunk workgroup is its requests: the tile, and behind it (loads return in issue order)
+        // the weights, at 64 bytes per clock into a compute unit.  The whole tile is one batch of requests without a
+        // condition between them (under one, uniform or not, the compiler waits for each vector), then six weights go
+        // out, the tile goes into LDS, then the other weights of a ring of 15 or 18 (all of them ahead of the tile's way into
+        // LDS: + 0.3 us, the wave stands in the issue queue; a ring of 36: + 1.0).  Nothing is fetched past the share.
+        // Weights from memory, before -> now: 640 -> 640 channels on six 8x8 blocks 14.2 -> 10.8 us (with patches of 32 rows,
+        // see plan_conv), 320 -> 320 on ten 11.6 -> 9.5, 128 -> 128 on sixteen 16x16 blocks 6.4 -> 5.9; 512 -> 512 at 16x16
+        // 11.1 -> 9.7, and 7.7 with 16 channels per workgroup (NARROW), 1024 -> 512, two chunks ahead, 17.6 -> 13.2.
+        if constexpr (ONCE) {
+            constexpr int UO = once_vectors(KC, NARROW ? 1 : TM), N = Vec16<T>::N;
+            uint4 tv[UO];
+            unsigned in = 0u;
+            auto request = [&](auto fused_c, auto single_c) {      // (as in stage_as)
+                constexpr bool FUSED = decltype(fused_c)::value, SINGLE = decltype(single_c)::value;
+                const char* const base = (FUSED ? (const char*)a.x : tiles) + (long)ch0 * (KC * KS * S) + sv * 16;
+                const int px_bytes = (FUSED ? a.x_ld : a.Cin) * S;
+                int g = sg0, r = sr0, x = sx0, gc = -1, oyb = 0, oxb = 0, tb = 0;
+                auto origin = [&](int gg) {
+                    gc = gg;
+                    if (FUSED) {
+                        const int gl = min(gg, a.G - 1);
+                        oyb = org[2 * gl] * a.stride - a.pad + trow0;
+                        oxb = org[2 * gl + 1] * a.stride - a.pad;
+                    } else {
+                        tb = (min(g0 + gg, n_eff - 1) * a.th + trow0) * a.tw;
+                    }
+                };
+                if (SINGLE) origin(0);
+#pragma unroll
+                for (int u = 0; u < UO; ++u) {
+                    if (!SINGLE && g != gc) origin(g);
+                    bool ok = r <= rmax && (SINGLE || g0 + g < n_eff);
+                    const int rr = min(r, rmax);
+                    int pix;
+                    if (!FUSED) {
+                        pix = tb + rr * a.tw + x;
+                    } else {
+                        const int iy = oyb + rr, ix = oxb + x;
+                        ok = ok && iy >= 0 && iy < a.Hin && ix >= 0 && ix < a.Win;
+                        pix = (min(max(iy, 0), a.Hin - 1) >> a.up) * Ws + (min(max(ix, 0), a.Win - 1) >> a.up);
+                    }
+                    tv[u] = *(const uint4*)(base + (long)pix * px_bytes);
+                    in |= ok ? 1u << u : 0u;
+                    x += step_x;
+                    r += step_r;
+                    if (x >= a.tw) { x -= a.tw; ++r; }
+                    if (!SINGLE) {
+                        g += step_g;
+                        if (r >= a.trows) { r -= a.trows; ++g; }
+                    }
+                }
+            };
+            using yes = std::true_type;
+            using no = std::false_type;
+            if (fused) {
+                if (a.G == 1) request(yes{}, yes{});
+                else request(yes{}, no{});
+            } else {
+                if (a.G == 1) request(no{}, yes{});
+                else request(no{}, no{});
+            }
+            float sc[N], sh[N];
+            if (fuse_math) {
+#pragma unroll
+                for (int i = 0; i < N; ++i) { sc[i] = 1.0f; sh[i] = 0.0f; }
+                if (a.scale != nullptr) {
+                    load_f32_run<N>(a.scale, ch0 * (KC * KS) + sv * N, sc);
+                    load_f32_run<N>(a.shift, ch0 * (KC * KS) + sv * N, sh);
+                }
+            }
+            constexpr int D1 = D < 6 ? D : 6;
+            fill_ring(0, D1);
+            __builtin_amdgcn_sched_barrier(0);                 // (the scheduler would sink the requests to their first use)
+#pragma unroll
+            for (int u = 0; u < UO; ++u) {
+                uint4 w = tv[u];
+                if (fuse_math) {
+                    float f[N];
+                    unpack<T>(w, f);
+                    scale_shift_act<N>(f, sc, sh, a.act);
+                    w = pack<T>(f);
+                }
+                if (!((in >> u) & 1u)) w = make_uint4(0, 0, 0, 0);
+                if (sq0 + u * PPI < npix) *(uint4*)(lds + (sq0 + u * PPI) * a.ps + sv * 16) = w;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            fill_ring(D1, D);
+            __syncthreads();
+        }
+        for (int chunk = ch0; chunk < (ONCE ? ch0 + 1 : ch1); ++chunk) {
+            long ahead = 0;                                   // bytes to the chunk requested next
             if constexpr (PIPE) {
                 if (chunk != ch0) __syncthreads();
 #pragma unroll
@@ -702,8 +843,8 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                     if (sq0 + u * PPI < npix)
                         *(uint4*)(lds + (sq0 + u * PPI) * a.ps + sv * 16) = (inside >> u) & 1u ? nextv[u] : make_uint4(0, 0, 0, 0);
                 __syncthreads();
-                ahead = (long)(min(chunk + 1, ch1 - 1) - ch0) * (KC * KS * S);
-            } else {
+                ahead = (long)(chunk + 1 - ch0) * (KC * KS * S);
+            } else if constexpr (!ONCE) {
                 if (!SWAP || chunk != ch0) stage(chunk);
             }
             // A rows run AD steps ahead of their MFMAs: one step where a step holds four MFMAs or
@@ -721,9 +862,9 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 if constexpr (TM * TN < 4) __builtin_amdgcn_sched_barrier(0);
                 multiply(af[st % (AD + 1)], ring[st % D]);
                 const int nx = (st + D) % STEPS;              // the step that takes over this slot
-                fetch(ring[st % D], st + D < STEPS ? chunk : chunk + 1, nx / KW, nx % KW);
+                if (!ONCE || st + D < STEPS) fetch(ring[st % D], st + D < STEPS ? chunk : chunk + 1, nx / KW, nx % KW);
                 if constexpr (PIPE)
-                    if (st < U) nextv[st] = *(const uint4*)(src[st] + ahead);
+                    if (st < U) nextv[st] = *(const uint4*)(chunk + 1 < ch1 ? src[st] + ahead : (const char*)a.w);   // (as in fetch)
                 // nothing moves across a step boundary: left alone, the scheduler sinks every prefetch
                 // down to its first use to save registers and the ring collapses
                 __builtin_amdgcn_sched_barrier(0);
@@ -750,7 +891,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // split over workgroups, ragged channel counts - the accumulators go through LDS (the staged tile is
     // no longer needed) so that every thread then owns 8 consecutive output channels of one pixel.
     constexpr int N = Vec16<T>::N;
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+    constexpr int BM = WM * TM * TILE, BN = WN * TN * TILE;
     constexpr int RS = BN + 4;                                // fp32 row stride: pad keeps 16-byte alignment
     float* red = reinterpret_cast<float*>(lds);               // [WK][BM][RS]
     const bool vec_ok = emit_vec_ok<T>(a);
@@ -825,11 +966,11 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
+                for (int r = 0; r < (NARROW ? 4 : 16); ++r) {
                     // (swapped operands: the lane is the pixel and the registers are the channels)
-                    const int rr = 8 * (r >> 2) + 4 * half + (r & 3);
-                    const int m = (wm * TM + tm) * 32 + (SWAP ? l32 : rr);
-                    const int nn = (wn * TN + tn) * 32 + (SWAP ? rr : l32);
+                    const int rr = NARROW ? 4 * quarter + r : 8 * (r >> 2) + 4 * half + (r & 3);
+                    const int m = (wm * TM + tm) * TILE + (SWAP ? l32 : rr);
+                    const int nn = (wn * TN + tn) * TILE + (SWAP ? rr : lt);
                     red[(wk * BM + m) * RS + nn] = acc[tm][tn][r] + bias_v[tn];
                 }
         __syncthreads();
@@ -888,7 +1029,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     }
 }
 
-template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool PIPE = false>
+template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, int MODE = kPlain, bool NARROW = false>
 __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK > 4 ? 1 : 2)) void conv_kernel(ConvArgs a)
 {
     if constexpr (WK == 1 && TM * TN >= 4) {
@@ -902,7 +1043,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK > 4 ? 1 : 2)) void
                 for (int i = 0; i < a.stagger; ++i) __builtin_amdgcn_s_sleep(127);
         }
     }
-    conv_body<T, TM, TN, WM, WN, WK, KC, KK, false, PIPE>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+    conv_body<T, TM, TN, WM, WN, WK, KC, KK, false, MODE, NARROW>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Two independent calls in ONE launch: a 3x3 convolution and a 1x1 convolution that both take the
@@ -911,7 +1052,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK > 4 ? 1 : 2)) void
 // MARKED: the launch follows the marking pass directly, without the compaction pass in between (on
 // this part a dependent launch costs more than the compaction's work): every workgroup derives its
 // blocks from the flags (see conv_body).
-template <typename T, int KC, bool MARKED>
+template <typename T, int KC, bool MARKED, int MODE>
 __global__ __launch_bounds__(256, 2) void conv_pair_kernel(ConvArgs a, ConvArgs b, int wgs_a, FastDiv xa, FastDiv ya,
                                                            int ta, FastDiv xb, FastDiv yb, int tb)
 {
@@ -929,8 +1070,8 @@ __global__ __launch_bounds__(256, 2) void conv_pair_kernel(ConvArgs a, ConvArgs 
     const int tile = jt * 8 + (id & 7);
     if (tile >= nt) return;
     divmod(tile, ny, bz, by);
-    if (first) conv_body<T, 2, 1, 1, 1, 4, KC, 9, MARKED>(a, bx, by, bz);
-    else conv_body<T, 2, 1, 1, 1, 4, KC, 1, MARKED>(b, bx, by, bz);
+    if (first) conv_body<T, 2, 1, 1, 1, 4, KC, 9, MARKED, MODE>(a, bx, by, bz);
+    else conv_body<T, 2, 1, 1, 1, 4, KC, 1, MARKED, MODE>(b, bx, by, bz);
 }
 
 // v += the ksplit shares of one run of N channels, B of them in flight at a time (each batch is a
@@ -1352,20 +1493,20 @@ struct ConvPlan {
     int kc;   // K steps per staged channel chunk: 8, 4 or 1; 16 to 40 in the shapes that stage the whole of Cin
     int G, rows, trows, Cc, ps, bands, slabs, groups;
     int ksplit;   // workgroups that share one output patch along K (1 = no split)
-    bool pipe;    // the 64 x 32 shape with chunks requested ahead (see conv_body)
+    int mode;     // how the chunks are requested in the shapes whose waves split K (ChunkMode, see conv_body)
     bool few_rows_alone;   // a 1x1 call: launched by itself it goes to pointwise_kernel, 64 x 64 patches (see conv.hip)
     size_t lds;
 };
 
 // M x N per workgroup and whether the four waves split K
 struct CfgShape { int M, N, WK; };
-constexpr int kNumCfg = 4;    // shapes that compete by score; the last two are chosen by a rule of their own
-static const CfgShape kCfg[kNumCfg + 2] = {{128, 128, 1}, {128, 64, 1}, {64, 64, 1}, {64, 32, 4}, {64, 32, 8}, {32, 32, 8}};
+constexpr int kNumCfg = 4;    // shapes that compete by score; the others are chosen by a rule of their own
+static const CfgShape kCfg[kNumCfg + 3] = {{128, 128, 1}, {128, 64, 1}, {64, 64, 1}, {64, 32, 4}, {64, 32, 8}, {32, 32, 8}, {32, 16, 8}};
 
-template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, bool PIPE = false>
+template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, int MODE = kPlain, bool NARROW = false>
 int launch_cfg(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
 {
-    auto kern = conv_kernel<T, TM, TN, WM, WN, WK, KC, KK, PIPE>;
+    auto kern = conv_kernel<T, TM, TN, WM, WN, WK, KC, KK, MODE, NARROW>;
     if (p.lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)p.lds);
@@ -1392,14 +1533,29 @@ int launch_kc(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
         break;
     case 3:
         if constexpr ((KC == 4 || KC == 8) && KK == 9)
-            if (p.pipe) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, true>(a, p, st);
-        if constexpr (KC % 4 == 0 && (KC <= 8 || (KC == 20 && KK == 9))) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK>(a, p, st);
+            if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kAhead>(a, p, st);
+        if constexpr (KC % 4 == 0 && (KC <= 8 || (KC == 20 && KK == 9))) {
+            if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kOnce>(a, p, st);
+            return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK>(a, p, st);
+        }
         break;
     case 4:
-        if constexpr (KC % 8 == 0 && KC >= 16 && KK == 9) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK>(a, p, st);
+        if constexpr (KC % 8 == 0 && KC >= 16 && KK == 9) {
+            if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kOnce>(a, p, st);
+            return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK>(a, p, st);
+        }
+        break;
+    case 5:
+        if constexpr (KC % 8 == 0 && KC >= 16 && KK == 9) {
+            if (p.mode == kOnce) return launch_cfg<T, 1, 1, 1, 1, 8, KC, KK, kOnce>(a, p, st);
+            return launch_cfg<T, 1, 1, 1, 1, 8, KC, KK>(a, p, st);
+        }
         break;
     default:
-        if constexpr (KC % 8 == 0 && KC >= 16 && KK == 9) return launch_cfg<T, 1, 1, 1, 1, 8, KC, KK>(a, p, st);
+        if constexpr (KC % 16 == 0 && KC >= 16 && KK == 9 && sizeof(T) == 2) {
+            if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kOnce, true>(a, p, st);
+            if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kAhead, true>(a, p, st);
+        }
         break;
     }
     return fail(SIGE_ERR_UNSUPPORTED, "sige_conv: internal: shape %d without a matching chunk %d", p.cfg, KC);
@@ -1497,8 +1653,13 @@ int launch_pair(const ConvArgs& a, const ConvPlan& pa, const ConvArgs& b, const 
         SIGE_LAUNCH_CHECK("sige_fused_conv_pair");
         return (int)SIGE_OK;
     };
-    if (marked) return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, true>) : launch(conv_pair_kernel<T, 4, true>);
-    return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, false>) : launch(conv_pair_kernel<T, 4, false>);
+    const bool once = pa.mode == kOnce && pb.mode == kOnce;   // (both read the same number of channels in practice)
+    if (marked) {
+        if (once) return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, true, kOnce>) : launch(conv_pair_kernel<T, 4, true, kOnce>);
+        return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, true, kPlain>) : launch(conv_pair_kernel<T, 4, true, kPlain>);
+    }
+    if (once) return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, false, kOnce>) : launch(conv_pair_kernel<T, 4, false, kOnce>);
+    return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, false, kPlain>) : launch(conv_pair_kernel<T, 4, false, kPlain>);
 }
 
 // Re-lays an OIHW weight into the fragment order the kernels read.

@@ -1403,6 +1403,78 @@ def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, form, kn
         assert_close(got[0][1], oracle.select_blocks(act, np.full((Ho, Wo, Cout), 3.0), blocks.cpu().numpy(), b, b), td, "copy")
 
 
+@pytest.mark.parametrize("dtype,Cin,Cout,H,W,b,form,shape,kn", [
+    ("f16", 128, 96, 40, 44, 16, "silu", 3, dict(CONV_CFG=3, CONV_KC=8)),        # one chunk, arithmetic on the way in
+    ("f32", 32, 40, 21, 23, 6, "silu", 3, dict(CONV_CFG=3, CONV_KC=4)),          # ragged blocks and channels
+    ("bf16", 64, 48, 24, 20, 4, "copies", 3, dict(CONV_CFG=3, CONV_KC=4)),       # four blocks per workgroup
+    ("f16", 128, 64, 27, 29, 6, "1x1", 3, dict(CONV_CFG=3, CONV_KC=8)),
+    ("bf16", 320, 72, 20, 22, 8, "copies", 3, {}),                               # the whole of 320 channels
+    ("f16", 320, 64, 22, 26, 8, "up", 3, {}),
+    ("bf16", 640, 96, 24, 24, 8, "copies", 5, {}),                               # 32 rows, 640 channels
+    ("f32", 256, 64, 20, 20, 8, "", 5, {}),
+    ("f16", 512, 96, 48, 80, 16, "", 4, {}),                                     # 64 rows: too many workgroups for 32
+    ("f16", 256, 40, 19, 21, 8, "copies", 6, {}),                                # 32 x 16 patches, the last one half empty
+    ("bf16", 512, 64, 16, 16, 16, "", 6, {}),
+    ("bf16", 512, 64, 22, 26, 8, "up", 6, {}),
+    ("f16", 1024, 72, 15, 17, 8, "copies", 6, {}),                               # ... two chunks, the second requested ahead
+])
+def test_conv_chunk_requested_at_once(oracle, dtype, Cin, Cout, H, W, b, form, shape, kn):
+    """Shapes whose waves split K, one chunk per workgroup (or two in the 32 x 16 patches): tile and weights requested
+    together.  Against the oracle, with the plan's shape as named; where the plan without it (CONV_AHEAD=0) has the same
+    shape the sums have the same order: equal bit for bit."""
+    rng = np.random.default_rng(7 * Cin + Cout + H)
+    td = DT[dtype]
+    up, k, staged = int(form == "up"), 1 if form == "1x1" else 3, form == "silu"
+    x = torch.from_numpy(rng.standard_normal((H >> up, W >> up, Cin)).astype(np.float32)).to(td)
+    w, bias = inputs.conv_params(rng, Cout, Cin, k, td)
+    conv = SigeConv(dev(w), bias, H, W, b, 1, k // 2, up=up)
+    cache = torch.from_numpy(rng.standard_normal((H, W, Cout)).astype(np.float32)).to(td)
+    bl = BlockList(conv.g, "cuda").all_active()
+    n = conv.g.grid_blocks
+    pick = np.arange(n) if shape == 4 else np.unique(np.append(rng.permutation(n)[:max(2, n // 3)], n - 1))
+    n = len(pick)
+    blocks = bl.indices[torch.from_numpy(pick).cuda()].clone()
+    bl.indices.fill_(0)
+    bl.indices[:n].copy_(blocks)
+    bl.count.fill_(n)
+    bl.n_host = n
+    scale = shift = None
+    act = api.ACT_NONE
+    if staged:
+        scale, shift = (torch.from_numpy(rng.standard_normal(Cin).astype(np.float32)) for _ in range(2))
+        act = api.ACT_SILU
+    resid = torch.from_numpy(rng.standard_normal((H, W, Cout)).astype(np.float32)).to(td) if form == "copies" else None
+    asc, ash = torch.full((Cout,), 0.75, device="cuda"), torch.full((Cout,), -0.25, device="cuda")
+    kn = {**dict(CONV_POINTWISE=0), **kn}
+    got, shapes = [], []
+    for ahead in (-1, 0):
+        y = dev(cache).clone()
+        copy = torch.full((H, W, Cout), 3.0, dtype=td, device="cuda")
+        aos = api.act_out_array([(copy, asc, ash, api.ACT_SILU)]) if form == "copies" else None
+        with api.knobs(CONV_AHEAD=ahead, **kn):
+            shapes.append(api.sige_conv_plan(td, conv.g, Cin, Cout, n, staged_math=int(staged), up=up, workspace_bytes=0).shape)
+            conv.forward(dev(x), y, bl, Workspace("cuda"), scale=None if scale is None else dev(scale), split_k=False,
+                         shift=None if shift is None else dev(shift), act=act, fused=True,
+                         residual=None if resid is None else dev(resid), act_outs=aos)
+        got.append((y, copy))
+    assert shapes[0] == shape
+    if shapes[1] == shape:
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    xin = f64(x).repeat(2, axis=0).repeat(2, axis=1) if up else f64(x)
+    if staged:
+        v = xin * f64(scale) + f64(shift)
+        xin = round_to(v / (1.0 + np.exp(-v)), td)
+    want = oracle.conv2d(xin, f64(w), f64(bias), 1, k // 2) + (f64(resid) if resid is not None else 0)
+    want = oracle.select_blocks(want, f64(cache), blocks.cpu().numpy(), b, b)
+    for y, copy in got:
+        assert_close(y, want, td, "requested at once")
+        if form == "copies":
+            v = f64(y) * 0.75 - 0.25
+            v = oracle.select_blocks(v / (1.0 + np.exp(-v)), np.full(v.shape, 3.0), blocks.cpu().numpy(), b, b)
+            assert_close(copy, v, td, "activated copy")
+
+
+
 @pytest.mark.parametrize("dtype,Cin,Cout,b,n,kernel", [
     ("bf16", 320, 2560, 8, 10, 1),       # 400 patches of 64 x 64: beyond one per compute unit
     ("f16", 320, 2536, 5, 27, 1),        # 675 rows and a channel count that end inside a patch

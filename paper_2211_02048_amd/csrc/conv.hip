@@ -110,11 +110,12 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
     const bool force_split = force_split_v >= 0;
     // Few workgroups and a long K, nothing to compute while staging (no Scale+Shift, no activation):
     // 64 x 32 patches whose waves split K, with the whole of Cin (or half of it) staged at once -
-    // eight waves over 256, 512 or 640 channels, four over 320.  One kernel, no workspace; the waves'
+    // eight waves over 256, 512 or 640 channels, four over 320 (256 -> 256 at 64 x 64 on one / four / eight 16x16 blocks
+    // 9.2 / 9.2 / 9.3 us in two chunks requested ahead, 5.8 / 6.8 / 7.9 here).  One kernel, no workspace; the waves'
     // sums meet in LDS.  (With staged arithmetic the chunk would cost every workgroup many times the
     // activation work of the plain four-wave shape's.)
     if (g->k == 3 && g->block_w <= 64 &&
-        (force_whole || (!staged_math && !force && !force_kc && !force_split && Cin >= 20 * kstep))) {
+        (force_whole || (!staged_math && !force && !force_kc && !force_split && Cin >= (s == 2 ? 16 : 20) * kstep))) {
         ConvPlan q;
         q.ksplit = 1;
         const int M = 64, pbfull = g->block_h * g->block_w;
@@ -152,7 +153,7 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
             wgs4 = (long)q.groups * q.bands * q.slabs;
             // still at most 128 of them, half types: 16 output channels each (see NARROW in conv_kernels.h; 512 -> 512 at
             // 16 x 16 9.7 -> 7.7 us, at 8 x 8 10.1 -> 7.9), whose workgroups request everything ahead
-            if (s == 2 && wgs4 <= 128 && q.kc % 16 == 0 && !force_whole && knob(SIGE_KNOB_CONV_AHEAD) != 0 &&
+            if (s == 2 && wgs4 <= 128 && (q.kc == 32 || (q.kc == 16 && Cin == 16 * kstep)) && !force_whole && knob(SIGE_KNOB_CONV_AHEAD) != 0 &&
                 (long)q.trows * tw <= (long)once_vectors(q.kc, 1) * (512 / (2 * q.kc))) {
                 q.cfg = 6;
                 q.slabs = (Cout + 15) / 16;

@@ -538,8 +538,8 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     const int ntaps = KK ? KK : kk;
     uint4 ring[D][TN];
     auto fetch = [&](uint4 (&slot)[TN], int chunk, int tp, int kc) {
-        if constexpr (PIPE) {
-            // past this workgroup's last chunk every lane reads the same 16 bytes: one request, and the loads in flight stay a fixed number
+        if constexpr (NARROW) {
+            // past this workgroup's last chunk (one of two) every lane reads the same 16 bytes: one request, and the loads in flight stay a fixed number
             const uint4* src = chunk < ch1 ? wp[0] + ((long)tp * kcs + chunk * KC + kc * GW) * 64 : (const uint4*)a.w;
             slot[0] = *src;
         } else {
@@ -691,7 +691,10 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
 #pragma unroll
             for (int d = d0; d < d1; ++d) {
                 fetch(ring[d], ch0, d / KW, d % KW);
-                if constexpr (MODE != kPlain) __builtin_amdgcn_sched_barrier(0);   // in the order of the steps: loads return in issue order
+                // in the order of the steps: loads return in issue order, and left free the scheduler mixes them so that every
+                // chunk's first step waits for the whole ring (1280 -> 1280 on three 8x8 blocks 20.6 -> 19.6 us; with chunks of
+                // four K steps, whose ring is the chunk, it is the barriers that cost: 960 -> 320 on ten 17.5 -> 18.5)
+                if constexpr (ONCE || KC >= 8) __builtin_amdgcn_sched_barrier(0);
             }
         };
         if constexpr (MODE == kPlain) fill_ring(0, D);
@@ -843,7 +846,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                     if (sq0 + u * PPI < npix)
                         *(uint4*)(lds + (sq0 + u * PPI) * a.ps + sv * 16) = (inside >> u) & 1u ? nextv[u] : make_uint4(0, 0, 0, 0);
                 __syncthreads();
-                ahead = (long)(chunk + 1 - ch0) * (KC * KS * S);
+                ahead = (long)((NARROW ? chunk + 1 : min(chunk + 1, ch1 - 1)) - ch0) * (KC * KS * S);   // (the last one again at the end)
             } else if constexpr (!ONCE) {
                 if (!SWAP || chunk != ch0) stage(chunk);
             }
@@ -864,7 +867,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 const int nx = (st + D) % STEPS;              // the step that takes over this slot
                 if (!ONCE || st + D < STEPS) fetch(ring[st % D], st + D < STEPS ? chunk : chunk + 1, nx / KW, nx % KW);
                 if constexpr (PIPE)
-                    if (st < U) nextv[st] = *(const uint4*)(chunk + 1 < ch1 ? src[st] + ahead : (const char*)a.w);   // (as in fetch)
+                    if (st < U) nextv[st] = *(const uint4*)(!NARROW || chunk + 1 < ch1 ? src[st] + ahead : (const char*)a.w);   // (as in fetch)
                 // nothing moves across a step boundary: left alone, the scheduler sinks every prefetch
                 // down to its first use to save registers and the ring collapses
                 __builtin_amdgcn_sched_barrier(0);
@@ -1554,7 +1557,8 @@ int launch_kc(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
     default:
         if constexpr (KC % 16 == 0 && KC >= 16 && KK == 9 && sizeof(T) == 2) {
             if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kOnce, true>(a, p, st);
-            if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kAhead, true>(a, p, st);
+            if constexpr (KC == 32)
+                if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kAhead, true>(a, p, st);
         }
         break;
     }

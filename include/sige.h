@@ -466,7 +466,7 @@ int sige_version(void);
  *   CONV_POINTWISE     the few-row 1x1 kernel: 0 = never, 1 = 64x32, 2 = 64x64, 3 = 32x32 patches
  *   CONV_POINTWISE_W4  its four-wave variant for 64x64 patches: 0 = never, 1 = always
  *   CONV_PAIR_WGS      most workgroups up to which sige_fused_conv_pair shares one launch
- *   ATTN_WGS           workgroups the key split of sige_sparse_attn aims for
+ *   ATTN_WGS           workgroups the cut of sige_sparse_attn aims for
  *   DIFF_LOADS         16-byte loads per lane and tensor in flight in the difference kernel (1, 2, 4)
  *   DIFF_WGS           accepted and ignored (the difference kernel runs one step per wave)
  *   CONV_DIRECT        0: the shapes whose waves do not split K send their accumulators through LDS

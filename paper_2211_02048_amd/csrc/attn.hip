@@ -2,24 +2,21 @@
 // keys and values (Sec. 3.2 "Extension to attention layers", Fig. "sige-attention"):
 // the attention map is Nq x T instead of T x T.
 //
-// One wave owns 32 queries of one head and streams the keys in chunks of 32 * KT
-// (64 keys for head sizes up to 96, 32 beyond; small heads keep two waves per SIMD resident);
-// the next chunk's K and V rows travel from HBM to registers while the current one is
-// multiplied.  All
-// products run transposed so that everything belonging to a query stays in one lane
-// (pair): S^T = K Q^T leaves a query's 32 logits in the registers of lanes l and
+// One wave owns 32 queries of one head and streams its share of the keys in chunks of 32 * KT
+// (64 keys for head sizes up to 96, 32 beyond); the next chunk's K and V rows travel to registers
+// while the current one is multiplied.  All products run transposed so that everything belonging
+// to a query stays in one lane (pair): S^T = K Q^T leaves a query's 32 logits in the registers of lanes l and
 // l+32, the online softmax needs a single cross-lane exchange, the probabilities
 // feed the second MFMA (O^T = V^T P^T) straight from registers because the
 // contraction index may be permuted freely as long as V^T is read with the same
-// permutation, and the running rescale of O^T is lane-local.  K and V chunks are
-// staged in LDS once per workgroup (4 waves = 128 queries); V is transposed on the
-// way in, with an XOR swizzle on 4-key groups to keep the 2-byte stores off the same
-// banks.  When few queries are active the key range is split over workgroups and a
-// second small kernel merges the partial (max, sum, O) triples.  Single precision has a kernel of
+// permutation, and the running rescale of O^T is lane-local.  The waves of a workgroup share
+// 32 queries and split the keys; when few queries are active the key range is also split over
+// workgroups and a second small kernel merges the partial (max, sum, O) triples.  Single precision has a kernel of
 // its own further down (attn_f32_kernel).
 #include "common.h"
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace sige {
@@ -27,6 +24,9 @@ namespace sige {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 as_uint4(const u32x4& v) { return make_uint4(v.x, v.y, v.z, v.w); }
 
 template <typename T> struct Mma16;
 template <> struct Mma16<f16> {
@@ -80,110 +80,147 @@ struct AttnArgs {
     // block i / q_tpb, at row (y0 + py) * q_W + x0 + px of q (clamped into the q_H x q_W map)
     const int32_t* q_blocks;
     int q_tpb, q_bw, q_H, q_W;
+    FastDiv d_tpb, d_qbw, d_dvec, d_dq;   // divisors prepared on the host: q_tpb, q_bw, 16-byte vectors and quarters of a head's row
 };
 
 // 32-key tiles per chunk, by head size (DT = 32-wide tiles over d)
 constexpr int key_tiles(int DT) { return DT <= 3 ? 2 : 1; }
+// bytes between the V rows of a chunk in LDS: an odd multiple of 64, so that the eight keys of a transposed read fall on
+// different banks
+constexpr int v_row_bytes(int DT) { return 64 * (DT | 1); }
+// waves per workgroup, at most: what their sums take in LDS when they meet
+constexpr int max_waves(int DT) { return DT <= 4 ? 8 : 4; }
+// key groups of a workgroup whose four waves share their chunks
+constexpr int common_groups(int DT) { return DT <= 3 ? 2 : 1; }
 static int keys_per_chunk(int d, sige_dtype dt) { return dt == SIGE_F32 ? 32 : 32 * key_tiles((d + 31) / 32); }
 
 // DT = 32-wide tiles over d; ODD: d takes an odd number of 16-wide steps (d % 32 is 8 or 16), so the
 // last tile of V^T has spare rows.  One of them is then a row of ones: the second product sums the
 // probabilities of a query - exactly the rounded values that it multiplies V with - into that row of
 // O^T, the running rescale included, and the softmax spends no vector instruction on the denominator.
-// The softmax is what bounds this kernel (for d = 40 its vector instructions outweigh the matrix
+// The softmax is what bounds a wave (for d = 40 its vector instructions outweigh the matrix
 // instructions), so it is kept to a maximum, one fused multiply-add, one exponential and the rounding
 // per logit: logits are compared raw and scaled inside the exponent, keys past T are masked only in
 // the chunk that holds them, and the accumulators are rescaled only when some query's maximum moved.
-template <typename T, int DT, int ODD>
-__global__ __launch_bounds__(256, DT <= 3 ? 2 : 1) void attn_kernel(AttnArgs a)
+//
+// The waves of a workgroup are NK groups of NQ: a group takes every NK-th chunk of keys for 32 * NQ queries, and the groups' (maximum,
+// denominator, sums) meet in LDS at the end.  NQ = 4 (many queries): the group fetches K and V once for its four waves and passes
+// them through LDS, two barriers per chunk.  NQ = 1 (few queries, large heads): every wave for itself, K from memory straight into
+// the first product's operands, no barrier in the loop.  V goes into LDS row by row and out of it transposed (ds_read_b64_tr_b16).
+// One form alone, four waves on 128 queries and 2-byte stores to transpose V, left most compute units without work where
+// there were a few hundred queries, or needed many splits and the merge kernel behind them.  Before -> now, bf16, eight heads unless
+// said: 192 of 256 x 160 12.1 -> 10.3 us, 384 of 1024 x 80 16.0 -> 13.2, 1024 of 1024 x 80 22.9 -> 14.2, 96 of 4096 x 40 12.9 -> 11.2,
+// 672 of 8192 x 40 37.3 -> 33.5, 2240 of 4096 x 40 47.7 -> 42.7, 192 on 77 keys x 160 10.8 -> 7.6, 9216 of 9216 x 128 930 -> 780,
+// fp16 5000 of 9000 x 160 747 -> 553.
+template <typename T, int DT, int ODD, int NQ, int NK>
+__global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kernel(AttnArgs a)
 {
+    constexpr int NW = NQ * NK;
     constexpr int KT = key_tiles(DT);
     constexpr int KCH = 32 * KT;                   // keys per chunk
-    constexpr int VT_STRIDE = KCH * 2 + 8;         // bytes per row of the transposed V chunk (pad 8)
-    constexpr int DKMAX = 2 * DT;                  // 16-wide steps over d for S^T, at most
-    constexpr int DK = 2 * DT - ODD;               // ... and exactly
-    constexpr int NV = (KT * DT + 1) / 2;          // K (and V) vectors a thread stages per chunk, at most
+    constexpr int VROW = v_row_bytes(DT);
+    constexpr int DK = 2 * DT - ODD;               // 16-wide steps over d for S^T
+    constexpr int GT = 64 * NQ;                    // threads that have a chunk in common
+    constexpr int NV = (KCH * (4 * DT - 2 * ODD) + GT - 1) / GT;   // V (and K) vectors a thread stages per chunk, at most
     extern __shared__ uint4 lds4[];
     char* lds = reinterpret_cast<char*>(lds4);
     const int d = a.d;
-    const int k_stride = d * 2 + 16;               // bytes per staged K row
-    char* ks = lds;                                // [KCH][k_stride]
-    char* vt = lds + KCH * k_stride;               // [DT*32][VT_STRIDE]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wq = wave % NQ, wk = wave / NQ, gt = wq * 64 + lane;
     const int half = lane >> 5, l32 = lane & 31;
     const int head = blockIdx.y;
-    const int qi = (blockIdx.x * 4 + wave) * 32 + l32;
+    const int q0 = (blockIdx.x * NQ + wq) * 32, qi = q0 + l32;
     const bool q_ok = qi < a.Nq;
-    const int dvec = d / 8;                        // 16-byte vectors per row
+    const int dvec = d / 8, nvec = KCH * dvec;     // 16-byte vectors per row, per chunk
+    const unsigned kv2 = (unsigned)a.kv_ld * 2u;   // bytes between keys
+    const int k_stride = d * 2 + 16;               // bytes per K row in LDS (NQ > 1)
+    const int vs0 = wk * (KCH * VROW);             // this group's V rows, then the groups' K rows
+    char* const vs = lds + vs0;
+    char* const ks = lds + NK * KCH * VROW + wk * (KCH * k_stride);
 
     const int chunks_total = (a.T + KCH - 1) / KCH;
     const int c_begin = blockIdx.z * a.chunks_per_split;
     const int c_end = min(c_begin + a.chunks_per_split, chunks_total);
+    const char* const kb = (const char*)a.k + (long)head * d * 2;
+    const char* const vb = (const char*)a.v + (long)head * d * 2;
+
+    // The vectors of a chunk this lane fetches: of K, row l32 (and l32 + 32) at the 16 bytes of its half in every step - the last
+    // step's upper half may lie past d: the row's first bytes instead, made zero below -; of V, the vectors lane, lane + 64, ...
+    // (past the chunk's last one: that one again, not stored).
+    const bool k_tail = ODD && 16 * (DK - 1) + 8 * half >= d;
+    unsigned koff[KT], klast[KT], voff[NV];
+    int vkey[NV], vdst[NV];
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) koff[kt] = (unsigned)(kt * 32 + l32) * kv2 + half * 16;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) {
+        int dv;
+        divmod(min(gt + GT * u, nvec - 1), a.d_dvec, vkey[u], dv);
+        voff[u] = (unsigned)vkey[u] * kv2 + dv * 16;
+        vdst[u] = vkey[u] * VROW + dv * 16;
+    }
+    u32x4 kreg[NQ == 1 ? KT * DK : NV], vreg[NV];                  // (native vectors: arrays of structs end up in scratch memory)
+    auto fetch = [&](int c) {
+        const int t0 = c * KCH;
+        if (t0 + KCH > a.T) {                      // the chunk that holds the end: keys past it read the last key's rows
+            const int last = a.T - 1 - t0;
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) koff[kt] = (unsigned)min(kt * 32 + l32, last) * kv2 + half * 16;
+#pragma unroll
+            for (int u = 0; u < NV; ++u) voff[u] += (unsigned)(min(vkey[u], last) - vkey[u]) * kv2;
+        }
+        const char* const kc = kb + (long)t0 * kv2;
+        const char* const vc = vb + (long)t0 * kv2;
+        if constexpr (NQ == 1) {
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt) {
+                klast[kt] = k_tail ? koff[kt] - half * 16 : koff[kt] + 32 * (DK - 1);
+#pragma unroll
+                for (int s = 0; s < DK; ++s) kreg[kt * DK + s] = *(const u32x4*)(kc + (s == DK - 1 ? klast[kt] : koff[kt] + 32 * s));
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < NV; ++u) kreg[u] = *(const u32x4*)(kc + voff[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < NV; ++u) vreg[u] = *(const u32x4*)(vc + voff[u]);
+    };
+    int c = c_begin + wk;
+    if (c < c_end) fetch(c);
 
     // Q fragments (B operand of S^T = K Q^T): 8 consecutive d values of this lane's query
-    uint4 qf[DKMAX];
+    u32x4 qf[DK];
     long qrow = qi;
     if (a.q_blocks != nullptr && q_ok) {
-        const int b = qi / a.q_tpb, p = qi - b * a.q_tpb;
-        const int py = p / a.q_bw, px = p - py * a.q_bw;
+        int b, p, py, px;
+        divmod(qi, a.d_tpb, b, p);
+        divmod(p, a.d_qbw, py, px);
         const int y0 = a.q_blocks[2 * b], x0 = a.q_blocks[2 * b + 1];
         qrow = (long)min(max(y0 + py, 0), a.q_H - 1) * a.q_W + min(max(x0 + px, 0), a.q_W - 1);
     }
 #pragma unroll
-    for (int s = 0; s < DKMAX; ++s) {
+    for (int s = 0; s < DK; ++s) {
         const int dd = 16 * s + 8 * half;
-        qf[s] = make_uint4(0, 0, 0, 0);
+        qf[s] = u32x4{0u, 0u, 0u, 0u};
         if (q_ok && dd < d)
-            qf[s] = *(const uint4*)((const char*)a.q + (qrow * a.q_ld + head * d + dd) * 2);
+            qf[s] = *(const u32x4*)((const char*)a.q + (qrow * a.q_ld + head * d + dd) * 2);
     }
-    // rows d .. DT*32 of V^T never receive data: zero them once (row d: ones, see above); likewise the
-    // 16 bytes behind the d values of every staged K row, which the last 16-wide step reads when d is
-    // not a multiple of 16
-    constexpr uint32_t ONE2 = std::is_same<T, bf16>::value ? 0x3f803f80u : 0x3c003c00u;
-    for (int j = tid; j < (DT * 32 - d) * (VT_STRIDE / 4); j += 256)
-        *(uint32_t*)(vt + d * VT_STRIDE + j * 4) = (ODD && j < KCH / 2) ? ONE2 : 0u;
-    for (int j = tid; j < KCH; j += 256) *(uint4*)(ks + j * k_stride + d * 2) = make_uint4(0, 0, 0, 0);
-
-    // The vectors of a chunk this thread stages: (key, 16-byte group of d), the same for every chunk.
-    int skey[NV], sdv[NV];
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-        const int j = tid + u * 256;
-        skey[u] = j < KCH * dvec ? j / dvec : -1;
-        sdv[u] = j < KCH * dvec ? j - skey[u] * dvec : 0;
+    // columns d .. DT*32 of the wave's V rows never receive data: zero them once (column d: ones, see above)
+    constexpr uint32_t ONE = std::is_same<T, bf16>::value ? 0x3f80u : 0x3c00u;
+    {
+        const int pad = 4 * DT - dvec;             // 16-byte vectors per row, at most 3
+        for (int j = gt; j < KCH * 4; j += GT)
+            if ((j & 3) < pad)
+                *(uint4*)(vs + (j >> 2) * VROW + (dvec + (j & 3)) * 16) = make_uint4(ODD && (j & 3) == 0 ? ONE : 0u, 0, 0, 0);
     }
-    uint4 kreg[NV], vreg[NV];
-    // HBM -> registers; keys past the end read the last key's row (a valid address) and are zeroed
-    // when they are written to LDS
-    auto fetch = [&](int c) {
-        const int t0 = c * KCH;
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            if (skey[u] < 0) continue;
-            const long off = ((long)min(t0 + skey[u], a.T - 1) * a.kv_ld + head * d + sdv[u] * 8) * 2;
-            kreg[u] = *(const uint4*)((const char*)a.k + off);
-            vreg[u] = *(const uint4*)((const char*)a.v + off);
-        }
-    };
-    // registers -> LDS: K rows as they are, V transposed
-    auto commit = [&]() {
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            if (skey[u] < 0) continue;
-            const int key = skey[u], dv = sdv[u];
-            // (keys past the end hold a copy of the last key's rows: their logits are masked, so their
-            // probabilities are exactly zero)
-            const uint4 kv = kreg[u], vv = vreg[u];
-            *(uint4*)(ks + key * k_stride + dv * 16) = kv;
-            // element e of this vector is row dv*8+e of V^T; the index of the 4-key group is swizzled
-            // by dv in its low three bits
-            const int col = ((((key >> 2) ^ (dv & 7)) << 2) | (key & 3)) * 2;
-            union { uint4 u4; uint16_t h[8]; } x;
-            x.u4 = vv;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) *(uint16_t*)(vt + (dv * 8 + e) * VT_STRIDE + col) = x.h[e];
-        }
+    // where this lane's share of a transposed read starts: four lanes take the 16 columns of one key, four keys per 16 lanes,
+    // lane i of the 16 receives column i of the four keys
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const int tr = vs0 + (4 * half + ((lane & 15) >> 2)) * VROW + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    auto read_v = [&](int key, int nt) {
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(__attribute__((address_space(3))) char*)(lds + tr + key * VROW + nt * 64));
     };
 
     f32x16 oacc[DT];
@@ -193,14 +230,33 @@ __global__ __launch_bounds__(256, DT <= 3 ? 2 : 1) void attn_kernel(AttnArgs a)
         for (int r = 0; r < 16; ++r) oacc[nt][r] = 0.0f;
     float m_run = -INFINITY, l_run = 0.0f;
 
-    if (c_begin < c_end) fetch(c_begin);
-    for (int c = c_begin; c < c_end; ++c) {
+    if constexpr (NQ > 1) {                        // the 16 bytes behind the d values of every K row, which the last step reads when d % 16 is 8
+        for (int j = gt; j < KCH; j += GT) *(uint4*)(ks + j * k_stride + d * 2) = make_uint4(0, 0, 0, 0);
+    }
+    for (; c - wk < c_end; c += NK) {              // (as often in every group: the barriers are the workgroup's)
         const int t0 = c * KCH;
-        __syncthreads();  // previous chunk fully consumed
-        commit();
-        __syncthreads();
-        if (c + 1 < c_end) fetch(c + 1);          // in flight while this chunk is multiplied
-        __builtin_amdgcn_sched_barrier(0);        // (kept above the MFMAs: the scheduler would sink the loads)
+        const bool mine = c < c_end && (NQ == 1 || q0 < a.Nq);
+        if constexpr (NQ > 1) {
+            __syncthreads();                       // the last chunk's rows have been read
+            if (c < c_end) {
+#pragma unroll
+                for (int u = 0; u < NV; ++u)
+                    if (gt + GT * u < nvec) *(u32x4*)(ks + vdst[u] - vkey[u] * (VROW - k_stride)) = kreg[u];
+            }
+        }
+        if (NQ == 1 && !mine) break;
+        // V rows as they are (NQ == 1: LDS operations of a wave stay in order, the last chunk's reads are behind it)
+        if (NQ == 1 || c < c_end) {
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                if (gt + GT * u < nvec) *(u32x4*)(vs + vdst[u]) = vreg[u];
+        }
+        if constexpr (NQ > 1) {
+            __syncthreads();
+            if (c + NK < c_end) fetch(c + NK);     // in flight while this chunk is multiplied
+            __builtin_amdgcn_sched_barrier(0);
+            if (!mine) continue;
+        }
 
         // S^T chunk: rows = keys (KT tiles of 32), cols = queries
         f32x16 sacc[KT];
@@ -208,15 +264,23 @@ __global__ __launch_bounds__(256, DT <= 3 ? 2 : 1) void attn_kernel(AttnArgs a)
         for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) sacc[kt][r] = 0.0f;
-            // all K fragments of the tile first (independent LDS reads, one latency), then the MFMAs:
-            // read one by one, each in front of its MFMA, they cost a round trip to LDS per step
-            uint4 kf[DK];
+            if constexpr (NQ == 1) {
+                if (k_tail) kreg[kt * DK + DK - 1] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int s = 0; s < DK; ++s)
-                kf[s] = *(const uint4*)(ks + (kt * 32 + l32) * k_stride + (16 * s + 8 * half) * 2);
+                for (int s = 0; s < DK; ++s) Mma16<T>::run(as_uint4(kreg[kt * DK + s]), as_uint4(qf[s]), sacc[kt]);
+            } else {
+                // all K fragments of the tile first (independent LDS reads, one latency), then the MFMAs
+                u32x4 kf[DK];
 #pragma unroll
-            for (int s = 0; s < DK; ++s) Mma16<T>::run(kf[s], qf[s], sacc[kt]);
+                for (int s = 0; s < DK; ++s)
+                    kf[s] = *(const u32x4*)(ks + (kt * 32 + l32) * k_stride + (16 * s + 8 * half) * 2);
+#pragma unroll
+                for (int s = 0; s < DK; ++s) Mma16<T>::run(as_uint4(kf[s]), as_uint4(qf[s]), sacc[kt]);
+            }
         }
+        if constexpr (NQ == 1)
+            if (c + NK < c_end) fetch(c + NK);     // in flight during the softmax and the second product
+        __builtin_amdgcn_sched_barrier(0);         // (kept above them: the scheduler would sink the loads)
         // online softmax; of tile kt this lane holds keys 8*(r/4) + 4*half + r%4 of its query
         if (t0 + KCH > a.T) {                      // the chunk that holds the end of the keys
 #pragma unroll
@@ -285,20 +349,19 @@ __global__ __launch_bounds__(256, DT <= 3 ? 2 : 1) void attn_kernel(AttnArgs a)
                     }
                 }
                 const uint4 pf = make_uint4(ph[0], ph[1], ph[2], ph[3]);
-                uint2 lo[DT], hi[DT];                        // likewise: the V^T fragments of all tiles, then the MFMAs
+                s16x4 lo[DT], hi[DT];                        // the V^T fragments of all tiles, then the MFMAs
 #pragma unroll
                 for (int nt = 0; nt < DT; ++nt) {
-                    const int row = nt * 32 + l32;
-                    const int sw = (row >> 3) & 7;
-                    const int g_lo = kt * 8 + ((4 * s + half) ^ sw), g_hi = kt * 8 + ((4 * s + 2 + half) ^ sw);
-                    lo[nt] = *(const uint2*)(vt + row * VT_STRIDE + g_lo * 8);
-                    hi[nt] = *(const uint2*)(vt + row * VT_STRIDE + g_hi * 8);
+                    lo[nt] = read_v(kt * 32 + 16 * s, nt);
+                    hi[nt] = read_v(kt * 32 + 16 * s + 8, nt);
                 }
 #pragma unroll
                 for (int nt = 0; nt < DT; ++nt) {
-                    const uint4 vf = make_uint4(lo[nt].x, lo[nt].y, hi[nt].x, hi[nt].y);
-                    Mma16<T>::run(vf, pf, oacc[nt]);
-                    if constexpr (TWO) Mma16<T>::run(vf, make_uint4(pl[0], pl[1], pl[2], pl[3]), oacc[nt]);
+                    union { s16x4 h[2]; uint4 u; } vf;
+                    vf.h[0] = lo[nt];
+                    vf.h[1] = hi[nt];
+                    Mma16<T>::run(vf.u, pf, oacc[nt]);
+                    if constexpr (TWO) Mma16<T>::run(vf.u, make_uint4(pl[0], pl[1], pl[2], pl[3]), oacc[nt]);
                 }
             }
         l_run += lsum;
@@ -312,33 +375,81 @@ __global__ __launch_bounds__(256, DT <= 3 ? 2 : 1) void attn_kernel(AttnArgs a)
     } else {
         l_tot = l_run + __shfl_xor(l_run, 32);
     }
-    if (!q_ok) return;
-    if (a.splits == 1) {
+    if constexpr (NK == 1) {                       // no other wave has keys of these queries: straight from the registers
+        if (!q_ok) return;
         const float inv = 1.0f / l_tot;
+        float* const w = a.ws + (((long)blockIdx.z * a.heads + head) * a.Nq + qi) * (d + 4);
+        if (a.splits > 1 && half == 0) *(float2*)(w + d) = make_float2(m_run, l_tot);
 #pragma unroll
         for (int nt = 0; nt < DT; ++nt)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
                 const int dd = nt * 32 + 8 * rq + 4 * half;
-                if (dd < d) {
+                if (dd >= d) continue;
+                if (a.splits == 1) {
                     union { uint2 u; T h[4]; } x;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) x.h[e] = from_f32<T>(oacc[nt][4 * rq + e] * inv);
                     *(uint2*)((char*)a.o + ((long)qi * a.o_ld + head * d + dd) * 2) = x.u;
+                } else {
+                    *(float4*)(w + dd) = make_float4(oacc[nt][4 * rq], oacc[nt][4 * rq + 1], oacc[nt][4 * rq + 2],
+                                                     oacc[nt][4 * rq + 3]);
                 }
             }
-    } else {
-        float* w = a.ws + (((long)blockIdx.z * a.heads + head) * a.Nq + qi) * (d + 4);
-        if (half == 0) *(float2*)(w + d) = make_float2(m_run, l_tot);
+        return;
+    }
+    // the waves' shares of the keys, brought to a common maximum and added in wave order
+    float* const comb = reinterpret_cast<float*>(lds);       // [NK][32 * NQ queries][d sums, maximum, denominator, 2 unused]
+    const int cs = d + 4;
+    __syncthreads();                                         // (V rows no longer needed)
+    {
+        float* const mine = comb + ((wk * NQ + wq) * 32 + l32) * cs;
+        if (half == 0) *(float2*)(mine + d) = make_float2(m_run, l_tot);
 #pragma unroll
         for (int nt = 0; nt < DT; ++nt)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
                 const int dd = nt * 32 + 8 * rq + 4 * half;
                 if (dd < d)
-                    *(float4*)(w + dd) = make_float4(oacc[nt][4 * rq], oacc[nt][4 * rq + 1], oacc[nt][4 * rq + 2],
-                                                     oacc[nt][4 * rq + 3]);
+                    *(float4*)(mine + dd) = make_float4(oacc[nt][4 * rq], oacc[nt][4 * rq + 1], oacc[nt][4 * rq + 2],
+                                                        oacc[nt][4 * rq + 3]);
             }
+    }
+    __syncthreads();
+    const int dq = d >> 2;
+    for (int e = tid; e < 32 * NQ * dq; e += 64 * NW) {
+        int q, g;
+        divmod(e, a.d_dq, q, g);
+        const int qq = blockIdx.x * (32 * NQ) + q;
+        if (qq >= a.Nq) break;
+        const float* const src = comb + q * cs;
+        float m = -INFINITY;
+        float2 ml[NK];
+#pragma unroll
+        for (int w = 0; w < NK; ++w) {
+            ml[w] = *(const float2*)(src + w * (32 * NQ) * cs + d);
+            m = fmaxf(m, ml[w].x);
+        }
+        float den = 0.0f;
+        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < NK; ++w) {
+            const float4 v = *(const float4*)(src + w * (32 * NQ) * cs + 4 * g);
+            const float f = __builtin_amdgcn_exp2f(ml[w].x - m);     // a wave without keys: exp2(-inf) = 0
+            num.x += v.x * f; num.y += v.y * f; num.z += v.z * f; num.w += v.w * f;
+            den += ml[w].y * f;
+        }
+        if (a.splits == 1) {
+            const float inv = 1.0f / den;
+            union { uint2 u; T h[4]; } x;
+            x.h[0] = from_f32<T>(num.x * inv); x.h[1] = from_f32<T>(num.y * inv);
+            x.h[2] = from_f32<T>(num.z * inv); x.h[3] = from_f32<T>(num.w * inv);
+            *(uint2*)((char*)a.o + ((long)qq * a.o_ld + head * d + 4 * g) * 2) = x.u;
+        } else {
+            float* const w = a.ws + (((long)blockIdx.z * a.heads + head) * a.Nq + qq) * cs;
+            if (g == 0) *(float2*)(w + d) = make_float2(m, den);
+            *(float4*)(w + 4 * g) = num;
+        }
     }
 }
 
@@ -598,56 +709,105 @@ static int launch_merge(const AttnArgs& a, hipStream_t st)
     return SIGE_OK;
 }
 
-// Number of key splits: a workgroup walks through its key chunks one after the other and each costs
-// a staging round trip, so few queries are spread over about two workgroups per compute unit (more
-// splits cost the merge kernel more than they save: measured at 64 to 1280 queries), at least 2
-// chunks each.
-static int pick_splits(int Nq, int T, int heads, int d, sige_dtype dt)
+// How a call is cut.  Single precision: a workgroup (128 queries) walks through its key chunks one after the other and each
+// costs a staging round trip, so few queries are spread over about two workgroups per compute unit (more
+// splits cost the merge kernel more than they save: measured at 64 to 1280 queries), at least 2 chunks each.
+// Half types: the cheapest of three forms and their splits over workgroups by a model of measured times (24 calls of 24 to 9216
+// queries on 77 to 9216 keys, one head to eight, each form with up to twelve splits; the choice is within 5 % of the best of them but
+// for 4096 x 4096 of 40: 69 against 62 us).  What it trades: four waves on the same chunks fetch them once, waves with chunks of their
+// own have no barriers and need no merge kernel (5 us with its launch, and 0.4 us per megabyte of partial sums) where a call has
+// enough queries to fill the chip.
+struct AttnForm { int nq, nk, splits; };           // waves with the same chunks, key groups, splits over workgroups
+static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt)
 {
     const int KCH = keys_per_chunk(d, dt);
-    const long base = (long)heads * ((Nq + 127) / 128);
     const int chunks = (T + KCH - 1) / KCH;
     const int target = knob(SIGE_KNOB_ATTN_WGS);            // workgroups to aim for
-    long want = ((target >= 0 ? target : 512) + base - 1) / base;
-    long cap = chunks / 2;
-    if (want > cap) want = cap;
-    if (want > 64) want = 64;
-    if (want < 1) want = 1;
-    const int per = (int)((chunks + want - 1) / want);
-    return (chunks + per - 1) / per;
+    AttnForm f = {4, 1, 1};
+    if (dt == SIGE_F32) {
+        const long base = (long)heads * ((Nq + 127) / 128);
+        long want = ((target >= 0 ? target : 512) + base - 1) / base;
+        long cap = chunks / 2;
+        if (want > cap) want = cap;
+        if (want > 64) want = 64;
+        if (want < 1) want = 1;
+        const int per = (int)((chunks + want - 1) / want);
+        f.splits = (chunks + per - 1) / per;
+        return f;
+    }
+    // microseconds a workgroup takes beside its chunks, and per chunk of a wave, by 32-wide tiles of a head and form (four waves with
+    // the same chunks; one wave each, four of them; eight)
+    static const double fixed_us[9][3] = {{}, {4, 4, 4}, {3, 5, 5}, {5, 6.5, 6.5}, {7, 6.5, 6.5}, {7, 7.5, 0}, {7.5, 8, 0}, {}, {8, 9, 0}};
+    static const double chunk_us[9][3] = {{}, {1.2, 0.85, 1.3}, {2.0, 1.35, 2.75}, {2.35, 2.2, 3.5}, {1.2, 1.28, 2.3}, {1.56, 1.5, 0}, {1.9, 2.5, 0},
+                                          {}, {2.6, 5.5, 0}};
+    const int DT = (d + 31) / 32 == 7 ? 8 : (d + 31) / 32;
+    double best_us = 1e30;
+    const bool odd = ((d + 15) / 16) & 1;
+    // (eight waves on heads of 88 or 96 do not have the registers)
+    for (int form = 0; form < (max_waves(DT) == 8 && (DT != 3 || odd) ? 3 : 2); ++form) {
+        const AttnForm g = form == 0 ? AttnForm{4, common_groups(DT), 1} : AttnForm{1, form == 1 ? 4 : 8, 1};
+        const long base = (long)heads * ((Nq + 32 * g.nq - 1) / (32 * g.nq));
+        const bool two = form == 0 && (DT == 1 || (DT == 2 && odd));     // registers for two workgroups per compute unit
+        for (int z = 1; z <= 64 && (z == 1 || z * g.nk <= chunks); ++z) {
+            const int per = (chunks + z - 1) / z, real = (chunks + per - 1) / per;
+            const long on_one = (base * real + 255) / 256;      // workgroups of the fullest compute unit
+            const double chunk = (per + g.nk - 1) / g.nk * chunk_us[DT][form];
+            const double us = two ? on_one / 2 * (fixed_us[DT][form] + 1.7 * chunk) + on_one % 2 * (fixed_us[DT][form] + chunk)
+                                  : on_one * (fixed_us[DT][form] + chunk);
+            const double merge = real == 1 ? 0.0 : (real > 16 ? 7.0 : 5.0) + 1.6e-6 * real * heads * Nq * (d + 4);
+            const double cost = target >= 0 ? std::abs(target - (double)base * real) : us + merge;
+            if (cost < best_us) { best_us = cost; f = g; f.splits = real; }
+        }
+    }
+    return f;
 }
 
-template <typename T, int DT>
+template <typename T, int DT, int NQ, int NK>
 static int launch_attn_dt(const AttnArgs& a, hipStream_t st)
 {
     constexpr int KCH = 32 * key_tiles(DT);
-    const size_t lds = (size_t)KCH * (a.d * 2 + 16) + (size_t)DT * 32 * (KCH * 2 + 8);
-    dim3 grid((a.Nq + 127) / 128, a.heads, a.splits);
+    const size_t lds = std::max((size_t)NK * KCH * (v_row_bytes(DT) + (NQ > 1 ? a.d * 2 + 16 : 0)),
+                                NK == 1 ? 0 : (size_t)NK * NQ * 32 * (a.d + 4) * sizeof(float));
+    dim3 grid((a.Nq + 32 * NQ - 1) / (32 * NQ), a.heads, a.splits);
     const bool odd = ((a.d + 15) / 16) & 1;        // d % 32 is 8 or 16
-    auto kern = odd ? attn_kernel<T, DT, 1> : attn_kernel<T, DT, 0>;
+    auto kern = attn_kernel<T, DT, 1, NQ, NK>;
+    if constexpr (DT != 3 || NK != 8) {
+        if (!odd) kern = attn_kernel<T, DT, 0, NQ, NK>;
+    } else {
+        SIGE_REQUIRE(odd, SIGE_ERR_UNSUPPORTED, "sige_sparse_attn: internal: eight waves on heads of %d", a.d);
+    }
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         SIGE_REQUIRE(e == hipSuccess, SIGE_ERR_HIP, "sige_sparse_attn: cannot reserve %zu bytes of LDS: %s", lds,
                      hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * NQ * NK), lds, st, a);
     SIGE_LAUNCH_CHECK("sige_sparse_attn");
     if (a.splits > 1) return launch_merge<T>(a, st);
     return SIGE_OK;
 }
 
+template <typename T, int DT>
+static int launch_attn_form(const AttnArgs& a, const AttnForm& f, hipStream_t st)
+{
+    if (f.nq == 4) return launch_attn_dt<T, DT, 4, common_groups(DT)>(a, st);
+    if constexpr (max_waves(DT) == 8)
+        if (f.nk == 8) return launch_attn_dt<T, DT, 1, 8>(a, st);
+    return launch_attn_dt<T, DT, 1, 4>(a, st);
+}
+
 template <typename T>
-static int launch_attn(const AttnArgs& a, hipStream_t st)
+static int launch_attn(const AttnArgs& a, const AttnForm& f, hipStream_t st)
 {
     const int dt = (a.d + 31) / 32;
     switch (dt) {
-    case 1: return launch_attn_dt<T, 1>(a, st);
-    case 2: return launch_attn_dt<T, 2>(a, st);
-    case 3: return launch_attn_dt<T, 3>(a, st);
-    case 4: return launch_attn_dt<T, 4>(a, st);
-    case 5: return launch_attn_dt<T, 5>(a, st);
-    case 6: return launch_attn_dt<T, 6>(a, st);
-    default: return launch_attn_dt<T, 8>(a, st);
+    case 1: return launch_attn_form<T, 1>(a, f, st);
+    case 2: return launch_attn_form<T, 2>(a, f, st);
+    case 3: return launch_attn_form<T, 3>(a, f, st);
+    case 4: return launch_attn_form<T, 4>(a, f, st);
+    case 5: return launch_attn_form<T, 5>(a, f, st);
+    case 6: return launch_attn_form<T, 6>(a, f, st);
+    default: return launch_attn_form<T, 8>(a, f, st);
     }
 }
 
@@ -691,7 +851,7 @@ extern "C" size_t sige_sparse_attn_workspace_bytes(int32_t Nq, int32_t T, int32_
 {
     if (Nq <= 0 || T <= 0 || heads <= 0 || d <= 0) return 0;
     // the larger of what the half-precision and the single-precision kernels would use
-    const int splits = std::max(pick_splits(Nq, T, heads, d, SIGE_F16), pick_splits(Nq, T, heads, d, SIGE_F32));
+    const int splits = std::max(plan_attn(Nq, T, heads, d, SIGE_F16).splits, plan_attn(Nq, T, heads, d, SIGE_F32).splits);
     if (splits <= 1) return 0;
     return (size_t)splits * heads * Nq * (d + 4) * sizeof(float);
 }
@@ -717,11 +877,13 @@ static int attn_entry(const char* who, AttnArgs& a, const void* q, int32_t q_ld,
     a.q = q; a.k = k; a.v = v; a.o = o; a.ws = (float*)workspace;
     a.q_ld = q_ld; a.kv_ld = kv_ld; a.o_ld = o_ld;
     a.Nq = Nq; a.T = T; a.heads = heads; a.d = d;
+    a.d_tpb = fast_div(a.q_tpb); a.d_qbw = fast_div(a.q_bw); a.d_dvec = fast_div(std::max(d / 8, 1)); a.d_dq = fast_div(d / 4);
     SIGE_REQUIRE(scale >= 0.0f, SIGE_ERR_UNSUPPORTED, "%s: the scale must not be negative", who);
     a.scale_log2e = scale * 1.4426950408889634f;
     const int KCH = keys_per_chunk(d, dt);
     const int chunks = (T + KCH - 1) / KCH;
-    int splits = pick_splits(Nq, T, heads, d, dt);
+    const AttnForm f = plan_attn(Nq, T, heads, d, dt);
+    int splits = f.splits;
     if (splits > 1 && (workspace == nullptr ||
                        workspace_bytes < (size_t)splits * heads * Nq * (d + 4) * sizeof(float) ||
                        (reinterpret_cast<uintptr_t>(workspace) & 15u)))
@@ -730,7 +892,7 @@ static int attn_entry(const char* who, AttnArgs& a, const void* q, int32_t q_ld,
     a.splits = (chunks + a.chunks_per_split - 1) / a.chunks_per_split;
     hipStream_t st = (hipStream_t)stream;
     if (dt == SIGE_F32) return launch_attn_f32(a, st);
-    return dt == SIGE_F16 ? launch_attn<f16>(a, st) : launch_attn<bf16>(a, st);
+    return dt == SIGE_F16 ? launch_attn<f16>(a, f, st) : launch_attn<bf16>(a, f, st);
 }
 
 extern "C" int sige_sparse_attn(const void* q, int32_t q_ld, const void* k, const void* v, int32_t kv_ld,

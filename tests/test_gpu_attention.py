@@ -58,6 +58,34 @@ def test_sparse_attention_matches_oracle(oracle, T, heads, d, n_q, dtype):
         assert splits == [True, False]  # the small-query cases do exercise the split + merge path
 
 
+@pytest.mark.parametrize("T,heads,d,n_q,dtype", [
+    (65, 1, 40, 33, "bf16"),        # one key in the second chunk, one query in the second tile
+    (257, 2, 80, 65, "bf16"),       # five chunks for eight waves, the last one of one key
+    (1500, 1, 72, 1500, "f16"),     # a ragged last chunk, several chunks per wave
+    (320, 3, 160, 40, "bf16"),      # one wave each, four waves, heads of five tiles
+    (700, 4, 96, 130, "f16"),       # heads without a spare row in the last tile, splits
+    (3000, 1, 40, 700, "bf16"),     # chunks in common to four waves: groups with unequal numbers of them, splits
+    (4100, 2, 48, 2500, "f16"),     # ... two workgroups per compute unit, idle waves at the end
+    (500, 2, 192, 300, "bf16"),     # ... one group of waves
+    (2000, 8, 24, 96, "f16"),
+    (999, 1, 256, 31, "f16"),
+])
+def test_sparse_attention_forms_at_their_edges(oracle, T, heads, d, n_q, dtype):
+    """Calls on both sides of the rule that cuts them, with ragged keys and queries, against the oracle; other heads' keys
+    and values that are not numbers must not leak into a head (the last step over d may read past it)."""
+    c = inputs.attention_case(T + d + n_q, T, heads, d, n_q, dtype)
+    want = oracle.attention(f64(c["q"]), f64(c["k"]), f64(c["v"]), c["scale"])
+    for use_ws in (True, False):
+        o, _ = run_attn(c, use_ws)
+        attn_close(o, want, DT[dtype], f"attention T={T} d={d} nq={n_q} workspace={use_ws}")
+    if heads > 1:
+        bad = dict(c)
+        bad["k"], bad["v"] = c["k"].clone(), c["v"].clone()
+        bad["k"][:, 1:], bad["v"][:, 1:] = float("nan"), float("inf")
+        o, _ = run_attn(bad)
+        attn_close(o[:, :1], want[:, :1], DT[dtype], "the first head beside heads of NaN")
+
+
 @pytest.mark.parametrize("dtype,res,b,heads,d,n", [("bf16", 32, 8, 8, 40, 3), ("f16", 16, 4, 4, 64, 16),
                                                    ("bf16", 20, 8, 2, 24, 4), ("f16", 64, 8, 8, 40, 1),
                                                    ("f32", 20, 8, 2, 24, 4), ("f32", 32, 8, 8, 40, 3)])

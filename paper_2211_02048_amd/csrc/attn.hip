@@ -148,7 +148,7 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
     // The vectors of a chunk this lane fetches: of K, row l32 (and l32 + 32) at the 16 bytes of its half in every step - the last
     // step's upper half may lie past d: the row's first bytes instead, made zero below -; of V, the vectors lane, lane + 64, ...
     // (past the chunk's last one: that one again, not stored).
-    const bool k_tail = ODD && 16 * (DK - 1) + 8 * half >= d;
+    const bool k_tail = 16 * (DK - 1) + 8 * half >= d;
     unsigned koff[KT], klast[KT], voff[NV];
     int vkey[NV], vdst[NV];
 #pragma unroll

@@ -1191,7 +1191,12 @@ __global__ __launch_bounds__(256) void conv_reduce_kernel(ConvArgs a, long n_run
 // launch (conv_pair_kernel).  With 8 a wave still loads what it multiplies.  With 4 that would be half rows, two
 // requests for 64 bytes (2 - 12 % slower): the waves load 64 bytes of a row each, as with 8, into one buffer, and take
 // their steps from there, one barrier per pair of chunks.
-template <typename T, int W, int P, int TM, int TN, int ORDER = 0>
+//
+// LIST_FIRST: the block list is asked for ahead of the first weights.  Loads return in issue order, so behind the weights the list
+// is a trip to memory late; but where a wave's share of K is half of what it may have in flight or more, every load starts later instead
+// (weights from memory: 640 rows 320 -> 320 with the scatter 6.4 -> 6.1 us, 384 rows 640 -> 640 6.9 -> 6.7; 192 rows 1280 -> 1280
+// 7.3 -> 7.6, 5120 -> 1280 16.7 -> 17.2).
+template <typename T, int W, int P, int TM, int TN, int ORDER = 0, bool LIST_FIRST = false>
 __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvArgs a)
 {
     constexpr int KS = Mma<T>::KSTEP, S = (int)sizeof(T), N = Vec16<T>::N;
@@ -1228,8 +1233,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
     auto w_second = [&](int q) { return ORDER == 4 ? (8 * q + 4 < kcs ? 4 * 64 : 0) : q < q1 ? 64 : 0; };
     const int ntn_total = (a.Cout + 31) / 32;
 
-    // The weight fragments do not depend on the block list: their first loads go out before it is
-    // read.  A fetch past the wave's share still happens, so that the loads in flight stay a fixed
+    // A fetch past the wave's share still happens, so that the loads in flight stay a fixed
     // number, but every lane then reads the same 16 bytes: one request instead of a kilobyte.
     const u32x4* const idle = (const u32x4*)a.w;
     const u32x4* __restrict__ wp[TN];
@@ -1245,57 +1249,61 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
             rb[st][tn][1] = src[w_second(q)];
         }
     };
+    if constexpr (!LIST_FIRST) {
 #pragma unroll
-    for (int st = 0; st < P; ++st) fetch_b(st, q0 + st);
-
-    // rows this lane loads from: row 16*i + lane/4 of the patch, i < NI, clamped to rows that exist;
-    // in fused mode the block origins are fetched together with the count (row n exists for
-    // n < max_blocks)
-    int oy[NI], ox[NI], rr[NI];
+        for (int st = 0; st < P; ++st) fetch_b(st, q0 + st);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // The block list: rows that are gathered come from it; of stacked rows only the epilogue reads the origins, those of the patch's
+    // rows through LDS, that of this thread's first run for the residuals, fetched ahead.
+    const bool to_y = a.y != nullptr;                         // scatter epilogue (block origins given)
+    const int e_runs = BN / N;                                // 16-byte runs of a patch row
+    const int m_pre = tid / e_runs, o_pre = blockIdx.x * BN + (tid - m_pre * e_runs) * N;
+    int oy[NI], ox[NI], pp[NI], rr[NI], org_y = 0, org_x = 0, pre_y = 0, pre_x = 0, pre_p = 0;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         rr[i] = r0 + 16 * i + (lane >> 2);
-        oy[i] = ox[i] = 0;
-        if (have_org) {
-            int n, rem_;
-            divmod(rr[i], a.d_pbfull, n, rem_);
-            n = min(n, a.max_blocks - 1);
+        oy[i] = ox[i] = pp[i] = 0;
+        if (gathered) {
+            int n;
+            divmod(rr[i], a.d_pbfull, n, pp[i]);
+            n = min(n, a.max_blocks - 1);                     // (row n of the list exists, whatever the count says)
             oy[i] = a.indices[2 * n];
             ox[i] = a.indices[2 * n + 1];
         }
     }
-    int n_eff = effective_blocks(a.count, a.max_blocks, a.n_host);
-#pragma unroll
-    for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(oy[i]), "+v"(ox[i]), "+v"(n_eff));
+    if (have_org) {
+        int n, p;
+        divmod(r0 + min(tid, BM - 1), a.d_pbfull, n, p);
+        n = min(n, a.max_blocks - 1);
+        org_y = a.indices[2 * n];
+        org_x = a.indices[2 * n + 1];
+        divmod(r0 + min(m_pre, BM - 1), a.d_pbfull, n, pre_p);
+        n = min(n, a.max_blocks - 1);
+        pre_y = a.indices[2 * n];
+        pre_x = a.indices[2 * n + 1];
+    }
+    const int n_eff = effective_blocks(a.count, a.max_blocks, a.n_host);
     const int rows = n_eff * pb;
     if (r0 >= rows) return;
-    // the epilogue needs the origin of every row's block again: the first NI waves hold those of
-    // rows 16*wave + lane/4 (the i = wave entry of what they just fetched)
-    __shared__ int org[2 * BM];
-    if (have_org && wave < NI && (lane & 3) == 0) {
-        int yy = oy[0], xx = ox[0];
+    if constexpr (LIST_FIRST) {
 #pragma unroll
-        for (int i = 1; i < NI; ++i)
-            if (wave == i) { yy = oy[i]; xx = ox[i]; }
-        org[2 * (16 * wave + (lane >> 2))] = yy;
-        org[2 * (16 * wave + (lane >> 2)) + 1] = xx;
+        for (int st = 0; st < P; ++st) fetch_b(st, q0 + st);
+        __builtin_amdgcn_sched_barrier(0);
     }
     const char* __restrict__ rp[NI];
     bool outside = false;                                     // one of this lane's rows is a pixel outside the image
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        const int r = min(rr[i], rows - 1);
-        long pixel = r;
+        long pixel = min(rr[i], rows - 1);
         long ld = a.Cin;
         if (gathered) {
-            int n, p, py, px;
-            divmod(r, a.d_pbfull, n, p);
-            divmod(p, a.d_bw, py, px);
-            // the origin fetched above belongs to row rr; a clamped row reads the last block's
-            const int y0 = r == rr[i] ? oy[i] : a.indices[2 * n];
-            const int x0 = r == rr[i] ? ox[i] : a.indices[2 * n + 1];
-            pixel = (long)min(y0 + py, a.Hin - 1) * a.Win + min(x0 + px, a.Win - 1);
-            outside = outside || y0 + py >= a.Hin || x0 + px >= a.Win;
+            // (rows past the count read some pixel of the image: a list entry past it may hold anything)
+            int py, px;
+            divmod(pp[i], a.d_bw, py, px);
+            const int iy = oy[i] + py, ix = ox[i] + px;
+            pixel = (long)min(max(iy, 0), a.Hin - 1) * a.Win + min(max(ix, 0), a.Win - 1);
+            outside = outside || (rr[i] < rows && (iy >= a.Hin || ix >= a.Win));
             ld = a.x_ld;
         }
         rp[i] = (gathered ? (const char*)a.x : (const char*)a.tiles) + pixel * ld * S + (lane & 3) * 16;
@@ -1306,42 +1314,46 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
             ra[st][i] = *(row_live(q) ? (const u32x4*)(rp[i] + (long)row_pair(q) * 64) : idle);
     };
 #pragma unroll
-    for (int st = 0; st < P; ++st) fetch_a(st, q0 + st);
+    for (int st = 0; st < P; ++st) {
+        fetch_a(st, q0 + st);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
     // (every wave has looked at all rows of the patch: the answer is the workgroup's)
     const bool clear_outside = gathered && a.y == nullptr && __ballot(outside) != 0ull;
 
+    __shared__ int org[2 * BM];
+    if (have_org && tid < BM) { org[2 * tid] = org_y; org[2 * tid + 1] = org_x; }
     // What the epilogue needs for this thread's first run of output channels and does not depend on
-    // the sums - bias and residuals - is fetched now and arrives during the K loop (the origin of the
-    // run's row comes straight from the list: LDS holds it only later).
+    // the sums - bias and residuals - is fetched now and arrives during the K loop.
     const bool vec_ok = emit_vec_ok<T>(a);
-    const bool to_y = a.y != nullptr;                    // scatter epilogue (block origins given)
     bool pre_ok = false;
-    long pre_pix = 0;
     uint4 pre_t = make_uint4(0, 0, 0, 0), pre_f = make_uint4(0, 0, 0, 0);
     float pre_bv[N];
-    {
-        const int m = tid / (BN / N), nn = (tid - m * (BN / N)) * N;
-        const int r = r0 + m, o = blockIdx.x * BN + nn;
 #pragma unroll
-        for (int i = 0; i < N; ++i) pre_bv[i] = 0.0f;
-        if (tid < BM * (BN / N) && r < rows && o < a.Cout) {
-            load_bias<N>(a, o, pre_bv);
-            if (to_y && vec_ok && o + N <= a.Cout) {
-                int n, p, py, px;
-                divmod(r, a.d_pbfull, n, p);
-                divmod(p, a.d_bw, py, px);
-                const int yy = a.indices[2 * n] + py, xx = a.indices[2 * n + 1] + px;
-                if (yy >= 0 && yy < a.Hout && xx >= 0 && xx < a.Wout) {
-                    pre_ok = true;
-                    pre_pix = (long)yy * a.Wout + xx;
-                    if (a.res_tiles) pre_t = *(const uint4*)((const T*)a.res_tiles + (long)r * a.Cout + o);
-                    if (a.res_full) pre_f = *(const uint4*)((const T*)a.res_full + pre_pix * a.res_ld + o);
-                }
+    for (int i = 0; i < N; ++i) pre_bv[i] = 0.0f;
+    if (tid < BM * e_runs && r0 + m_pre < rows && o_pre < a.Cout && !a.glu) {
+        load_bias<N>(a, o_pre, pre_bv);
+        if (to_y && vec_ok && o_pre + N <= a.Cout) {
+            int py, px;
+            divmod(pre_p, a.d_bw, py, px);
+            const int yy = pre_y + py, xx = pre_x + px;
+            if (yy >= 0 && yy < a.Hout && xx >= 0 && xx < a.Wout) {
+                pre_ok = true;
+                if (a.res_tiles) pre_t = *(const uint4*)((const T*)a.res_tiles + (long)(r0 + m_pre) * a.Cout + o_pre);
+                if (a.res_full) pre_f = *(const uint4*)((const T*)a.res_full + ((long)yy * a.Wout + xx) * a.res_ld + o_pre);
             }
         }
     }
-
+    // gated GELU: a run of values and its gates are one thread's, in rows of BN / 16 such runs
+    constexpr int GR = BN / 16;
+    float glu_v[N], glu_g[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) glu_v[i] = glu_g[i] = 0.0f;
+    if (a.glu && a.bias != nullptr && blockIdx.x * BN + (tid % GR) * 16 < a.Cout) {       // whole runs: the channel count is a multiple of 16 here
+        load_f32_run<N>(a.bias, blockIdx.x * BN + (tid % GR) * 16, glu_v);
+        load_f32_run<N>(a.bias, blockIdx.x * BN + (tid % GR) * 16 + 8, glu_g);
+    }
     f32x16 acc[TM][TN];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
@@ -1413,29 +1425,33 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
         }
         __syncthreads();
     }
+    if (a.glu) {
+        static_assert(BM * GR % 64 == 0 && 64 * W % GR == 0, "a thread keeps its column of runs");
+        for (int e = tid; e < BM * GR; e += 64 * W) {
+            const int m = e / GR, nn = (e % GR) * 16;
+            const int r = r0 + m, o = blockIdx.x * BN + nn;
+            if (r >= rows || o >= a.Cout) continue;
+            float v[N], gt[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) { v[i] = glu_v[i]; gt[i] = glu_g[i]; }
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const float4* src = (const float4*)(red + (w * BM + m) * RS + nn);
+#pragma unroll
+                for (int i = 0; i < N / 4; ++i) {
+                    const float4 q = src[i], g = src[2 + i];
+                    v[4 * i] += q.x; v[4 * i + 1] += q.y; v[4 * i + 2] += q.z; v[4 * i + 3] += q.w;
+                    gt[4 * i] += g.x; gt[4 * i + 1] += g.y; gt[4 * i + 2] += g.z; gt[4 * i + 3] += g.w;
+                }
+            }
+            emit_glu<T>(a, r, o, v, gt);
+        }
+        return;
+    }
     for (int e = tid; e < BM * (BN / N); e += 64 * W) {
         const int m = e / (BN / N), nn = (e - m * (BN / N)) * N;
         const int r = r0 + m, o = blockIdx.x * BN + nn;
         if (r >= rows || o >= a.Cout) continue;
-        if (a.glu) {              // value runs finish themselves and their gates, gate runs have nothing to do
-            if ((o & 15) >= 8) continue;
-            float v[N], gt[N];
-#pragma unroll
-            for (int i = 0; i < N; ++i) { v[i] = 0.0f; gt[i] = 0.0f; }
-            if (a.bias != nullptr) {      // whole runs: the channel count is a multiple of 16 here
-                load_f32_run<N>(a.bias, o, v);
-                load_f32_run<N>(a.bias, o + 8, gt);
-            }
-#pragma unroll
-            for (int w = 0; w < W; ++w)
-#pragma unroll
-                for (int i = 0; i < N; ++i) {
-                    v[i] += red[(w * BM + m) * RS + nn + i];
-                    gt[i] += red[(w * BM + m) * RS + nn + 8 + i];
-                }
-            emit_glu<T>(a, r, o, v, gt);
-            continue;
-        }
         const long t = (long)r * a.Cout + o;
         long pix = 0;
         if (to_y) {
@@ -1591,10 +1607,10 @@ int launch_conv(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
 }
 
 
-template <typename T, int W, int P, int TM, int TN, int ORDER = 0>
+template <typename T, int W, int P, int TM, int TN, int ORDER = 0, bool LIST_FIRST = false>
 int launch_pointwise_as(const ConvArgs& a, int nl, hipStream_t st)
 {
-    auto kern = pointwise_kernel<T, W, P, TM, TN, ORDER>;
+    auto kern = pointwise_kernel<T, W, P, TM, TN, ORDER, LIST_FIRST>;
     constexpr int BM = 32 * TM;
     const size_t lds = std::max((size_t)W * BM * (32 * TN + 4) * sizeof(float), (size_t)W * 2 * BM * 80);
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1614,7 +1630,10 @@ int launch_pointwise(const ConvArgs& a, int nl, int tiles, int order, hipStream_
         if (order == 8) return launch_pointwise_as<T, 4, 3, 2, 2, 8>(a, nl, st);
         if (order == 4) return launch_pointwise_as<T, 4, 3, 2, 2, 4>(a, nl, st);
     }
-    if (tiles == 3) return launch_pointwise_as<T, 8, 6, 1, 1>(a, nl, st);
+    if (tiles == 3) {
+        const bool short_k = a.Cin / (2 * Mma<T>::KSTEP) <= 8 * 3;     // three of the six pairs of K steps a wave may have in flight
+        return short_k ? launch_pointwise_as<T, 8, 6, 1, 1, 0, true>(a, nl, st) : launch_pointwise_as<T, 8, 6, 1, 1>(a, nl, st);
+    }
     if (tiles == 2) {
         // more 64 x 64 patches than compute units: four waves per workgroup, so that two workgroups
         // share a compute unit and all of them run at once instead of in two rounds

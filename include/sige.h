@@ -448,6 +448,14 @@ int sige_gn_stats(const void* x, sige_dtype dt, int32_t H, int32_t W, int32_t C,
                   int32_t groups, const float* gamma, const float* beta, float eps,
                   float* mean, float* var, float* scale, float* shift, void* stream);
 
+/* sige_gn_stats and, with the folded scale and shift, the activated copy of the tensor that a layer normalising
+ * it reads: out[y][x][c] = act(scale[c] * x[y][x][c] + shift[c]), computed in fp32 and rounded once, with out_ld
+ * elements between its pixels.  scale and shift are required.  (One kernel for small tensors.)     */
+int sige_gn_stats_act(const void* x, sige_dtype dt, int32_t H, int32_t W, int32_t C, int32_t x_ld,
+                      int32_t groups, const float* gamma, const float* beta, float eps,
+                      float* mean, float* var, float* scale, float* shift, sige_act act,
+                      void* out, int32_t out_ld, void* stream);
+
 const char* sige_last_error(void);
 int sige_version(void);
 

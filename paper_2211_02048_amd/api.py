@@ -24,7 +24,7 @@ STATUS = {0: "SIGE_OK", 1: "SIGE_ERR_INVALID_ARG", 2: "SIGE_ERR_UNSUPPORTED", 3:
 
 EXPORTS = ["sige_reduce_mask", "sige_reduce_mask_workspace_bytes", "sige_reduce_mask_lists", "sige_gather", "sige_gather_modulated", "sige_conv", "sige_conv_workspace_bytes", "sige_conv_geglu", "sige_conv_scatter", "sige_scatter", "sige_fused_conv", "sige_fused_conv_pair", "sige_sparse_attn", "sige_sparse_attn_blocks",
            "sige_sparse_attn_workspace_bytes", "sige_token_norm", "sige_gather_token_norm", "sige_geglu", "sige_packed_weight_bytes", "sige_pack_weight",
-           "sige_gn_stats", "sige_last_error", "sige_version", "sige_set_knob", "sige_get_knob", "sige_conv_plan", "sige_reduce_mask_noalloc", "sige_mark_blocks",
+           "sige_gn_stats", "sige_gn_stats_act", "sige_last_error", "sige_version", "sige_set_knob", "sige_get_knob", "sige_conv_plan", "sige_reduce_mask_noalloc", "sige_mark_blocks",
            "sige_fused_conv_pair_marked"]
 
 # sige_knob of the header
@@ -130,6 +130,7 @@ def lib() -> ctypes.CDLL:
         L.sige_gather_token_norm.argtypes = [vp, i32, i32, i32, gp, vp, vp, i32, i32, vp, vp, f32, vp, vp]
         L.sige_geglu.argtypes = [vp, i32, i32, i32, vp, i32, i32, i32, vp, i32, vp]
         L.sige_gn_stats.argtypes = [vp, i32, i32, i32, i32, i32, i32, vp, vp, f32, vp, vp, vp, vp, vp]
+        L.sige_gn_stats_act.argtypes = [vp, i32, i32, i32, i32, i32, i32, vp, vp, f32, vp, vp, vp, vp, i32, vp, i32, vp]
         L.sige_conv_plan.argtypes = [i32, gp, i32, i32, i32, i32, i32, sz, ctypes.POINTER(ConvPlanInfo)]
         L.sige_set_knob.argtypes = [i32, i32]
         L.sige_get_knob.argtypes = [i32]
@@ -541,6 +542,17 @@ def sige_gn_stats(x, groups, mean, var, *, gamma=None, beta=None, eps=1e-5, scal
     x_ld = x.stride(1) if x_ld is None else x_ld
     _check(lib().sige_gn_stats(_ptr(x), _DT[x.dtype], H, W, C, x_ld, groups, _ptr(gamma), _ptr(beta), eps,
                                _ptr(mean), _ptr(var), _ptr(scale), _ptr(shift), _stream()))
+
+
+def sige_gn_stats_act(x, groups, mean, var, scale, shift, out, *, act=ACT_NONE, gamma=None, beta=None, eps=1e-5,
+                      C=None, x_ld=None, out_ld=None):
+    """sige_gn_stats and out = act(scale * x + shift) of the whole tensor."""
+    H, W = x.shape[0], x.shape[1]
+    C = x.shape[2] if C is None else C
+    x_ld = x.stride(1) if x_ld is None else x_ld
+    out_ld = out.stride(1) if out_ld is None else out_ld
+    _check(lib().sige_gn_stats_act(_ptr(x), _DT[x.dtype], H, W, C, x_ld, groups, _ptr(gamma), _ptr(beta), eps,
+                                   _ptr(mean), _ptr(var), _ptr(scale), _ptr(shift), act, _ptr(out), out_ld, _stream()))
 
 
 def sige_version() -> int:

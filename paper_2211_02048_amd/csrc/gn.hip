@@ -147,29 +147,65 @@ __global__ __launch_bounds__(256) void gn_fold_kernel(float* mean, float* var, f
     }
 }
 
+// act(scale * x + shift) of a whole tensor, once its statistics are folded: a lane keeps one 16-byte channel group and its
+// parameters and walks down the pixels, four loads in flight.
+struct GnOut { uint4* out; int ld_vec, act; };
+template <typename T>
+__global__ __launch_bounds__(256) void gn_act_kernel(const uint4* __restrict__ x, int n_pix, int V, int ld_vec, int ppi, FastDiv d_v,
+                                                     const float* __restrict__ scale, const float* __restrict__ shift, GnOut o)
+{
+    constexpr int N = Vec16<T>::N, U = 4;
+    int pl, cv;
+    divmod(threadIdx.x, d_v, pl, cv);
+    if (pl >= ppi) return;
+    cv += blockIdx.y * 256;                                  // (more than 256 vectors per pixel: 256 of them per row of the grid)
+    if (cv >= V) return;
+    float sc[N], sh[N];
+    load_f32_run<N>(scale, cv * N, sc);
+    load_f32_run<N>(shift, cv * N, sh);
+    const int stride = gridDim.x * ppi;
+    for (int p = blockIdx.x * ppi + pl; p < n_pix; p += U * stride) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = x[(long)min(p + u * stride, n_pix - 1) * ld_vec + cv];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (p + u * stride >= n_pix) break;
+            float f[N];
+            unpack<T>(v[u], f);
+            scale_shift_act<N>(f, sc, sh, o.act);
+            o.out[(long)(p + u * stride) * o.ld_vec + cv] = pack<T>(f);
+        }
+    }
+}
+
 // One workgroup = VW channel vectors (VW * N channels, a whole number of groups) x 256 / VW pixel
 // lanes.  Every lane sums its pixels, the lanes' sums meet in LDS and are added in lane order, the
-// channels of a group likewise.
-template <typename T>
+// channels of a group likewise.  With o.out given the workgroup then reads its channels again and stores act(scale * x + shift).
+// A workgroup takes 16 bytes of a line of memory at a time, so what bounds it is its compute unit's way into memory: more threads
+// do not help (1024 of them: 64 x 64 x 256 7.1 -> 11.4 us), and the copy is made here only where a lane has one batch of loads
+// (statistics and gather -> this: 8 x 8 x 512 6.4 -> 4.7 us, 16 x 16 x 512 6.7 -> 5.3, 32 x 32 x 256 7.7 -> 7.0; 64 x 64 x 256 9.7 -> 18).
 // ppl = 256 / VW pixel lanes, strips = 256 / CW, per = ceil(ppl / strips), gpw = CW / cg groups per
 // workgroup and the reciprocals of VW, CW and cg come from the host.
+template <typename T>
 __global__ __launch_bounds__(256) void gn_small_kernel(const uint4* __restrict__ x, int n_pix, int ld_vec, int VW,
-                                                       int cg, int ppl, int strips, int per, int gpw,
-                                                       FastDiv d_vw, FastDiv d_cw, FastDiv d_cg,
-                                                       const float* __restrict__ gamma,
-                                                       const float* __restrict__ beta, float eps,
-                                                       float* __restrict__ mean, float* __restrict__ var,
-                                                       float* __restrict__ scale, float* __restrict__ shift)
+                                                      int cg, int ppl, int strips, int per, int gpw,
+                                                      FastDiv d_vw, FastDiv d_cw, FastDiv d_cg,
+                                                      const float* __restrict__ gamma,
+                                                      const float* __restrict__ beta, float eps,
+                                                      float* __restrict__ mean, float* __restrict__ var,
+                                                      float* __restrict__ scale, float* __restrict__ shift, GnOut o)
 {
     constexpr int N = Vec16<T>::N;
     constexpr int U = 4;               // loads in flight per lane
-    extern __shared__ float red[];     // [2][ppl][CW] sums and sums of squares, then [2][CW] mean and variance
+    extern __shared__ float red[];     // [2][ppl][CW] sums and sums of squares, then [2][CW] mean and variance, [2][CW] scale and shift
     const int CW = VW * N;
     int cv, pl;
     divmod(threadIdx.x, d_vw, pl, cv);
     const int v0 = blockIdx.x * VW;    // first channel vector of this workgroup
     float* sq = red + ppl * CW;
     float* stat = red + 2 * ppl * CW;
+    float* par = stat + 2 * CW;
     if (pl < ppl) {
         float s[N], q[N];
 #pragma unroll
@@ -236,8 +272,30 @@ __global__ __launch_bounds__(256) void gn_small_kernel(const uint4* __restrict__
         divmod(c, d_cg, g, rem_);
         const int ch = v0 * N + c;
         const float sc = (gamma ? gamma[ch] : 1.0f) * rsqrtf(stat[CW + g] + eps);
+        const float sh = (beta ? beta[ch] : 0.0f) - stat[g] * sc;
         scale[ch] = sc;
-        shift[ch] = (beta ? beta[ch] : 0.0f) - stat[g] * sc;
+        shift[ch] = sh;
+        par[c] = sc;
+        par[CW + c] = sh;
+    }
+    if (o.out == nullptr) return;
+    __syncthreads();
+    if (pl >= ppl) return;
+    float sc[N], sh[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) { sc[i] = par[cv * N + i]; sh[i] = par[CW + cv * N + i]; }
+    for (int p = pl; p < n_pix; p += U * ppl) {
+        uint4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = x[(long)min(p + u * ppl, n_pix - 1) * ld_vec + v0 + cv];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (p + u * ppl >= n_pix) break;
+            float f[N];
+            unpack<T>(v[u], f);
+            scale_shift_act<N>(f, sc, sh, o.act);
+            o.out[(long)(p + u * ppl) * o.ld_vec + v0 + cv] = pack<T>(f);
+        }
     }
 }
 
@@ -253,15 +311,29 @@ static int small_path_vectors(long n_pix, int cg, int N)
 }
 
 template <typename T>
-static void launch_small(const void* x, int n_pix, int V, int ld_vec, int VW, int cg, const float* gamma,
-                         const float* beta, float eps, float* mean, float* var, float* scale, float* shift,
-                         hipStream_t st)
+static int launch_act(const void* x, long n_pix, int V, int ld_vec, const float* scale, const float* shift, const GnOut& o, hipStream_t st)
+{
+    const int vrow = V < 256 ? V : 256, ppi = 256 / vrow;
+    const long want = (n_pix + 4L * ppi - 1) / (4L * ppi);
+    hipLaunchKernelGGL((gn_act_kernel<T>), dim3((int)(want > 8192 ? 8192 : want), (V + 255) / 256), dim3(256), 0, st, (const uint4*)x, (int)n_pix, V,
+                       ld_vec, ppi, fast_div(vrow), scale, shift, o);
+    SIGE_LAUNCH_CHECK("sige_gn_stats_act");
+    return SIGE_OK;
+}
+
+template <typename T>
+static int launch_small(const void* x, int n_pix, int V, int ld_vec, int VW, int cg, const float* gamma,
+                        const float* beta, float eps, float* mean, float* var, float* scale, float* shift,
+                        const GnOut& o, hipStream_t st)
 {
     const int ppl = 256 / VW, CW = VW * Vec16<T>::N, strips = 256 / CW;
-    const size_t lds = (size_t)(2 * ppl * CW + 2 * CW) * sizeof(float);
+    const bool copy_here = o.out != nullptr && n_pix <= 4 * ppl;          // one batch of loads per lane
+    const size_t lds = (size_t)(2 * ppl * CW + 4 * CW) * sizeof(float);
     hipLaunchKernelGGL((gn_small_kernel<T>), dim3(V / VW), dim3(256), lds, st, (const uint4*)x, n_pix, ld_vec, VW,
                        cg, ppl, strips, (ppl + strips - 1) / strips, CW / cg, fast_div(VW), fast_div(CW), fast_div(cg), gamma,
-                       beta, eps, mean, var, scale, shift);
+                       beta, eps, mean, var, scale, shift, copy_here ? o : GnOut{nullptr, 0, 0});
+    SIGE_LAUNCH_CHECK("sige_gn_stats(small)");
+    return o.out == nullptr || copy_here ? (int)SIGE_OK : launch_act<T>(x, n_pix, V, ld_vec, scale, shift, o, st);
 }
 
 template <typename T>
@@ -280,12 +352,10 @@ static void launch_sum(const void* x, long n_pix, int V, int ld_vec, int cg, int
 
 using namespace sige;
 
-extern "C" int sige_gn_stats(const void* x, sige_dtype dt, int32_t H, int32_t W, int32_t C, int32_t x_ld,
-                             int32_t groups, const float* gamma, const float* beta, float eps,
-                             float* mean, float* var, float* scale, float* shift, void* stream)
+static int gn_entry(const char* who, const void* x, sige_dtype dt, int32_t H, int32_t W, int32_t C, int32_t x_ld,
+                    int32_t groups, const float* gamma, const float* beta, float eps, float* mean, float* var,
+                    float* scale, float* shift, const GnOut& o, void* stream)
 {
-    clear_error();
-    const char* who = "sige_gn_stats";
     SIGE_REQUIRE(x && mean && var, SIGE_ERR_INVALID_ARG, "%s: x, mean and var are required", who);
     SIGE_REQUIRE((scale == nullptr) == (shift == nullptr), SIGE_ERR_INVALID_ARG,
                  "%s: scale and shift must be given together", who);
@@ -300,11 +370,9 @@ extern "C" int sige_gn_stats(const void* x, sige_dtype dt, int32_t H, int32_t W,
     const long n_pix = (long)H * W;
     const int V = (int)(C * s / 16), ld_vec = (int)(x_ld * s / 16), cg = C / groups;
     if (const int VW = small_path_vectors(n_pix, cg, (int)(16 / s))) {
-        if (dt == SIGE_F32) launch_small<float>(x, (int)n_pix, V, ld_vec, VW, cg, gamma, beta, eps, mean, var, scale, shift, st);
-        else if (dt == SIGE_F16) launch_small<f16>(x, (int)n_pix, V, ld_vec, VW, cg, gamma, beta, eps, mean, var, scale, shift, st);
-        else launch_small<bf16>(x, (int)n_pix, V, ld_vec, VW, cg, gamma, beta, eps, mean, var, scale, shift, st);
-        SIGE_LAUNCH_CHECK("sige_gn_stats(small)");
-        return SIGE_OK;
+        return dt == SIGE_F32 ? launch_small<float>(x, (int)n_pix, V, ld_vec, VW, cg, gamma, beta, eps, mean, var, scale, shift, o, st)
+               : dt == SIGE_F16 ? launch_small<f16>(x, (int)n_pix, V, ld_vec, VW, cg, gamma, beta, eps, mean, var, scale, shift, o, st)
+                                : launch_small<bf16>(x, (int)n_pix, V, ld_vec, VW, cg, gamma, beta, eps, mean, var, scale, shift, o, st);
     }
     hipLaunchKernelGGL(gn_zero_kernel, dim3((groups + 255) / 256), dim3(256), 0, st, mean, var, groups);
     SIGE_LAUNCH_CHECK("sige_gn_stats(zero)");
@@ -315,5 +383,35 @@ extern "C" int sige_gn_stats(const void* x, sige_dtype dt, int32_t H, int32_t W,
     hipLaunchKernelGGL(gn_fold_kernel, dim3(1), dim3(256), 2 * groups * sizeof(float), st, mean, var,
                        (float)n_pix * (float)cg, C, cg, groups, gamma, beta, eps, scale, shift);
     SIGE_LAUNCH_CHECK("sige_gn_stats(fold)");
-    return SIGE_OK;
+    if (o.out == nullptr) return SIGE_OK;
+    return dt == SIGE_F32 ? launch_act<float>(x, n_pix, V, ld_vec, scale, shift, o, st)
+           : dt == SIGE_F16 ? launch_act<f16>(x, n_pix, V, ld_vec, scale, shift, o, st)
+                            : launch_act<bf16>(x, n_pix, V, ld_vec, scale, shift, o, st);
+}
+
+extern "C" int sige_gn_stats(const void* x, sige_dtype dt, int32_t H, int32_t W, int32_t C, int32_t x_ld,
+                             int32_t groups, const float* gamma, const float* beta, float eps,
+                             float* mean, float* var, float* scale, float* shift, void* stream)
+{
+    clear_error();
+    return gn_entry("sige_gn_stats", x, dt, H, W, C, x_ld, groups, gamma, beta, eps, mean, var, scale, shift, GnOut{nullptr, 0, 0}, stream);
+}
+
+extern "C" int sige_gn_stats_act(const void* x, sige_dtype dt, int32_t H, int32_t W, int32_t C, int32_t x_ld,
+                                 int32_t groups, const float* gamma, const float* beta, float eps, float* mean,
+                                 float* var, float* scale, float* shift, sige_act act, void* out, int32_t out_ld,
+                                 void* stream)
+{
+    clear_error();
+    const char* who = "sige_gn_stats_act";
+    SIGE_REQUIRE(out && scale && shift, SIGE_ERR_INVALID_ARG, "%s: out, scale and shift are required", who);
+    SIGE_REQUIRE(act_ok(act), SIGE_ERR_INVALID_ARG, "%s: unknown activation %d", who, (int)act);
+    SIGE_REQUIRE(dtype_ok(dt), SIGE_ERR_INVALID_ARG, "%s: unknown dtype %d", who, (int)dt);
+    SIGE_REQUIRE(out_ld >= C, SIGE_ERR_INVALID_ARG, "%s: bad shape", who);
+    SIGE_REQUIRE((long)H * W <= 0x7fffffffL - (1 << 24), SIGE_ERR_UNSUPPORTED, "%s: too many pixels", who);
+    const size_t s = dtype_size(dt);
+    SIGE_REQUIRE((out_ld * s) % 16 == 0 && aligned16(out), SIGE_ERR_UNSUPPORTED,
+                 "%s: out_ld must be a multiple of %zu elements and out 16-byte aligned", who, 16 / s);
+    return gn_entry(who, x, dt, H, W, C, x_ld, groups, gamma, beta, eps, mean, var, scale, shift,
+                    GnOut{(uint4*)out, (int)(out_ld * s / 16), (int)act}, stream);
 }

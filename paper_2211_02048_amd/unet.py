@@ -227,12 +227,16 @@ class SigeUNet:
             act = api.ACT_SILU if (op["kind"] == "conv" and op["act"]) else api.ACT_NONE
             if "scale" in L:
                 scale, shift = L["scale"], L["shift"]
-                if dense:   # statistics of the original activation, computed where a dense model would
-                    api.sige_gn_stats(x, self.groups, L["mean"], L["var"], gamma=L["gamma"], beta=L["beta"],
-                                      eps=self.eps, scale=scale, shift=shift, C=op["x"][2])
-                if "pre" in L and use_copies and (fill_copies or not dense):
-                    if dense:
-                        self._fill_copy(L, x, scale, shift, act)
+                copied = "pre" in L and use_copies and (fill_copies or not dense)
+                if dense:   # statistics of the original activation, computed where a dense model would; the copy with them
+                    stat = dict(gamma=L["gamma"], beta=L["beta"], eps=self.eps, C=op["x"][2])
+                    if copied and x.shape[0] <= WHOLE_IMAGE_BLOCK:
+                        api.sige_gn_stats_act(x, self.groups, L["mean"], L["var"], scale, shift, L["pre"], act=act, **stat)
+                    else:
+                        api.sige_gn_stats(x, self.groups, L["mean"], L["var"], scale=scale, shift=shift, **stat)
+                        if copied:
+                            self._fill_copy(L, x, scale, shift, act)
+                if copied:
                     xn, scale, shift, act = L["pre"], None, None, api.ACT_NONE
             # the sparse pass keeps the copies of its output up to date; the dense pass fills them where
             # they are consumed (the statistics are not known before)

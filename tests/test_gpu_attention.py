@@ -434,3 +434,44 @@ def test_conv_geglu(oracle, dtype, Cin, Cg, b, n):
     assert_close(y2, oracle.geglu(f64(o2).reshape(-1, 2 * Cg)).reshape(n, b, b, Cg), td, "sige_geglu of the stored intermediate")
     with pytest.raises(api.SigeError):
         api.sige_conv_geglu(dev(tiles), g, Cin, Cg + 4, packed, None, cnt, out, n_blocks=n, max_blocks=n)
+
+
+@pytest.mark.parametrize("dtype,H,W,C,G,act", [
+    ("f16", 16, 16, 64, 32, "silu"),        # one kernel
+    ("bf16", 64, 64, 320, 32, "none"),      # groups of ten channels: five vectors per workgroup, ragged pixel lanes
+    ("f32", 33, 31, 96, 32, "silu"),        # three channels per group: three vectors per workgroup
+    ("f16", 32, 32, 256, 32, "leaky"),      # the most pixels copied by the statistics kernel
+    ("f16", 91, 90, 256, 32, "silu"),       # the most pixels of that kernel: 8190 of 8192
+    ("f16", 128, 65, 256, 32, "leaky"),     # just beyond
+    ("bf16", 150, 70, 24, 4, "relu"),       # streaming kernels, three vectors per pixel
+    ("f32", 100, 90, 1088, 32, "none"),     # more than 256 vectors per pixel
+])
+def test_gn_stats_with_activated_copy(oracle, dtype, H, W, C, G, act):
+    """Statistics, folding and the activated copy in one call: against the oracle, the copy also bit for bit against the gather
+    of the whole image with the call's own scale and shift; a strided source and copy, nothing outside the channels written."""
+    td, code = DT[dtype], dict(none=api.ACT_NONE, silu=api.ACT_SILU, relu=api.ACT_RELU, leaky=api.ACT_LEAKY_RELU)[act]
+    rng = np.random.default_rng(H + C)
+    wide = torch.from_numpy((rng.standard_normal((H, W, C + 16)) * 1.5 + 0.3).astype(np.float32)).to(td)
+    gamma, beta = (torch.from_numpy(rng.standard_normal(C).astype(np.float32)) for _ in range(2))
+    xd = dev(wide)
+    x = xd[:, :, 8:8 + C]
+    mean, var = torch.zeros(G, device="cuda"), torch.zeros(G, device="cuda")
+    scale, shift = torch.zeros(C, device="cuda"), torch.zeros(C, device="cuda")
+    out = torch.full((H, W, C + 8), 5.0, dtype=td, device="cuda")
+    api.sige_gn_stats_act(x, G, mean, var, scale, shift, out, act=code, gamma=dev(gamma), beta=dev(beta), C=C)
+    torch.cuda.synchronize()
+    x64 = f64(wide)[:, :, 8:8 + C]
+    wm, wv = oracle.gn_stats(x64, G)
+    # fp32 sums of n values: relative error of a few n * 2^-24 at worst, far less for sums in parts
+    assert np.allclose(f64(mean), wm, rtol=1e-4, atol=1e-5) and np.allclose(f64(var), wv, rtol=1e-4)
+    sc = f64(gamma) / np.sqrt(np.repeat(wv, C // G) + 1e-5)
+    v = x64 * sc + (f64(beta) - np.repeat(wm, C // G) * sc)
+    v = dict(none=lambda t: t, silu=lambda t: t / (1.0 + np.exp(-t)), relu=lambda t: np.maximum(t, 0),
+             leaky=lambda t: np.where(t > 0, t, 0.2 * t))[act](v)
+    assert_close(out[:, :, :C], v, td, "activated copy")
+    assert (out[:, :, C:] == 5.0).all()
+    g = api.geom(H, W, (H, W), 1, 1, 0)
+    t = torch.zeros((1, H, W, C), dtype=td, device="cuda")
+    idx, one = torch.zeros((1, 2), dtype=torch.int32, device="cuda"), torch.ones(1, dtype=torch.int32, device="cuda")
+    api.sige_gather(x, g, idx, one, t, n_blocks=1, scale=scale, shift=shift, act=code, C=C, max_blocks=1)
+    assert torch.equal(t[0], out[:, :, :C].contiguous())

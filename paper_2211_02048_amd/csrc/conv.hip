@@ -161,7 +161,8 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
                 wgs4 = (long)q.groups * q.bands * q.slabs;
             }
         }
-        if (q.kc && (wgs4 <= 256 || force_whole)) {
+        // (256 channels: with more workgroups the whole is 1 us faster alone, and a shortcut beside it no longer shares the launch: 17 -> 11)
+        if (q.kc && (wgs4 <= (Cin == 16 * kstep && q.cfg == 4 ? 128 : 256) || force_whole)) {
             q.Cc = q.kc * kstep;
             q.ps = (int)(q.Cc * s + pad_of(q.kc));
             p = q;
@@ -337,11 +338,11 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     // batch of vectors for the 256 threads (a pixel of a chunk is 2 * kc vectors).  Where every workgroup has one
     // chunk there is nothing to hide; shares of one and two still gain (bf16 960 -> 640 on one 8x8 block, 15 chunks in
     // ten shares: 14.5 -> 13.9 us).
-    const long pipe_vectors = (long)p->G * p->trows * tw * 2 * p->kc;
+    const long vectors = (long)p->G * p->trows * tw * 2 * p->kc;
     const int nch = Cin / (p->kc * ks);
     const bool can_ahead = nch > p->ksplit && (p->cfg == 6 || (p->cfg == 3 && g->k == 3 && (p->kc == 4 || p->kc == 8) &&
                                                                a.scale == nullptr && a.act == SIGE_ACT_NONE &&
-                                                               pipe_vectors <= 256L * kPipeVectors));
+                                                               vectors <= 256L * pipe_vectors(p->kc)));
     const int ahead = knob(SIGE_KNOB_CONV_AHEAD);           // 0 = never, 1 = refuse what cannot
     SIGE_REQUIRE(ahead < 1 || can_ahead, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
     // One chunk per workgroup (the whole of Cin staged at once, or as many shares as chunks): requested in one go where

@@ -310,7 +310,8 @@ constexpr int ring_depth(int steps, int limit)
 // kAhead  the next chunk's pixels are requested while the current chunk is multiplied
 // kOnce   the workgroup has one chunk: its tile and its first weights are requested together, nothing is fetched twice
 enum ChunkMode { kPlain = 0, kAhead = 1, kOnce = 2 };
-constexpr int kPipeVectors = 8;   // 16-byte vectors per thread of a chunk that is requested ahead
+// 16-byte vectors per thread of a chunk that is requested ahead (ten: the 17 x 17 and 9 x 33 tiles of stride 2, chunks of four K steps)
+constexpr int pipe_vectors(int kc) { return kc == 4 ? 10 : 8; }
 // ... and of a chunk that is requested at once: the tile of a 16 x 16 or 8 x 8 block's band with a halo of one, by the K steps of
 // the chunk and the 32-row tiles of the patch (a fixed number: under a condition, uniform or not, the compiler waits for each)
 constexpr int once_vectors(int kc, int tm)
@@ -555,7 +556,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // group and walks over the pixels NT / VPC at a time without dividing.  Each batch of U vectors
     // is loaded before any of them is used (addresses are clamped into the source, so the loads are
     // unconditional and overlap; what lies outside becomes zero afterwards).
-    constexpr int U = TM * TN >= 4 ? 6 : NARROW ? once_vectors(KC, 1) : PIPE ? kPipeVectors : 8;   // fewer where the accumulators leave fewer registers
+    constexpr int U = TM * TN >= 4 ? 6 : NARROW ? once_vectors(KC, 1) : PIPE ? pipe_vectors(KC) : 8;   // fewer where the accumulators leave fewer registers
     constexpr int PPI = NT / VPC;                             // pixels covered by one step of the walk
     constexpr int NTS = PPI * VPC;                            // threads that stage (all of them unless VPC is 40 or 80)
     const int sv = tid % VPC;
@@ -720,7 +721,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         uint4 nextv[PIPE ? U : 1];
         unsigned inside = 0u;
         if constexpr (PIPE) {
-            static_assert(!SWAP && U <= STEPS, "one request per step");
+            static_assert(!SWAP && U <= 2 * STEPS, "one request per step, two in the first ones where there are fewer steps");
             const char* const base = (fused ? (const char*)a.x : tiles) + (long)ch0 * (KC * KS * S) + sv * 16;
             const long px_bytes = (long)(fused ? a.x_ld : a.Cin) * S;
             int q = sq0, g = sg0, r = sr0, x = sx0;
@@ -867,7 +868,12 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 const int nx = (st + D) % STEPS;              // the step that takes over this slot
                 if (!ONCE || st + D < STEPS) fetch(ring[st % D], st + D < STEPS ? chunk : chunk + 1, nx / KW, nx % KW);
                 if constexpr (PIPE)
-                    if (st < U) nextv[st] = *(const uint4*)(!NARROW || chunk + 1 < ch1 ? src[st] + ahead : (const char*)a.w);   // (as in fetch)
+                    {
+                        constexpr int R = (U + STEPS - 1) / STEPS;
+#pragma unroll
+                        for (int j = st * R; j < (st + 1) * R && j < U; ++j)
+                            nextv[j] = *(const uint4*)(!NARROW || chunk + 1 < ch1 ? src[j] + ahead : (const char*)a.w);   // (as in fetch)
+                    }
                 // nothing moves across a step boundary: left alone, the scheduler sinks every prefetch
                 // down to its first use to save registers and the ring collapses
                 __builtin_amdgcn_sched_barrier(0);

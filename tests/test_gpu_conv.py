@@ -1338,6 +1338,7 @@ def test_recorded_calls_repeat_the_step():
     ("bf16", 384, 64, 24, 24, 8, "stored", {}),                          # stored tiles
     ("f16", 256, 48, 22, 26, 8, "up", {}),                               # up-sampled source
     ("bf16", 192, 48, 27, 29, 6, "stride 2", dict(CONV_KC=4)),           # 13 x 13 tiles, ragged
+    ("f16", 128, 64, 43, 38, 8, "stride 2", dict(CONV_KC=4)),            # 17 x 17 tiles: ten vectors per thread
     ("f16", 256, 64, 22, 26, 8, "copies", {}),                           # residual and an activated copy in the epilogue
 ])
 def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, form, kn):

@@ -35,6 +35,7 @@ class BlockList:
         self.indices = torch.zeros((max(self.max_blocks, 1), 2), dtype=torch.int32, device=device)
         self.count = torch.zeros(1, dtype=torch.int32, device=device)
         self.n_host = -1
+        self.joint = None      # the tensor that holds this count beside others' (share_counts)
         # per-block flag scratch for the reduction; starts zero and every call leaves it zero
         self.scratch = torch.zeros(api.sige_reduce_mask_workspace_bytes(g), dtype=torch.uint8,
                                    device=device) if use_workspace else None
@@ -79,9 +80,30 @@ class BlockList:
         self.n_host = n
         return self
 
+    @staticmethod
+    def share_counts(lists):
+        """Puts the counts of several lists side by side in one tensor, so that sync_counts reads them back at once."""
+        if lists:
+            joint = torch.cat([b.count for b in lists])
+            for i, b in enumerate(lists):
+                b.count = joint[i:i + 1]
+                b.joint = joint
+
+    @staticmethod
+    def sync_counts(lists):
+        """sync_count of several lists: one device->host readback where they share their counts (each is a wait for the
+        device and back, 15 us), one per list otherwise."""
+        joint = lists[0].joint if lists else None
+        if joint is None or any(b.joint is not joint for b in lists):
+            return [b.sync_count() for b in lists]
+        host = joint.tolist()
+        return [b._counted(host[(b.count.data_ptr() - joint.data_ptr()) // 4]) for b in lists]
+
     def sync_count(self) -> int:
         """One device->host readback of the block count (once per edit and list)."""
-        n = int(self.count.item())
+        return self._counted(int(self.count.item()))
+
+    def _counted(self, n: int) -> int:
         if n > self.max_blocks:
             raise api.SigeError(3, f"{n} active blocks exceed max_blocks={self.max_blocks}")
         self.n_host = n

@@ -56,6 +56,7 @@ class SigeSpade:
             else:
                 L["g1"] = api.geom(h, w, b, 1, 1, 0)
             self.layers[n] = L
+        BlockList.share_counts([v[1] for v in self.lists.values()])
         if merge_label_convs:
             self._merge_label_convs(P)
 
@@ -116,8 +117,7 @@ class SigeSpade:
             bl.max_blocks = bl.indices.shape[0]
             bl.reduce(mask_in=self.mask, pool_log2=int(math.log2(full[0] // h)), dilate=self.dilate)
         counts = {}
-        for (h, w, b), bl in lists.items():
-            n = bl.sync_count()
+        for ((h, w, b), bl), n in zip(lists.items(), BlockList.sync_counts(list(lists.values()))):
             counts[(h, w)] = n
             if not exact:
                 bl.n_host = -1

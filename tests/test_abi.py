@@ -320,3 +320,22 @@ def test_struct_layouts_match_the_header(tmp_path):
         assert ctypes.sizeof(cls) == int(out[cname]), cname
         for f in fs:
             assert getattr(cls, f).offset == int(out[f"{cname}.{f}"]), (cname, f)
+
+
+def test_counts_read_back_together():
+    """Lists that share their counts are read back at once, in their order, each against its own capacity; lists that do not
+    share them one by one."""
+    import torch
+    from paper_2211_02048_amd.layers import BlockList
+    lists = [BlockList(api.geom(32, 32, b, 3, 1, 1), "cpu") for b in (16, 8, 4)]
+    for b, n in zip(lists, (3, 0, 64)):
+        b.count.fill_(n)
+    assert BlockList.sync_counts(lists) == [3, 0, 64]
+    BlockList.share_counts(lists)
+    assert BlockList.sync_counts(lists[::-1]) == [64, 0, 3] and [b.n_host for b in lists] == [3, 0, 64]
+    lists[1].count.fill_(16)
+    assert BlockList.sync_counts(lists) == [3, 16, 64]
+    lists[0].count.fill_(5)                 # the 2 x 2 grid of 16 x 16 blocks
+    with pytest.raises(api.SigeError):
+        BlockList.sync_counts(lists)
+    assert BlockList.sync_counts([]) == []

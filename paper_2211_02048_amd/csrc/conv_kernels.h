@@ -1351,14 +1351,15 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
             }
         }
     }
-    // gated GELU: a run of values and its gates are one thread's, in rows of BN / 16 such runs
-    constexpr int GR = BN / 16;
+    // gated GELU: a run of values and its gates are one thread's, GR such runs per row (of eight values N at a time)
+    constexpr int GR = BN / 16 * (8 / N);
+    const int glu_nn = (tid % GR) / (8 / N) * 16 + (tid % GR) % (8 / N) * N;
     float glu_v[N], glu_g[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) glu_v[i] = glu_g[i] = 0.0f;
-    if (a.glu && a.bias != nullptr && blockIdx.x * BN + (tid % GR) * 16 < a.Cout) {       // whole runs: the channel count is a multiple of 16 here
-        load_f32_run<N>(a.bias, blockIdx.x * BN + (tid % GR) * 16, glu_v);
-        load_f32_run<N>(a.bias, blockIdx.x * BN + (tid % GR) * 16 + 8, glu_g);
+    if (a.glu && a.bias != nullptr && blockIdx.x * BN + glu_nn < a.Cout) {       // whole runs: the channel count is a multiple of 16 here
+        load_f32_run<N>(a.bias, blockIdx.x * BN + glu_nn, glu_v);
+        load_f32_run<N>(a.bias, blockIdx.x * BN + glu_nn + 8, glu_g);
     }
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -1434,7 +1435,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
     if (a.glu) {
         static_assert(BM * GR % 64 == 0 && 64 * W % GR == 0, "a thread keeps its column of runs");
         for (int e = tid; e < BM * GR; e += 64 * W) {
-            const int m = e / GR, nn = (e % GR) * 16;
+            const int m = e / GR, nn = glu_nn;
             const int r = r0 + m, o = blockIdx.x * BN + nn;
             if (r >= rows || o >= a.Cout) continue;
             float v[N], gt[N];
@@ -1445,7 +1446,7 @@ __global__ __launch_bounds__(64 * W, W == 4 ? 2 : 1) void pointwise_kernel(ConvA
                 const float4* src = (const float4*)(red + (w * BM + m) * RS + nn);
 #pragma unroll
                 for (int i = 0; i < N / 4; ++i) {
-                    const float4 q = src[i], g = src[2 + i];
+                    const float4 q = src[i], g = src[2 + i];        // (the gates: eight channels further)
                     v[4 * i] += q.x; v[4 * i + 1] += q.y; v[4 * i + 2] += q.z; v[4 * i + 3] += q.w;
                     gt[4 * i] += g.x; gt[4 * i + 1] += g.y; gt[4 * i + 2] += g.z; gt[4 * i + 3] += g.w;
                 }

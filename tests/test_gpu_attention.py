@@ -401,7 +401,7 @@ def test_gather_token_norm(oracle, dtype, C, res, b, n):
         api.sige_gather_token_norm(x, api.geom(res, res, b, 3, 1, 1), idx, cnt, tiles, C, n_blocks=n)
 
 
-@pytest.mark.parametrize("dtype,Cin,Cg,b,n", [("bf16", 320, 1280, 8, 10), ("f16", 64, 24, 4, 5), ("f32", 32, 16, 3, 7),
+@pytest.mark.parametrize("dtype,Cin,Cg,b,n", [("f32", 192, 40, 8, 3), ("f32", 320, 96, 6, 2), ("bf16", 320, 1280, 8, 10), ("f16", 64, 24, 4, 5), ("f32", 32, 16, 3, 7),
                                                ("bf16", 1280, 512, 8, 2), ("f16", 128, 2560, 8, 1)])
 def test_conv_geglu(oracle, dtype, Cin, Cg, b, n):
     """The feed-forward layer with the gated GELU folded into its epilogue (one layer, one stored

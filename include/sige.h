@@ -227,7 +227,7 @@ size_t sige_conv_workspace_bytes(sige_dtype dt, const sige_geom* g, int32_t Cin,
  *   kernel             0 = tiled implicit GEMM, 1 = the 1x1 kernel that streams K (built for few rows; the half
  *                      types take it up to 2048 patches of 64x64)
  *   shape              tiled: 0 = 128x128, 1 = 128x64, 2 = 64x64, 3 = 64x32 with four waves splitting K,
- *                      4 = 64x32, 5 = 32x32 and 6 = 32x16 with eight waves splitting K; few rows: 1 = 64x32, 2 = 64x64,
+ *                      4 = 64x32, 5 = 32x32 and 6 = 32x16 with eight waves splitting K, 7 = 32x32 with four; few rows: 1 = 64x32, 2 = 64x64,
  *                      3 = 32x32
  *   patch_m, patch_n   output rows (pixels) x channels per workgroup
  *   k_steps_per_chunk  MFMA K steps per staged channel chunk (tiled kernel)

@@ -161,6 +161,21 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
                 wgs4 = (long)q.groups * q.bands * q.slabs;
             }
         }
+        // 320 channels, half types: 32 rows as well (320 -> 320 on ten 8x8 blocks 9.5 -> 8.4 us, weights from memory)
+        if (q.kc == 20 && q.cfg == 3 && Cin == 20 * kstep && s == 2 && wgs4 <= half_max && pbfull >= 64 && g->block_w <= 32 &&
+            !force_whole && knob(SIGE_KNOB_CONV_AHEAD) != 0) {
+            const int rows = 32 / g->block_w, trows = (rows - 1) * g->stride + g->k;
+            if ((long)trows * tw <= (long)once_vectors(20, 1) * (256 / 40)) {
+                q.cfg = 7;
+                q.G = 1;
+                q.rows = rows;
+                q.bands = (g->block_h + rows - 1) / rows;
+                q.trows = trows;
+                q.groups = nblocks;
+                q.lds = lds_bytes(7, (long)trows * tw, q.kc);
+                wgs4 = (long)q.groups * q.bands * q.slabs;
+            }
+        }
         // (256 channels: with more workgroups the whole is 1 us faster alone, and a shortcut beside it no longer shares the launch: 17 -> 11)
         if (q.kc && (wgs4 <= (Cin == 16 * kstep && q.cfg == 4 ? 128 : 256) || force_whole)) {
             q.Cc = q.kc * kstep;

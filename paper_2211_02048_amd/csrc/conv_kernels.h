@@ -316,7 +316,7 @@ constexpr int pipe_vectors(int kc) { return kc == 4 ? 10 : 8; }
 // the chunk and the 32-row tiles of the patch (a fixed number: under a condition, uniform or not, the compiler waits for each)
 constexpr int once_vectors(int kc, int tm)
 {
-    return kc == 40 ? (tm == 1 ? 10 : 18) : kc == 32 ? (tm == 1 ? 9 : 14) : kc == 20 ? 18 : kc == 16 ? (tm == 1 ? 5 : 7) : kc == 8 ? 7 : 4;
+    return kc == 40 ? (tm == 1 ? 10 : 18) : kc == 32 ? (tm == 1 ? 9 : 14) : kc == 20 ? (tm == 1 ? 12 : 18) : kc == 16 ? (tm == 1 ? 5 : 7) : kc == 8 ? 7 : 4;
 }
 constexpr int MAX_G = 256;   // most blocks one workgroup can hold (1x1 blocks in a 256-row patch)
 
@@ -1527,7 +1527,7 @@ struct ConvPlan {
 // M x N per workgroup and whether the four waves split K
 struct CfgShape { int M, N, WK; };
 constexpr int kNumCfg = 4;    // shapes that compete by score; the others are chosen by a rule of their own
-static const CfgShape kCfg[kNumCfg + 3] = {{128, 128, 1}, {128, 64, 1}, {64, 64, 1}, {64, 32, 4}, {64, 32, 8}, {32, 32, 8}, {32, 16, 8}};
+static const CfgShape kCfg[kNumCfg + 4] = {{128, 128, 1}, {128, 64, 1}, {64, 64, 1}, {64, 32, 4}, {64, 32, 8}, {32, 32, 8}, {32, 16, 8}, {32, 32, 4}};
 
 template <typename T, int TM, int TN, int WM, int WN, int WK, int KC, int KK, int MODE = kPlain, bool NARROW = false>
 int launch_cfg(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
@@ -1577,12 +1577,16 @@ int launch_kc(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
             return launch_cfg<T, 1, 1, 1, 1, 8, KC, KK>(a, p, st);
         }
         break;
-    default:
+    case 6:
         if constexpr (KC % 16 == 0 && KC >= 16 && KK == 9 && sizeof(T) == 2) {
             if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kOnce, true>(a, p, st);
             if constexpr (KC == 32)
                 if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 8, KC, KK, kAhead, true>(a, p, st);
         }
+        break;
+    default:
+        if constexpr (KC == 20 && KK == 9 && sizeof(T) == 2)
+            if (p.mode == kOnce) return launch_cfg<T, 1, 1, 1, 1, 4, KC, KK, kOnce>(a, p, st);
         break;
     }
     return fail(SIGE_ERR_UNSUPPORTED, "sige_conv: internal: shape %d without a matching chunk %d", p.cfg, KC);

@@ -1409,8 +1409,10 @@ def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, form, kn
     ("f32", 32, 40, 21, 23, 6, "silu", 3, dict(CONV_CFG=3, CONV_KC=4)),          # ragged blocks and channels
     ("bf16", 64, 48, 24, 20, 4, "copies", 3, dict(CONV_CFG=3, CONV_KC=4)),       # four blocks per workgroup
     ("f16", 128, 64, 27, 29, 6, "1x1", 3, dict(CONV_CFG=3, CONV_KC=8)),
-    ("bf16", 320, 72, 20, 22, 8, "copies", 3, {}),                               # the whole of 320 channels
-    ("f16", 320, 64, 22, 26, 8, "up", 3, {}),
+    ("bf16", 320, 72, 20, 22, 8, "copies", 7, {}),                               # the whole of 320 channels, 32 rows
+    ("f16", 320, 64, 22, 26, 8, "up", 7, {}),
+    ("f16", 320, 48, 32, 32, 16, "", 7, {}),
+    ("bf16", 320, 40, 21, 23, 6, "copies", 3, {}),                               # ... 64 rows (36 of them used)
     ("bf16", 640, 96, 24, 24, 8, "copies", 5, {}),                               # 32 rows, 640 channels
     ("f32", 256, 64, 20, 20, 8, "", 5, {}),
     ("f16", 512, 96, 48, 80, 16, "", 4, {}),                                     # 64 rows: too many workgroups for 32

@@ -310,8 +310,11 @@ constexpr int ring_depth(int steps, int limit)
 // kAhead  the next chunk's pixels are requested while the current chunk is multiplied
 // kOnce   the workgroup has one chunk: its tile and its first weights are requested together, nothing is fetched twice
 enum ChunkMode { kPlain = 0, kAhead = 1, kOnce = 2 };
-// 16-byte vectors per thread of a chunk that is requested ahead (ten: the 17 x 17 and 9 x 33 tiles of stride 2, chunks of four K steps)
-constexpr int pipe_vectors(int kc) { return kc == 4 ? 10 : 8; }
+// kAheadWide  ... with the larger tiles of stride 2 (17 x 17 and 9 x 33), in chunks of four K steps
+enum { kAheadWide = 3 };
+// 16-byte vectors per thread of a chunk that is requested ahead; a tile that is smaller asks for its last pixels again, so the number
+// follows the tiles: 320 -> 320 on 35 8x8 blocks, chunks of four K steps, 14.5 us with ten vectors, 13.8 with eight, 12.0 with four
+constexpr int pipe_vectors(int kc, int mode) { return mode == kAheadWide ? 10 : kc == 4 ? 4 : 8; }
 // ... and of a chunk that is requested at once: the tile of a 16 x 16 or 8 x 8 block's band with a halo of one, by the K steps of
 // the chunk and the 32-row tiles of the patch (a fixed number: under a condition, uniform or not, the compiler waits for each)
 constexpr int once_vectors(int kc, int tm)
@@ -337,7 +340,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     constexpr int NT = 64 * WM * WN * WK;                     // threads per workgroup
     static_assert(NT == 256 || NT == 512, "four or eight waves per workgroup");
     static_assert(KC % WK == 0, "waves that split K take whole K steps");
-    constexpr bool PIPE = MODE == kAhead, ONCE = MODE == kOnce;
+    constexpr bool PIPE = MODE == kAhead || MODE == kAheadWide, ONCE = MODE == kOnce;
     static_assert(!ONCE || (WK > 1 && KK > 0), "one chunk at once: the shapes whose waves split K");
     constexpr int KS = Mma<T>::KSTEP;
     constexpr int S = (int)sizeof(T);
@@ -556,7 +559,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     // group and walks over the pixels NT / VPC at a time without dividing.  Each batch of U vectors
     // is loaded before any of them is used (addresses are clamped into the source, so the loads are
     // unconditional and overlap; what lies outside becomes zero afterwards).
-    constexpr int U = TM * TN >= 4 ? 6 : NARROW ? once_vectors(KC, 1) : PIPE ? pipe_vectors(KC) : 8;   // fewer where the accumulators leave fewer registers
+    constexpr int U = TM * TN >= 4 ? 6 : NARROW ? once_vectors(KC, 1) : PIPE ? pipe_vectors(KC, MODE) : 8;   // fewer where the accumulators leave fewer registers
     constexpr int PPI = NT / VPC;                             // pixels covered by one step of the walk
     constexpr int NTS = PPI * VPC;                            // threads that stage (all of them unless VPC is 40 or 80)
     const int sv = tid % VPC;
@@ -1560,6 +1563,8 @@ int launch_kc(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
     case 3:
         if constexpr ((KC == 4 || KC == 8) && KK == 9)
             if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kAhead>(a, p, st);
+        if constexpr (KC == 4 && KK == 9)
+            if (p.mode == kAheadWide) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kAheadWide>(a, p, st);
         if constexpr (KC % 4 == 0 && (KC <= 8 || (KC == 20 && KK == 9))) {
             if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kOnce>(a, p, st);
             return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK>(a, p, st);

@@ -737,10 +737,10 @@ static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt)
     }
     // microseconds a workgroup takes beside its chunks, and per chunk of a wave, by 32-wide tiles of a head and form (four waves with
     // the same chunks; one wave each, four of them; eight)
-    static const double fixed_us[9][3] = {{}, {4, 4, 4}, {3, 5, 5}, {5, 6.5, 6.5}, {7, 6.5, 6.5}, {7, 7.5, 0}, {7.5, 8, 0}, {}, {8, 9, 0}};
+    static const double fixed_us[9][3] = {{}, {4, 4, 4}, {3, 5, 5}, {5, 6.5, 6.5}, {7, 6.5, 6.5}, {7, 7.5, 0}, {7.5, 8, 0}, {7.75, 8.5, 0}, {8, 9, 0}};
     static const double chunk_us[9][3] = {{}, {1.2, 0.85, 1.3}, {2.0, 1.35, 2.75}, {2.35, 2.2, 3.5}, {1.2, 1.28, 2.3}, {1.56, 1.5, 0}, {1.9, 2.5, 0},
-                                          {}, {2.6, 5.5, 0}};
-    const int DT = (d + 31) / 32 == 7 ? 8 : (d + 31) / 32;
+                                          {2.25, 4, 0}, {2.6, 5.5, 0}};
+    const int DT = (d + 31) / 32;
     double best_us = 1e30;
     const bool odd = ((d + 15) / 16) & 1;
     // (eight waves on heads of 88 or 96 do not have the registers)
@@ -796,6 +796,8 @@ static int launch_attn_form(const AttnArgs& a, const AttnForm& f, hipStream_t st
     return launch_attn_dt<T, DT, 1, 4>(a, st);
 }
 
+// One instantiation per number of 32-wide tiles: the steps over d, the spare columns of V and the tile that holds the column of ones
+// all follow from it.
 template <typename T>
 static int launch_attn(const AttnArgs& a, const AttnForm& f, hipStream_t st)
 {
@@ -807,6 +809,7 @@ static int launch_attn(const AttnArgs& a, const AttnForm& f, hipStream_t st)
     case 4: return launch_attn_form<T, 4>(a, f, st);
     case 5: return launch_attn_form<T, 5>(a, f, st);
     case 6: return launch_attn_form<T, 6>(a, f, st);
+    case 7: return launch_attn_form<T, 7>(a, f, st);
     default: return launch_attn_form<T, 8>(a, f, st);
     }
 }

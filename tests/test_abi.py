@@ -155,6 +155,10 @@ def test_attention_and_helper_errors(L):
     assert L.sige_gn_stats(FAKE, 1, 16, 16, 30, 32, 4, None, None, f, FAKE, FAKE, None, None, None) == 1
     assert L.sige_sparse_attn_workspace_bytes(16384, 4096, 8, 40) == 0     # enough queries: no split
     assert L.sige_sparse_attn_workspace_bytes(64, 4096, 8, 40) > 0
+    assert L.sige_sparse_attn_workspace_bytes(64, 4096, 8, 256) > 0
+    for d in (257, 264, 320, 512, 4096, 1 << 20, 2**31 - 1):                # heads that the calls refuse
+        assert L.sige_sparse_attn_workspace_bytes(64, 4096, 8, d) == 0, d
+        assert L.sige_sparse_attn(FAKE, 8192, FAKE, FAKE, 8192, 2, 16, 64, 1, d, f, FAKE, 8192, None, 0, None) == 2
 
 
 def test_token_layer_modulated_gather_and_list_errors(L):

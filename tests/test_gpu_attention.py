@@ -86,6 +86,37 @@ def test_sparse_attention_forms_at_their_edges(oracle, T, heads, d, n_q, dtype):
         attn_close(o[:, :1], want[:, :1], DT[dtype], "the first head beside heads of NaN")
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("d", [200, 208, 216, 224])
+@pytest.mark.parametrize("T", [77, 300])
+def test_sparse_attention_heads_of_seven_tiles(oracle, T, d, dtype):
+    """Heads of 193 to 224 in every form (chosen by the number of workgroups aimed for: 4 are four waves on the same chunks, 10 one
+    wave each): the column of ones and the last step over d belong to the seventh tile.  What lies behind the last head of the
+    last key, and the other head, is not a number: a read past the head would show."""
+    heads, n_q = 2, 130
+    c = inputs.attention_case(T + d, T, heads, d, n_q, dtype)
+    want = oracle.attention(f64(c["q"]), f64(c["k"]), f64(c["v"]), c["scale"])
+    q = dev(c["q"])
+
+    def behind(t):
+        buf = torch.full((t.numel() + 256,), float("nan"), dtype=t.dtype, device="cuda")
+        buf[:t.numel()] = t.reshape(-1)
+        return buf[:t.numel()].view(t.shape)
+
+    for wgs in (None, 4, 10):
+        with api.knobs(ATTN_WGS=wgs):
+            for first, last in ((0, heads), (0, 1), (1, heads)):
+                k, v = behind(dev(c["k"])), behind(dev(c["v"]))
+                for t in (k, v):
+                    t[:, :first] = t[:, last:] = float("nan")
+                o = torch.full_like(q, 7.0)
+                nb = api.sige_sparse_attn_workspace_bytes(n_q, T, heads, d)
+                ws = torch.empty(nb // 4, dtype=torch.float32, device="cuda") if nb else None
+                api.sige_sparse_attn(q, k, v, o, c["scale"], workspace=ws)
+                torch.cuda.synchronize()
+                attn_close(o[:, first:last], want[:, first:last], DT[dtype], f"heads {first}..{last - 1} of {d}, {wgs} workgroups")
+
+
 @pytest.mark.parametrize("dtype,res,b,heads,d,n", [("bf16", 32, 8, 8, 40, 3), ("f16", 16, 4, 4, 64, 16),
                                                    ("bf16", 20, 8, 2, 24, 4), ("f16", 64, 8, 8, 40, 1),
                                                    ("f32", 20, 8, 2, 24, 4), ("f32", 32, 8, 8, 40, 3)])

@@ -852,7 +852,7 @@ using namespace sige;
 
 extern "C" size_t sige_sparse_attn_workspace_bytes(int32_t Nq, int32_t T, int32_t heads, int32_t d)
 {
-    if (Nq <= 0 || T <= 0 || heads <= 0 || d <= 0) return 0;
+    if (Nq <= 0 || T <= 0 || heads <= 0 || d <= 0 || d > 256) return 0;     // (a head that no call takes has no plan)
     // the larger of what the half-precision and the single-precision kernels would use
     const int splits = std::max(plan_attn(Nq, T, heads, d, SIGE_F16).splits, plan_attn(Nq, T, heads, d, SIGE_F32).splits);
     if (splits <= 1) return 0;

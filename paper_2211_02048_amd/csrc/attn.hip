@@ -298,8 +298,11 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
             for (int r = 0; r < 16; ++r) mr = fmaxf(mr, sacc[kt][r]);
         mr = fmaxf(mr, __shfl_xor(mr, 32));
         const float mx = fmaxf(m_run, mr * a.scale_log2e);
+        // (logits of -inf, keys taken out of the map: a share of the keys may hold no others, and then nothing is subtracted,
+        // so that its probabilities are exp2(-inf) = 0 and not exp2(inf - inf), however the keys are cut)
+        const float m_sub = mx == -INFINITY ? 0.0f : mx;
         if (__builtin_amdgcn_ballot_w64(mx != m_run) != 0ull) {     // some query's maximum moved
-            const float alpha = __builtin_amdgcn_exp2f(m_run - mx);  // first chunk: exp2(-inf) = 0
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_sub);  // first chunk: exp2(-inf) = 0
             m_run = mx;
             l_run *= alpha;
 #pragma unroll
@@ -311,7 +314,7 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                sacc[kt][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kt][r], a.scale_log2e, -m_run));
+                sacc[kt][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kt][r], a.scale_log2e, -m_sub));
 
         // O^T += V^T P^T, two steps of 16 keys per tile; step s uses registers 8s..8s+7.
         // The probabilities enter this product in the storage type.  fp16 keeps 11 bits of a
@@ -430,12 +433,13 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
             ml[w] = *(const float2*)(src + w * (32 * NQ) * cs + d);
             m = fmaxf(m, ml[w].x);
         }
+        const float m_sub = m == -INFINITY ? 0.0f : m;               // (no wave has a finite logit)
         float den = 0.0f;
         float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
         for (int w = 0; w < NK; ++w) {
             const float4 v = *(const float4*)(src + w * (32 * NQ) * cs + 4 * g);
-            const float f = __builtin_amdgcn_exp2f(ml[w].x - m);     // a wave without keys: exp2(-inf) = 0
+            const float f = __builtin_amdgcn_exp2f(ml[w].x - m_sub); // a wave without keys: exp2(-inf) = 0
             num.x += v.x * f; num.y += v.y * f; num.z += v.z * f; num.w += v.w * f;
             den += ml[w].y * f;
         }
@@ -662,7 +666,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     float den = 0.0f, num[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int j = 0; j < B; ++j) {
-        const float f = sub + j * P < a.splits ? exp2f(ml[j].x - m) : 0.0f;
+        const float f = sub + j * P < a.splits && ml[j].x != -INFINITY ? exp2f(ml[j].x - m) : 0.0f;
         num[0] += val[j].x * f; num[1] += val[j].y * f; num[2] += val[j].z * f; num[3] += val[j].w * f;
         den += ml[j].y * f;
     }

@@ -117,6 +117,25 @@ def test_sparse_attention_heads_of_seven_tiles(oracle, T, d, dtype):
                 attn_close(o[:, first:last], want[:, first:last], DT[dtype], f"heads {first}..{last - 1} of {d}, {wgs} workgroups")
 
 
+@pytest.mark.parametrize("d,dtype", [(40, "bf16"), (64, "f16"), (96, "bf16"), (128, "f16"), (160, "bf16"), (224, "f16"), (256, "bf16")])
+def test_sparse_attention_keys_taken_out(oracle, d, dtype):
+    """Keys whose logits are -inf (the last value of every query is one, theirs -inf): runs of them that fill whole chunks, so that
+    a wave, a group of waves or a split may hold nothing else.  As if those keys were not there, however the call is cut."""
+    T, heads, n_q = 500, 2, 130
+    c = inputs.attention_case(d, T, heads, d, n_q, dtype)
+    out = torch.zeros(T, dtype=torch.bool)
+    out[64:224] = out[288:352] = out[416:] = True
+    c["q"][:, :, d - 1] = 1.0
+    c["k"][:, :, d - 1] = 0.0
+    c["k"][out, :, d - 1] = float("-inf")
+    want = oracle.attention(f64(c["q"]), f64(c["k"][~out]), f64(c["v"][~out]), c["scale"])
+    for wgs in (None, 4, 10, 40, 64):       # four waves on the same chunks, one wave each, splits over workgroups
+        with api.knobs(ATTN_WGS=wgs):
+            for use_ws in (True, False):
+                o, _ = run_attn(c, use_ws)
+                attn_close(o, want, DT[dtype], f"d={d}, {wgs} workgroups, workspace={use_ws}")
+
+
 @pytest.mark.parametrize("dtype,res,b,heads,d,n", [("bf16", 32, 8, 8, 40, 3), ("f16", 16, 4, 4, 64, 16),
                                                    ("bf16", 20, 8, 2, 24, 4), ("f16", 64, 8, 8, 40, 1),
                                                    ("f32", 20, 8, 2, 24, 4), ("f32", 32, 8, 8, 40, 3)])

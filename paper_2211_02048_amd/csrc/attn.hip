@@ -112,7 +112,10 @@ static int keys_per_chunk(int d, sige_dtype dt) { return dt == SIGE_F32 ? 32 : 3
 // said: 192 of 256 x 160 12.1 -> 10.3 us, 384 of 1024 x 80 16.0 -> 13.2, 1024 of 1024 x 80 22.9 -> 14.2, 96 of 4096 x 40 12.9 -> 11.2,
 // 672 of 8192 x 40 37.3 -> 33.5, 2240 of 4096 x 40 47.7 -> 42.7, 192 on 77 keys x 160 10.8 -> 7.6, 9216 of 9216 x 128 930 -> 780,
 // fp16 5000 of 9000 x 160 747 -> 553.
-template <typename T, int DT, int ODD, int NQ, int NK>
+//
+// FAR: keys so far apart that the byte offsets of a chunk's rows do not fit 32 bits (a column of a tensor of gigabytes).  Those take
+// 64-bit offsets, in one kernel for all head sizes: eight tiles, the columns past the head zero.
+template <typename T, int DT, int ODD, int NQ, int NK, bool FAR = false>
 __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kernel(AttnArgs a)
 {
     constexpr int NW = NQ * NK;
@@ -121,6 +124,8 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
     constexpr int VROW = v_row_bytes(DT);
     constexpr int DK = 2 * DT - ODD;               // 16-wide steps over d for S^T
     constexpr int GT = 64 * NQ;                    // threads that have a chunk in common
+    using Off = std::conditional_t<FAR, unsigned long, unsigned>;
+    static_assert(!FAR || (NQ > 1 && ODD == 0), "any head size: through LDS, no column of ones");
     constexpr int NV = (KCH * (4 * DT - 2 * ODD) + GT - 1) / GT;   // V (and K) vectors a thread stages per chunk, at most
     extern __shared__ uint4 lds4[];
     char* lds = reinterpret_cast<char*>(lds4);
@@ -133,8 +138,8 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
     const int q0 = (blockIdx.x * NQ + wq) * 32, qi = q0 + l32;
     const bool q_ok = qi < a.Nq;
     const int dvec = d / 8, nvec = KCH * dvec;     // 16-byte vectors per row, per chunk
-    const unsigned kv2 = (unsigned)a.kv_ld * 2u;   // bytes between keys
-    const int k_stride = d * 2 + 16;               // bytes per K row in LDS (NQ > 1)
+    const Off kv2 = (Off)a.kv_ld * 2u;             // bytes between keys
+    const int k_stride = (FAR ? 32 * DT : d) * 2 + 16;             // bytes per K row in LDS (NQ > 1)
     const int vs0 = wk * (KCH * VROW);             // this group's V rows, then the groups' K rows
     char* const vs = lds + vs0;
     char* const ks = lds + NK * KCH * VROW + wk * (KCH * k_stride);
@@ -149,15 +154,15 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
     // step's upper half may lie past d: the row's first bytes instead, made zero below -; of V, the vectors lane, lane + 64, ...
     // (past the chunk's last one: that one again, not stored).
     const bool k_tail = 16 * (DK - 1) + 8 * half >= d;
-    unsigned koff[KT], klast[KT], voff[NV];
+    Off koff[KT], klast[KT], voff[NV];
     int vkey[NV], vdst[NV];
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) koff[kt] = (unsigned)(kt * 32 + l32) * kv2 + half * 16;
+    for (int kt = 0; kt < KT; ++kt) koff[kt] = (Off)(kt * 32 + l32) * kv2 + half * 16;
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
         int dv;
         divmod(min(gt + GT * u, nvec - 1), a.d_dvec, vkey[u], dv);
-        voff[u] = (unsigned)vkey[u] * kv2 + dv * 16;
+        voff[u] = (Off)vkey[u] * kv2 + dv * 16;
         vdst[u] = vkey[u] * VROW + dv * 16;
     }
     u32x4 kreg[NQ == 1 ? KT * DK : NV], vreg[NV];                  // (native vectors: arrays of structs end up in scratch memory)
@@ -166,9 +171,9 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
         if (t0 + KCH > a.T) {                      // the chunk that holds the end: keys past it read the last key's rows
             const int last = a.T - 1 - t0;
 #pragma unroll
-            for (int kt = 0; kt < KT; ++kt) koff[kt] = (unsigned)min(kt * 32 + l32, last) * kv2 + half * 16;
+            for (int kt = 0; kt < KT; ++kt) koff[kt] = (Off)min(kt * 32 + l32, last) * kv2 + half * 16;
 #pragma unroll
-            for (int u = 0; u < NV; ++u) voff[u] += (unsigned)(min(vkey[u], last) - vkey[u]) * kv2;
+            for (int u = 0; u < NV; ++u) voff[u] -= (Off)(vkey[u] - min(vkey[u], last)) * kv2;
         }
         const char* const kc = kb + (long)t0 * kv2;
         const char* const vc = vb + (long)t0 * kv2;
@@ -208,7 +213,14 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
     }
     // columns d .. DT*32 of the wave's V rows never receive data: zero them once (column d: ones, see above)
     constexpr uint32_t ONE = std::is_same<T, bf16>::value ? 0x3f80u : 0x3c00u;
-    {
+    if constexpr (FAR) {                           // (any number of them, and as many behind every K row)
+        const int pad = 4 * DT - dvec;
+        for (int j = gt; j < KCH * pad; j += GT) {
+            const int row = j / pad, dv = dvec + j - row * pad;
+            *(uint4*)(vs + row * VROW + dv * 16) = make_uint4(0, 0, 0, 0);
+            *(uint4*)(ks + row * k_stride + dv * 16) = make_uint4(0, 0, 0, 0);
+        }
+    } else {
         const int pad = 4 * DT - dvec;             // 16-byte vectors per row, at most 3
         for (int j = gt; j < KCH * 4; j += GT)
             if ((j & 3) < pad)
@@ -230,7 +242,7 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kerne
         for (int r = 0; r < 16; ++r) oacc[nt][r] = 0.0f;
     float m_run = -INFINITY, l_run = 0.0f;
 
-    if constexpr (NQ > 1) {                        // the 16 bytes behind the d values of every K row, which the last step reads when d % 16 is 8
+    if constexpr (NQ > 1 && !FAR) {                // the 16 bytes behind the d values of every K row, which the last step reads when d % 16 is 8
         for (int j = gt; j < KCH; j += GT) *(uint4*)(ks + j * k_stride + d * 2) = make_uint4(0, 0, 0, 0);
     }
     for (; c - wk < c_end; c += NK) {              // (as often in every group: the barriers are the workgroup's)
@@ -766,18 +778,18 @@ static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt)
     return f;
 }
 
-template <typename T, int DT, int NQ, int NK>
+template <typename T, int DT, int NQ, int NK, bool FAR = false>
 static int launch_attn_dt(const AttnArgs& a, hipStream_t st)
 {
     constexpr int KCH = 32 * key_tiles(DT);
-    const size_t lds = std::max((size_t)NK * KCH * (v_row_bytes(DT) + (NQ > 1 ? a.d * 2 + 16 : 0)),
+    const size_t lds = std::max((size_t)NK * KCH * (v_row_bytes(DT) + (NQ > 1 ? (FAR ? 32 * DT : a.d) * 2 + 16 : 0)),
                                 NK == 1 ? 0 : (size_t)NK * NQ * 32 * (a.d + 4) * sizeof(float));
     dim3 grid((a.Nq + 32 * NQ - 1) / (32 * NQ), a.heads, a.splits);
     const bool odd = ((a.d + 15) / 16) & 1;        // d % 32 is 8 or 16
-    auto kern = attn_kernel<T, DT, 1, NQ, NK>;
-    if constexpr (DT != 3 || NK != 8) {
+    auto kern = attn_kernel<T, DT, !FAR, NQ, NK, FAR>;
+    if constexpr (!FAR && (DT != 3 || NK != 8)) {
         if (!odd) kern = attn_kernel<T, DT, 0, NQ, NK>;
-    } else {
+    } else if constexpr (!FAR) {
         SIGE_REQUIRE(odd, SIGE_ERR_UNSUPPORTED, "sige_sparse_attn: internal: eight waves on heads of %d", a.d);
     }
     if (lds > 48 * 1024) {
@@ -887,9 +899,12 @@ static int attn_entry(const char* who, AttnArgs& a, const void* q, int32_t q_ld,
     a.d_tpb = fast_div(a.q_tpb); a.d_qbw = fast_div(a.q_bw); a.d_dvec = fast_div(std::max(d / 8, 1)); a.d_dq = fast_div(d / 4);
     SIGE_REQUIRE(scale >= 0.0f, SIGE_ERR_UNSUPPORTED, "%s: the scale must not be negative", who);
     a.scale_log2e = scale * 1.4426950408889634f;
-    const int KCH = keys_per_chunk(d, dt);
+    // rows of a chunk too far apart for 32-bit offsets: a kernel of its own, cut like single precision (128 queries, 32 keys per chunk)
+    const bool far = dt != SIGE_F32 && (std::min(T, keys_per_chunk(d, dt)) - 1) * (long)kv_ld * 2 + 2L * d > (1L << 32);
+    const sige_dtype cut = far ? SIGE_F32 : dt;
+    const int KCH = keys_per_chunk(d, cut);
     const int chunks = (T + KCH - 1) / KCH;
-    const AttnForm f = plan_attn(Nq, T, heads, d, dt);
+    const AttnForm f = plan_attn(Nq, T, heads, d, cut);
     int splits = f.splits;
     if (splits > 1 && (workspace == nullptr ||
                        workspace_bytes < (size_t)splits * heads * Nq * (d + 4) * sizeof(float) ||
@@ -899,6 +914,7 @@ static int attn_entry(const char* who, AttnArgs& a, const void* q, int32_t q_ld,
     a.splits = (chunks + a.chunks_per_split - 1) / a.chunks_per_split;
     hipStream_t st = (hipStream_t)stream;
     if (dt == SIGE_F32) return launch_attn_f32(a, st);
+    if (far) return dt == SIGE_F16 ? launch_attn_dt<f16, 8, 4, 1, true>(a, st) : launch_attn_dt<bf16, 8, 4, 1, true>(a, st);
     return dt == SIGE_F16 ? launch_attn<f16>(a, f, st) : launch_attn<bf16>(a, f, st);
 }
 

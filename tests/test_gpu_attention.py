@@ -136,6 +136,30 @@ def test_sparse_attention_keys_taken_out(oracle, d, dtype):
                 attn_close(o, want, DT[dtype], f"d={d}, {wgs} workgroups, workspace={use_ws}")
 
 
+@pytest.mark.parametrize("T,d,n_q,apart,dtype", [
+    (40, 40, 70, 56 << 20, "bf16"),         # 64 keys per chunk otherwise; one chunk of 32 and a ragged one here
+    (128, 160, 33, 70 << 20, "f16"),        # two splits
+    (33, 256, 130, 68 << 20, "bf16"),       # 32 rows reach past 4 GiB, the last chunk is one key
+    (20, 64, 40, 107 << 20, "f16"),         # 19 rows below 4 GiB: 32-bit offsets
+])
+def test_sparse_attention_keys_far_apart(oracle, T, d, n_q, apart, dtype):
+    """Keys and values that are columns of a tensor of many gigabytes: the rows of one chunk lie further apart than 32 bits reach."""
+    heads = 2
+    c = inputs.attention_case(T + d, T, heads, d, n_q, dtype)
+    want = oracle.attention(f64(c["q"]), f64(c["k"]), f64(c["v"]), c["scale"])
+    big = torch.empty((T, apart), dtype=DT[dtype], device="cuda")
+    k, v = big[:, :heads * d].view(T, heads, d), big[:, heads * d:2 * heads * d].view(T, heads, d)
+    k.copy_(c["k"])
+    v.copy_(c["v"])
+    q = dev(c["q"])
+    nb = api.sige_sparse_attn_workspace_bytes(n_q, T, heads, d)
+    for ws in [None] + ([torch.empty(nb // 4, dtype=torch.float32, device="cuda")] if nb else []):
+        o = torch.full_like(q, 7.0)
+        api.sige_sparse_attn(q, k, v, o, c["scale"], workspace=ws)
+        torch.cuda.synchronize()
+        attn_close(o, want, DT[dtype], f"T={T} d={d}, workspace={ws is not None}")
+
+
 @pytest.mark.parametrize("dtype,res,b,heads,d,n", [("bf16", 32, 8, 8, 40, 3), ("f16", 16, 4, 4, 64, 16),
                                                    ("bf16", 20, 8, 2, 24, 4), ("f16", 64, 8, 8, 40, 1),
                                                    ("f32", 20, 8, 2, 24, 4), ("f32", 32, 8, 8, 40, 3)])

@@ -115,8 +115,13 @@ static int keys_per_chunk(int d, sige_dtype dt) { return dt == SIGE_F32 ? 32 : 3
 //
 // FAR: keys so far apart that the byte offsets of a chunk's rows do not fit 32 bits (a column of a tensor of gigabytes).  Those take
 // 64-bit offsets, in one kernel for all head sizes: eight tiles, the columns past the head zero.
+//
+// Registers: four waves on the same chunks hold heads of 97 to 128 in half of a SIMD's, two workgroups per compute unit - if told to:
+// free to take more the compiler spreads over 250 and moves the sums to the accumulation registers (fp16, heads of 128, 4000 queries
+// of 4096 x 8 154 -> 104 us with the splits of plan_attn, 64 of 1024 x 1 11.6 -> 8.0; larger heads do not fit, smaller ones are two
+// groups and have the bound as eight waves).
 template <typename T, int DT, int ODD, int NQ, int NK, bool FAR = false>
-__global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 ? 2 : 1) void attn_kernel(AttnArgs a)
+__global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) ? 2 : 1) void attn_kernel(AttnArgs a)
 {
     constexpr int NW = NQ * NK;
     constexpr int KT = key_tiles(DT);

@@ -448,7 +448,9 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     const int wk = wave % WK, wmn = wave / WK;
     const int wm = wmn / WN, wn = wmn - wm * WN;
     const int half = lane >> 5, l32 = lane & 31;
-    const int lt = lane % TILE, quarter = lane / TILE;        // row (or channel) and K share of this lane in an MFMA tile
+    // row (or channel) and K share of this lane in an MFMA tile (half and l32 by name: worked out anew for the 32-wide tiles they cost
+    // the 128 x 128 kernels one register more than there are)
+    const int lt = NARROW ? lane & 15 : l32, quarter = NARROW ? lane >> 4 : half;
     const int trow0 = band_row0 * a.stride;                   // first staged tile row
 
     // LDS byte offset of this lane's A row for each of its M tiles (clamped to a valid pixel)
@@ -697,8 +699,9 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
                 fetch(ring[d], ch0, d / KW, d % KW);
                 // in the order of the steps: loads return in issue order, and left free the scheduler mixes them so that every
                 // chunk's first step waits for the whole ring (1280 -> 1280 on three 8x8 blocks 20.6 -> 19.6 us; with chunks of
-                // four K steps, whose ring is the chunk, it is the barriers that cost: 960 -> 320 on ten 17.5 -> 18.5)
-                if constexpr (ONCE || KC >= 8) __builtin_amdgcn_sched_barrier(0);
+                // four K steps, whose ring is the chunk, it is the barriers that cost: 960 -> 320 on ten 17.5 -> 18.5; in the marked
+                // pair they cost scalar registers that it does not have: 128 + 256 -> 128 11.9 us with them, 11.6 without)
+                if constexpr (ONCE || (KC >= 8 && !MARKED)) __builtin_amdgcn_sched_barrier(0);
             }
         };
         if constexpr (MODE == kPlain) fill_ring(0, D);

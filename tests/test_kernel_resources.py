@@ -62,3 +62,11 @@ def test_attention_registers_for_two_workgroups(kernels):
     assert len(mine) == 4
     for n, k in mine.items():
         assert _registers(k) <= 256, (n, _registers(k))
+
+
+@pytest.mark.parametrize("name", ["conv_kernel", "conv_pair_kernel", "pointwise_kernel"])
+def test_no_scratch_memory(kernels, name):
+    """Everything a kernel holds is in registers and LDS: no spills, no arrays in memory."""
+    mine = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if name in n}
+    assert mine
+    assert not any(mine.values()), [n for n, size in mine.items() if size]

@@ -92,6 +92,9 @@ constexpr int v_row_bytes(int DT) { return 64 * (DT | 1); }
 constexpr int max_waves(int DT) { return DT <= 4 ? 8 : 4; }
 // key groups of a workgroup whose four waves share their chunks
 constexpr int common_groups(int DT) { return DT <= 3 ? 2 : 1; }
+// one wave per key group: whether Q waits in LDS for its products instead of in registers (K, V, Q and the sums of heads of 225 to 256
+// are more than a wave has: 20 to 51 registers of it went through memory, fp16 1500 of 4096 x 8 of 256 360 us in one split, 177 so)
+constexpr bool q_in_lds(int DT, int NQ) { return NQ == 1 && DT == 8; }
 static int keys_per_chunk(int d, sige_dtype dt) { return dt == SIGE_F32 ? 32 : 32 * key_tiles((d + 31) / 32); }
 
 // DT = 32-wide tiles over d; ODD: d takes an odd number of 16-wide steps (d % 32 is 8 or 16), so the
@@ -129,6 +132,7 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) 
     constexpr int VROW = v_row_bytes(DT);
     constexpr int DK = 2 * DT - ODD;               // 16-wide steps over d for S^T
     constexpr int GT = 64 * NQ;                    // threads that have a chunk in common
+    constexpr bool Q_LDS = q_in_lds(DT, NQ);
     using Off = std::conditional_t<FAR, unsigned long, unsigned>;
     static_assert(!FAR || (NQ > 1 && ODD == 0), "any head size: through LDS, no column of ones");
     constexpr int NV = (KCH * (4 * DT - 2 * ODD) + GT - 1) / GT;   // V (and K) vectors a thread stages per chunk, at most
@@ -148,6 +152,7 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) 
     const int vs0 = wk * (KCH * VROW);             // this group's V rows, then the groups' K rows
     char* const vs = lds + vs0;
     char* const ks = lds + NK * KCH * VROW + wk * (KCH * k_stride);
+    char* const qs = lds + NK * KCH * VROW;        // Q_LDS: [DK][64 lanes], behind the V rows
 
     const int chunks_total = (a.T + KCH - 1) / KCH;
     const int c_begin = blockIdx.z * a.chunks_per_split;
@@ -215,6 +220,12 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) 
         qf[s] = u32x4{0u, 0u, 0u, 0u};
         if (q_ok && dd < d)
             qf[s] = *(const u32x4*)((const char*)a.q + (qrow * a.q_ld + head * d + dd) * 2);
+    }
+    if constexpr (Q_LDS) {                         // (the waves have the same queries)
+#pragma unroll
+        for (int s = 0; s < DK; ++s)
+            if (s % NK == wk) *(u32x4*)(qs + s * 1024 + lane * 16) = qf[s];
+        __syncthreads();
     }
     // columns d .. DT*32 of the wave's V rows never receive data: zero them once (column d: ones, see above)
     constexpr uint32_t ONE = std::is_same<T, bf16>::value ? 0x3f80u : 0x3c00u;
@@ -284,7 +295,8 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) 
             if constexpr (NQ == 1) {
                 if (k_tail) kreg[kt * DK + DK - 1] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-                for (int s = 0; s < DK; ++s) Mma16<T>::run(as_uint4(kreg[kt * DK + s]), as_uint4(qf[s]), sacc[kt]);
+                for (int s = 0; s < DK; ++s)
+                    Mma16<T>::run(as_uint4(kreg[kt * DK + s]), as_uint4(Q_LDS ? *(const u32x4*)(qs + s * 1024 + lane * 16) : qf[s]), sacc[kt]);
             } else {
                 // all K fragments of the tile first (independent LDS reads, one latency), then the MFMAs
                 u32x4 kf[DK];
@@ -787,7 +799,8 @@ template <typename T, int DT, int NQ, int NK, bool FAR = false>
 static int launch_attn_dt(const AttnArgs& a, hipStream_t st)
 {
     constexpr int KCH = 32 * key_tiles(DT);
-    const size_t lds = std::max((size_t)NK * KCH * (v_row_bytes(DT) + (NQ > 1 ? (FAR ? 32 * DT : a.d) * 2 + 16 : 0)),
+    const size_t lds = std::max((size_t)NK * KCH * (v_row_bytes(DT) + (NQ > 1 ? (FAR ? 32 * DT : a.d) * 2 + 16 : 0)) +
+                                    (q_in_lds(DT, NQ) ? 2 * DT * 1024 : 0),
                                 NK == 1 ? 0 : (size_t)NK * NQ * 32 * (a.d + 4) * sizeof(float));
     dim3 grid((a.Nq + 32 * NQ - 1) / (32 * NQ), a.heads, a.splits);
     const bool odd = ((a.d + 15) / 16) & 1;        // d % 32 is 8 or 16

@@ -64,7 +64,7 @@ def test_attention_registers_for_two_workgroups(kernels):
         assert _registers(k) <= 256, (n, _registers(k))
 
 
-@pytest.mark.parametrize("name", ["conv_kernel", "conv_pair_kernel", "pointwise_kernel"])
+@pytest.mark.parametrize("name", ["conv_kernel", "conv_pair_kernel", "pointwise_kernel", "attn_kernel", "attn_f32_kernel", "attn_merge_kernel", "gn_"])
 def test_no_scratch_memory(kernels, name):
     """Everything a kernel holds is in registers and LDS: no spills, no arrays in memory."""
     mine = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if name in n}

@@ -358,7 +358,9 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     const bool can_ahead = nch > p->ksplit && (p->cfg == 6 || (p->cfg == 3 && g->k == 3 && (p->kc == 4 || p->kc == 8) &&
                                                                a.scale == nullptr && a.act == SIGE_ACT_NONE &&
                                                                vectors <= 256L * pipe_vectors(p->kc, p->kc == 4 ? kAheadWide : kAhead)));
-    const bool wide = can_ahead && p->cfg == 3 && vectors > 256L * pipe_vectors(p->kc, kAhead);
+    int mode_ahead = kAhead;                                // by the size of the tile; chunks of eight K steps have the one variant
+    for (int m : {kAheadMid, kAheadWide})
+        if (p->cfg == 3 && p->kc == 4 && vectors > 256L * pipe_vectors(4, mode_ahead)) mode_ahead = m;
     const int ahead = knob(SIGE_KNOB_CONV_AHEAD);           // 0 = never, 1 = refuse what cannot
     SIGE_REQUIRE(ahead < 1 || can_ahead, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
     // One chunk per workgroup (the whole of Cin staged at once, or as many shares as chunks): requested in one go where
@@ -366,7 +368,7 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     const int threads = kCfg[p->cfg].WK == 8 ? 512 : 256;
     const bool can_once = kCfg[p->cfg].WK > 1 && (g->k == 3 || g->k == 1) && nch == p->ksplit &&
                           (long)p->G * p->trows * tw <= (long)once_vectors(p->kc, p->cfg >= 5 ? 1 : 2) * (threads / (2 * p->kc));
-    p->mode = can_ahead && ahead != 0 ? (wide ? kAheadWide : kAhead) : can_once && ahead != 0 ? kOnce : kPlain;
+    p->mode = can_ahead && ahead != 0 ? mode_ahead : can_once && ahead != 0 ? kOnce : kPlain;
     a.d_pb = fast_div(p->rows * g->block_w);
     a.d_per = fast_div(p->trows * tw);
     a.d_tw = fast_div(tw);

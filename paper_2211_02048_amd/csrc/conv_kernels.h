@@ -310,11 +310,13 @@ constexpr int ring_depth(int steps, int limit)
 // kAhead  the next chunk's pixels are requested while the current chunk is multiplied
 // kOnce   the workgroup has one chunk: its tile and its first weights are requested together, nothing is fetched twice
 enum ChunkMode { kPlain = 0, kAhead = 1, kOnce = 2 };
-// kAheadWide  ... with the larger tiles of stride 2 (17 x 17 and 9 x 33), in chunks of four K steps
-enum { kAheadWide = 3 };
+// kAheadMid, kAheadWide  ... with larger tiles, in chunks of four K steps: several small blocks (four of 4 x 4, seven of 3 x 3, sixteen
+//         of 2 x 2) and 13 x 13 of stride 2; 17 x 17 and 9 x 33 of stride 2
+enum { kAheadWide = 3, kAheadMid = 4 };
 // 16-byte vectors per thread of a chunk that is requested ahead; a tile that is smaller asks for its last pixels again, so the number
-// follows the tiles: 320 -> 320 on 35 8x8 blocks, chunks of four K steps, 14.5 us with ten vectors, 13.8 with eight, 12.0 with four
-constexpr int pipe_vectors(int kc, int mode) { return mode == kAheadWide ? 10 : kc == 4 ? 4 : 8; }
+// follows the tiles: 320 -> 320 on 35 8x8 blocks, chunks of four K steps, 14.5 us with ten vectors, 13.8 with eight, 12.0 with four;
+// on 150 4x4 blocks, which take five, 14.9 with ten, 13.7 with eight
+constexpr int pipe_vectors(int kc, int mode) { return mode == kAheadWide ? 10 : mode == kAheadMid || kc != 4 ? 8 : 4; }
 // ... and of a chunk that is requested at once: the tile of a 16 x 16 or 8 x 8 block's band with a halo of one, by the K steps of
 // the chunk and the 32-row tiles of the patch (a fixed number: under a condition, uniform or not, the compiler waits for each)
 constexpr int once_vectors(int kc, int tm)
@@ -340,7 +342,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
     constexpr int NT = 64 * WM * WN * WK;                     // threads per workgroup
     static_assert(NT == 256 || NT == 512, "four or eight waves per workgroup");
     static_assert(KC % WK == 0, "waves that split K take whole K steps");
-    constexpr bool PIPE = MODE == kAhead || MODE == kAheadWide, ONCE = MODE == kOnce;
+    constexpr bool PIPE = MODE == kAhead || MODE == kAheadMid || MODE == kAheadWide, ONCE = MODE == kOnce;
     static_assert(!ONCE || (WK > 1 && KK > 0), "one chunk at once: the shapes whose waves split K");
     constexpr int KS = Mma<T>::KSTEP;
     constexpr int S = (int)sizeof(T);
@@ -1567,7 +1569,10 @@ int launch_kc(const ConvArgs& a, const ConvPlan& p, hipStream_t st)
         if constexpr ((KC == 4 || KC == 8) && KK == 9)
             if (p.mode == kAhead) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kAhead>(a, p, st);
         if constexpr (KC == 4 && KK == 9)
+        {
+            if (p.mode == kAheadMid) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kAheadMid>(a, p, st);
             if (p.mode == kAheadWide) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kAheadWide>(a, p, st);
+        }
         if constexpr (KC % 4 == 0 && (KC <= 8 || (KC == 20 && KK == 9))) {
             if (p.mode == kOnce) return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK, kOnce>(a, p, st);
             return launch_cfg<T, 2, 1, 1, 1, 4, KC, KK>(a, p, st);

@@ -1332,6 +1332,8 @@ def test_recorded_calls_repeat_the_step():
     ("bf16", 384, 72, 24, 24, 8, "", {}),                                # three chunks of 128, 10 x 10 tiles
     ("f16", 256, 40, 37, 50, 16, "", {}),                                # two chunks, row bands, ragged edges and channels
     ("bf16", 256, 64, 21, 19, 4, "", dict(CONV_KC=4)),       # four blocks per workgroup, chunks of 64
+    ("f16", 192, 64, 20, 22, 3, "", dict(CONV_KC=4)),        # seven blocks: six vectors per thread
+    ("f32", 96, 40, 19, 21, 2, "", dict(CONV_KC=4)),         # sixteen: eight, the most of their variant
     ("f16", 640, 64, 16, 16, 8, "", dict(CONV_KC=8, CONV_SPLIT=2)),      # shares of two and three chunks
     ("bf16", 960, 64, 16, 16, 8, "", dict(CONV_KC=4, CONV_SPLIT=10)),    # shares of one and two
     ("f32", 192, 40, 20, 20, 6, "", dict(CONV_KC=8)),

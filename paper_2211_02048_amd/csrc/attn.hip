@@ -745,13 +745,15 @@ static int launch_merge(const AttnArgs& a, hipStream_t st)
 // How a call is cut.  Single precision: a workgroup (128 queries) walks through its key chunks one after the other and each
 // costs a staging round trip, so few queries are spread over about two workgroups per compute unit (more
 // splits cost the merge kernel more than they save: measured at 64 to 1280 queries), at least 2 chunks each.
-// Half types: the cheapest of three forms and their splits over workgroups by a model of measured times (24 calls of 24 to 9216
-// queries on 77 to 9216 keys, one head to eight, each form with up to twelve splits; the choice is within 5 % of the best of them but
-// for 4096 x 4096 of 40: 69 against 62 us).  What it trades: four waves on the same chunks fetch them once, waves with chunks of their
-// own have no barriers and need no merge kernel (5 us with its launch, and 0.4 us per megabyte of partial sums) where a call has
-// enough queries to fill the chip.
+// Half types: the cheapest of three forms and their splits over workgroups by a model of measured times (1400 calls of 24 to 4000
+// queries on 77 to 9216 keys, heads of 24 to 256, one to eight of them, each form with every number of splits near its
+// best: 18000 times; the choice takes 1.01 times the best of them in the mean, 1.2 at worst; of the times before waves split the keys it makes 0.83 in the mean and 1.14 at worst, the model of 24 calls made 0.87 and 1.30).  What it trades:
+// four waves on the same chunks fetch them once; waves with chunks of their own have no barriers and no partial sums for a merge kernel
+// (3 us, and 2.75 per million of them) where a call has enough queries to fill the chip, but fetch K in pieces of 32 bytes of a row, which
+// costs more where the rows of a head are not side by side.
 struct AttnForm { int nq, nk, splits; };           // waves with the same chunks, key groups, splits over workgroups
-static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt)
+// room: floats of workspace, what the splits' partial sums have to fit into.
+static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt, size_t room = ~(size_t)0)
 {
     const int KCH = keys_per_chunk(d, dt);
     const int chunks = (T + KCH - 1) / KCH;
@@ -766,28 +768,39 @@ static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt)
         if (want < 1) want = 1;
         const int per = (int)((chunks + want - 1) / want);
         f.splits = (chunks + per - 1) / per;
+        if (f.splits > 1 && (size_t)f.splits * heads * Nq * (d + 4) > room) f.splits = 1;
         return f;
     }
-    // microseconds a workgroup takes beside its chunks, and per chunk of a wave, by 32-wide tiles of a head and form (four waves with
-    // the same chunks; one wave each, four of them; eight)
-    static const double fixed_us[9][3] = {{}, {4, 4, 4}, {3, 5, 5}, {5, 6.5, 6.5}, {7, 6.5, 6.5}, {7, 7.5, 0}, {7.5, 8, 0}, {7.75, 8.5, 0}, {8, 9, 0}};
-    static const double chunk_us[9][3] = {{}, {1.2, 0.85, 1.3}, {2.0, 1.35, 2.75}, {2.35, 2.2, 3.5}, {1.2, 1.28, 2.3}, {1.56, 1.5, 0}, {1.9, 2.5, 0},
-                                          {2.25, 4, 0}, {2.6, 5.5, 0}};
-    const int DT = (d + 31) / 32;
+    // by 16-wide steps over a head and form (four waves with the same chunks; one wave each, four of them; eight): microseconds of a
+    // workgroup beside its chunks, per chunk of a wave, and what several heads add to that; workgroups that a compute unit holds, by
+    // registers and LDS.  0: not built (heads of 88 or 96 in eight waves do not have the registers; four waves of their own on heads of 97
+    // to 128 are never the cheapest)
+    static const float fixed_us[17][3] = {{}, {3.72f, 3.09f, 3.54f}, {3.72f, 3.09f, 3.54f}, {2.86f, 4.16f, 4.19f}, {2.74f, 4.87f, 3.81f}, {3.59f, 6.14f, 3.76f},
+                                              {3.86f, 5.96f, 0}, {3.4f, 0, 5.04f}, {3.09f, 0, 5.24f}, {4.45f, 6.89f, 0}, {3.68f, 6.28f, 0},
+                                              {3.49f, 6.04f, 0}, {3.8f, 5.99f, 0}, {3.5f, 6.23f, 0}, {4.01f, 8.08f, 0}, {3.76f, 8.23f, 0}, {4.69f, 9.86f, 0}};
+    static const float chunk_us[17][3] = {{}, {1.23f, 0.85f, 0.96f}, {1.23f, 0.85f, 0.96f}, {1.53f, 1.19f, 1.56f}, {2.06f, 1.66f, 3.56f}, {1.83f, 1.72f, 2.81f},
+                                              {2.98f, 2.22f, 0}, {1.3f, 0, 2.07f}, {1.14f, 0, 2.8f}, {2.32f, 1.69f, 0}, {2.18f, 1.55f, 0},
+                                              {2.26f, 1.63f, 0}, {2.19f, 2.3f, 0}, {2.71f, 2.1f, 0}, {3.18f, 1.78f, 0}, {2.77f, 2.78f, 0}, {2.24f, 2.68f, 0}};
+    static const float heads_us[17][3] = {{}, {0.35f, 0.7f, 0.78f}, {0.35f, 0.7f, 0.78f}, {0.06f, 0.61f, 1.21f}, {0.04f, 0.28f, 0.92f}, {1.33f, 1.6f, 3.47f},
+                                              {0, 0.99f, 0}, {0.51f, 0, 2.41f}, {0.11f, 0, 0.6f}, {0.14f, 0.21f, 0}, {0.35f, 0.49f, 0},
+                                              {0.44f, 0.51f, 0}, {0.62f, 0.7f, 0}, {0.16f, 0.73f, 0}, {1.18f, 1.25f, 0}, {0.47f, 2.15f, 0}, {0.07f, 1.03f, 0}};
+    static const signed char held[9][3] = {{}, {2, 4, 2}, {2, 3, 1}, {2, 2, 1}, {1, 2, 1}, {1, 1, 1}, {1, 1, 1}, {3, 1, 1}, {2, 1, 1}};      // (one of each beyond)
+    const int DT = (d + 31) / 32, DK = (d + 15) / 16;
     double best_us = 1e30;
-    const bool odd = ((d + 15) / 16) & 1;
-    // (eight waves on heads of 88 or 96 do not have the registers)
-    for (int form = 0; form < (max_waves(DT) == 8 && (DT != 3 || odd) ? 3 : 2); ++form) {
+    for (int form = 0; form < 3; ++form) {
+        if (fixed_us[DK][form] == 0.0f) continue;
         const AttnForm g = form == 0 ? AttnForm{4, common_groups(DT), 1} : AttnForm{1, form == 1 ? 4 : 8, 1};
         const long base = (long)heads * ((Nq + 32 * g.nq - 1) / (32 * g.nq));
-        const bool two = form == 0 && (DT == 1 || (DT == 2 && odd));     // registers for two workgroups per compute unit
+        const int r = DK > 8 ? 1 : held[DK][form];
         for (int z = 1; z <= 64 && (z == 1 || z * g.nk <= chunks); ++z) {
             const int per = (chunks + z - 1) / z, real = (chunks + per - 1) / per;
+            if (real > 1 && (size_t)real * heads * Nq * (d + 4) > room) break;
             const long on_one = (base * real + 255) / 256;      // workgroups of the fullest compute unit
-            const double chunk = (per + g.nk - 1) / g.nk * chunk_us[DT][form];
-            const double us = two ? on_one / 2 * (fixed_us[DT][form] + 1.7 * chunk) + on_one % 2 * (fixed_us[DT][form] + chunk)
-                                  : on_one * (fixed_us[DT][form] + chunk);
-            const double merge = real == 1 ? 0.0 : (real > 16 ? 7.0 : 5.0) + 1.6e-6 * real * heads * Nq * (d + 4);
+            const double chunk = (per + g.nk - 1) / g.nk * (chunk_us[DK][form] + (heads > 1 ? heads_us[DK][form] : 0.0f));
+            // workgroups side by side lengthen each other's chunks; the fixed part of the next ones runs beside the chunks of those before
+            const double us = fixed_us[DK][form] * (1.0 + 0.5 * ((on_one + r - 1) / r - 1)) + on_one / r * chunk * (1.0 + 0.4 * (r - 1)) +
+                              (on_one % r ? chunk * (1.0 + 0.4 * (on_one % r - 1)) : 0.0);
+            const double merge = real == 1 ? 0.0 : (real > 16 ? 3.3 : 3.0) + 2.75e-6 * real * heads * Nq * (d + 4);
             const double cost = target >= 0 ? std::abs(target - (double)base * real) : us + merge;
             if (cost < best_us) { best_us = cost; f = g; f.splits = real; }
         }
@@ -827,7 +840,8 @@ static int launch_attn_form(const AttnArgs& a, const AttnForm& f, hipStream_t st
     if (f.nq == 4) return launch_attn_dt<T, DT, 4, common_groups(DT)>(a, st);
     if constexpr (max_waves(DT) == 8)
         if (f.nk == 8) return launch_attn_dt<T, DT, 1, 8>(a, st);
-    return launch_attn_dt<T, DT, 1, 4>(a, st);
+    if constexpr (DT != 4) return launch_attn_dt<T, DT, 1, 4>(a, st);
+    return fail(SIGE_ERR_UNSUPPORTED, "sige_sparse_attn: internal: four waves of their own on heads of %d", a.d);
 }
 
 // One instantiation per number of 32-wide tiles: the steps over d, the spare columns of V and the tile that holds the column of ones
@@ -922,13 +936,9 @@ static int attn_entry(const char* who, AttnArgs& a, const void* q, int32_t q_ld,
     const sige_dtype cut = far ? SIGE_F32 : dt;
     const int KCH = keys_per_chunk(d, cut);
     const int chunks = (T + KCH - 1) / KCH;
-    const AttnForm f = plan_attn(Nq, T, heads, d, cut);
-    int splits = f.splits;
-    if (splits > 1 && (workspace == nullptr ||
-                       workspace_bytes < (size_t)splits * heads * Nq * (d + 4) * sizeof(float) ||
-                       (reinterpret_cast<uintptr_t>(workspace) & 15u)))
-        splits = 1;
-    a.chunks_per_split = (chunks + splits - 1) / splits;
+    const bool room = workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+    const AttnForm f = plan_attn(Nq, T, heads, d, cut, room ? workspace_bytes / sizeof(float) : 0);
+    a.chunks_per_split = (chunks + f.splits - 1) / f.splits;
     a.splits = (chunks + a.chunks_per_split - 1) / a.chunks_per_split;
     hipStream_t st = (hipStream_t)stream;
     if (dt == SIGE_F32) return launch_attn_f32(a, st);

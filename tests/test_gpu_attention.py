@@ -117,6 +117,52 @@ def test_sparse_attention_heads_of_seven_tiles(oracle, T, d, dtype):
                 attn_close(o[:, first:last], want[:, first:last], DT[dtype], f"heads {first}..{last - 1} of {d}, {wgs} workgroups")
 
 
+@pytest.mark.parametrize("T,heads,d,n_q,dtype,wgs", [
+    (1024, 8, 72, 192, "bf16", 128), (512, 8, 88, 24, "bf16", 32), (512, 8, 160, 24, "bf16", 128), (1024, 8, 256, 64, "f16", 128),
+    (1024, 1, 128, 24, "f16", 32), (4096, 8, 64, 64, "f16", 256), (9216, 8, 40, 96, "bf16", 232),
+    (4096, 8, 128, 1500, "f16", 384), (1024, 4, 96, 800, "bf16", 100),
+])
+def test_sparse_attention_cut_is_near_the_best(T, heads, d, n_q, dtype, wgs):
+    """The cut chosen for a call against others it may be given (the knob: the number of workgroups nearest to wgs, a half and a quarter
+    of it and twice as many): at most a quarter slower than the fastest, both replayed from graphs; and a workspace that holds fewer
+    splits than wanted is used for as many as it holds."""
+    c = inputs.attention_case(T + d, T, heads, d, n_q, dtype)
+    q, k, v = dev(c["q"]), dev(c["k"]), dev(c["v"])
+    nb = 64 * heads * n_q * (d + 4)
+    ws = torch.empty(nb, dtype=torch.float32, device="cuda")
+    o = torch.empty_like(q)
+
+    def graphed():
+        g = torch.cuda.CUDAGraph()
+        api.sige_sparse_attn(q, k, v, o, c["scale"], workspace=ws)
+        with torch.cuda.graph(g):
+            for _ in range(20):
+                api.sige_sparse_attn(q, k, v, o, c["scale"], workspace=ws)
+        return g
+
+    graphs = {}
+    for n in (None, wgs // 4, wgs // 2, wgs, 2 * wgs):
+        with api.knobs(ATTN_WGS=n):
+            graphs[n] = graphed()
+    us = {n: 1e9 for n in graphs}
+    for _ in range(7):                      # in turn, the fastest replay of each
+        for n, g in graphs.items():
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g.replay()
+            b.record()
+            b.synchronize()
+            us[n] = min(us[n], a.elapsed_time(b) * 50)
+    assert us[None] <= 1.25 * min(us.values()), us
+    want = o.clone()
+    for part in (2, 3, 5):                  # the workspace of that many splits
+        small = ws[:part * heads * n_q * (d + 4)]
+        o.fill_(7.0)
+        api.sige_sparse_attn(q, k, v, o, c["scale"], workspace=small)
+        torch.cuda.synchronize()
+        assert_close(o, f64(want), DT[dtype], f"{part} splits fit")      # (sums in fp32 either way: a unit in the last place, 2^-7 in bf16)
+
+
 @pytest.mark.parametrize("d,dtype", [(40, "bf16"), (64, "f16"), (96, "bf16"), (128, "f16"), (160, "bf16"), (224, "f16"), (256, "bf16")])
 def test_sparse_attention_keys_taken_out(oracle, d, dtype):
     """Keys whose logits are -inf (the last value of every query is one, theirs -inf): runs of them that fill whole chunks, so that

@@ -481,7 +481,8 @@ int sige_version(void);
  *                      instead of straight from the registers
  *   CONV_LDS_PAD       bytes between the staged pixels' channel runs in LDS (a multiple of 16)
  *   CONV_AHEAD         requests ahead in the shapes whose waves split K (the next chunk, or the only one at once): 0 = never,
- *                      1 = a tiled call that cannot request its next chunk ahead ends in SIGE_ERR_UNSUPPORTED                                                             */
+ *                      1 = a tiled call that cannot request its next chunk ahead ends in SIGE_ERR_UNSUPPORTED,
+ *                      2 = one that cannot request its only chunk at once does                                */
 typedef enum {
     SIGE_KNOB_CONV_CFG = 0, SIGE_KNOB_CONV_KC = 1, SIGE_KNOB_CONV_SPLIT = 2, SIGE_KNOB_CONV_HALF = 3,
     SIGE_KNOB_CONV_SPLIT_WGS = 4, SIGE_KNOB_CONV_POINTWISE = 5, SIGE_KNOB_CONV_POINTWISE_W4 = 6,

@@ -361,13 +361,14 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     int mode_ahead = kAhead;                                // by the size of the tile; chunks of eight K steps have the one variant
     for (int m : {kAheadMid, kAheadWide})
         if (p->cfg == 3 && p->kc == 4 && vectors > 256L * pipe_vectors(4, mode_ahead)) mode_ahead = m;
-    const int ahead = knob(SIGE_KNOB_CONV_AHEAD);           // 0 = never, 1 = refuse what cannot
-    SIGE_REQUIRE(ahead < 1 || can_ahead, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
+    const int ahead = knob(SIGE_KNOB_CONV_AHEAD);           // 0 = never, 1 / 2 = refuse what cannot
+    SIGE_REQUIRE(ahead < 1 || ahead == 2 || can_ahead, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is set and this call cannot request its chunks ahead", who);
     // One chunk per workgroup (the whole of Cin staged at once, or as many shares as chunks): requested in one go where
     // the tile is one batch of vectors for the threads that stage (2 * kc vectors per pixel, whole pixels per step).
     const int threads = kCfg[p->cfg].WK == 8 ? 512 : 256;
     const bool can_once = kCfg[p->cfg].WK > 1 && (g->k == 3 || g->k == 1) && nch == p->ksplit &&
                           (long)p->G * p->trows * tw <= (long)once_vectors(p->kc, p->cfg >= 5 ? 1 : 2) * (threads / (2 * p->kc));
+    SIGE_REQUIRE(ahead != 2 || can_once, SIGE_ERR_UNSUPPORTED, "%s: CONV_AHEAD is 2 and this call cannot request its chunk at once", who);
     p->mode = can_ahead && ahead != 0 ? mode_ahead : can_once && ahead != 0 ? kOnce : kPlain;
     a.d_pb = fast_div(p->rows * g->block_w);
     a.d_per = fast_div(p->trows * tw);

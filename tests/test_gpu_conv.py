@@ -1409,7 +1409,11 @@ def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, form, kn
 @pytest.mark.parametrize("dtype,Cin,Cout,H,W,b,form,shape,kn", [
     ("f16", 128, 96, 40, 44, 16, "silu", 3, dict(CONV_CFG=3, CONV_KC=8)),        # one chunk, arithmetic on the way in
     ("f32", 32, 40, 21, 23, 6, "silu", 3, dict(CONV_CFG=3, CONV_KC=4)),          # ragged blocks and channels
-    ("bf16", 64, 48, 24, 20, 4, "copies", 3, dict(CONV_CFG=3, CONV_KC=4)),       # four blocks per workgroup
+    ("bf16", 64, 48, 24, 20, 5, "copies", 3, dict(CONV_CFG=3, CONV_KC=4)),       # two blocks per workgroup
+    ("f16", 320, 40, 21, 23, 5, "", 3, {}),                                      # ... of the whole of 320 channels
+    ("f16", 128, 64, 22, 26, 8, "stored", 3, dict(CONV_CFG=3, CONV_KC=8)),       # stored tiles, one block and two
+    ("bf16", 64, 48, 24, 20, 5, "stored", 3, dict(CONV_CFG=3, CONV_KC=4)),
+    ("bf16", 512, 40, 21, 23, 5, "stored", 4, {}),
     ("f16", 128, 64, 27, 29, 6, "1x1", 3, dict(CONV_CFG=3, CONV_KC=8)),
     ("bf16", 320, 72, 20, 22, 8, "copies", 7, {}),                               # the whole of 320 channels, 32 rows
     ("f16", 320, 64, 22, 26, 8, "up", 7, {}),
@@ -1425,8 +1429,8 @@ def test_conv_chunks_requested_ahead(oracle, dtype, Cin, Cout, H, W, b, form, kn
 ])
 def test_conv_chunk_requested_at_once(oracle, dtype, Cin, Cout, H, W, b, form, shape, kn):
     """Shapes whose waves split K, one chunk per workgroup (or two in the 32 x 16 patches): tile and weights requested
-    together.  Against the oracle, with the plan's shape as named; where the plan without it (CONV_AHEAD=0) has the same
-    shape the sums have the same order: equal bit for bit."""
+    together (CONV_AHEAD=2 refuses a call that does not, 1 one of two chunks).  Against the oracle, with the plan's shape as
+    named; where the plan without it (CONV_AHEAD=0) has the same shape the sums have the same order: equal bit for bit."""
     rng = np.random.default_rng(7 * Cin + Cout + H)
     td = DT[dtype]
     up, k, staged = int(form == "up"), 1 if form == "1x1" else 3, form == "silu"
@@ -1452,7 +1456,21 @@ def test_conv_chunk_requested_at_once(oracle, dtype, Cin, Cout, H, W, b, form, s
     asc, ash = torch.full((Cout,), 0.75, device="cuda"), torch.full((Cout,), -0.25, device="cuda")
     kn = {**dict(CONV_POINTWISE=0), **kn}
     got, shapes = [], []
-    for ahead in (-1, 0):
+    ahead_of = (1 if Cin == 1024 else 2, 0)
+    if form == "stored":
+        tiles = torch.from_numpy(rng.standard_normal((n, conv.g.tile_h, conv.g.tile_w, Cin)).astype(np.float32)).to(td)
+        for ahead in ahead_of:
+            out = torch.full((n + 1, b, b, Cout), 5.0, dtype=td, device="cuda")
+            with api.knobs(CONV_AHEAD=ahead, **kn):
+                shapes.append(api.sige_conv_plan(td, conv.g, Cin, Cout, n, workspace_bytes=0).shape)
+                api.sige_conv(dev(tiles), conv.g, Cin, Cout, conv.packed, conv.bias, bl.count, out, n_blocks=n, max_blocks=n)
+            got.append(out)
+        assert shapes == [shape, shape] and torch.equal(got[0], got[1])
+        want = np.stack([oracle.conv2d(f64(t), f64(w), f64(bias), 1, 0) for t in tiles])
+        assert_close(got[0][:n], want, td, "stored tiles")
+        assert (got[0][n:] == 5.0).all()
+        return
+    for ahead in ahead_of:
         y = dev(cache).clone()
         copy = torch.full((H, W, Cout), 3.0, dtype=td, device="cuda")
         aos = api.act_out_array([(copy, asc, ash, api.ACT_SILU)]) if form == "copies" else None

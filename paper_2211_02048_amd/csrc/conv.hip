@@ -25,6 +25,8 @@
 // instantiated once per storage type in conv_f32.hip, conv_f16.hip and conv_bf16.hip.
 #include "conv_kernels.h"
 
+#include <climits>
+
 namespace sige {
 
 // instantiated in conv_f32.hip, conv_f16.hip and conv_bf16.hip
@@ -34,9 +36,10 @@ SIGE_CONV_LAUNCHERS(extern, bf16)
 
 // Chooses the workgroup shape and the staged channel chunk for one call, then - when the caller
 // gave a workspace (partial_elems = fp32 elements it holds) and the call has few workgroups but a
-// long K - how many workgroups share one output patch along K.
+// long K - how many workgroups share one output patch along K.  most: workgroups up to which the shapes that stage
+// the whole of Cin may cut their patches smaller (fused_pair).
 static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, size_t s, int kstep,
-                      int nblocks, size_t partial_elems, bool staged_math, ConvPlan* best)
+                      int nblocks, size_t partial_elems, bool staged_math, long most, ConvPlan* best)
 {
     // overrides for tests and tuning runs (sige_set_knob; -1 = automatic): the shape / the K steps per chunk
     const int force_cfg = knob(SIGE_KNOB_CONV_CFG), force_kc_v = knob(SIGE_KNOB_CONV_KC);
@@ -142,18 +145,19 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
         // on four 16x16 blocks 12.1 -> 10.1)
         const int half_knob = knob(SIGE_KNOB_CONV_HALF);     // most workgroups for which rows are halved
         const long half_max = half_knob >= 0 ? half_knob : 128;
-        if (q.kc && q.cfg == 4 && wgs4 <= half_max && pbfull >= 64 && g->block_w <= 32) {
+        const int rows32 = 32 / std::min((int)g->block_w, 32), bands32 = (g->block_h + rows32 - 1) / rows32;
+        if (q.kc && q.cfg == 4 && wgs4 <= half_max && pbfull >= 64 && g->block_w <= 32 && (long)nblocks * bands32 * q.slabs <= most) {
             q.cfg = 5;
             q.G = 1;
-            q.rows = 32 / g->block_w;
-            q.bands = (g->block_h + q.rows - 1) / q.rows;
+            q.rows = rows32;
+            q.bands = bands32;
             q.trows = (q.rows - 1) * g->stride + g->k;
             q.groups = nblocks;
             q.lds = lds_bytes(5, (long)q.trows * tw, q.kc);
             wgs4 = (long)q.groups * q.bands * q.slabs;
             // still at most 128 of them, half types: 16 output channels each (see NARROW in conv_kernels.h; 512 -> 512 at
             // 16 x 16 9.7 -> 7.7 us, at 8 x 8 10.1 -> 7.9), whose workgroups request everything ahead
-            if (s == 2 && wgs4 <= 128 && (q.kc == 32 || (q.kc == 16 && Cin == 16 * kstep)) && !force_whole && knob(SIGE_KNOB_CONV_AHEAD) != 0 &&
+            if (s == 2 && wgs4 <= 128 && (long)q.groups * q.bands * ((Cout + 15) / 16) <= most && (q.kc == 32 || (q.kc == 16 && Cin == 16 * kstep)) && !force_whole && knob(SIGE_KNOB_CONV_AHEAD) != 0 &&
                 (long)q.trows * tw <= (long)once_vectors(q.kc, 1) * (512 / (2 * q.kc))) {
                 q.cfg = 6;
                 q.slabs = (Cout + 15) / 16;
@@ -176,7 +180,8 @@ static bool plan_conv(const sige_geom* g, int th, int tw, int Cin, int Cout, siz
                 wgs4 = (long)q.groups * q.bands * q.slabs;
             }
         }
-        // (256 channels: with more workgroups the whole is 1 us faster alone, and a shortcut beside it no longer shares the launch: 17 -> 11)
+        // (256 channels: more than 128 workgroups of 64 rows and a shortcut's do not run in one round; the whole is 1 us faster alone there, and
+        // the shared launch 11 us where two are 17)
         if (q.kc && (wgs4 <= (Cin == 16 * kstep && q.cfg == 4 ? 128 : 256) || force_whole)) {
             q.Cc = q.kc * kstep;
             q.ps = (int)(q.Cc * s + pad_of(q.kc));
@@ -315,7 +320,7 @@ static bool few_rows_alone(const sige_geom* g, const ConvArgs& a, int ks, int nl
 // launched by itself it goes to the few-row kernel all the same (64 x 64 patches) ...
 static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int th, int tw, int Cin, int Cout,
                         int max_blocks, int n_blocks, int nl, ConvArgs& a, void* workspace, size_t workspace_bytes,
-                        ConvPlan* p, int* pointwise)
+                        ConvPlan* p, int* pointwise, long most = LONG_MAX)
 {
     const int ks = dt == SIGE_F32 ? 8 : 16;
     a.bh = g->block_h; a.bw = g->block_w; a.Cin = Cin; a.Cout = Cout; a.max_blocks = max_blocks; a.n_host = n_blocks;
@@ -327,7 +332,7 @@ static int prepare_conv(const char* who, sige_dtype dt, const sige_geom* g, int 
     const bool ws_ok = workspace != nullptr && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
     const bool planned = plan_conv(g, th, tw, Cin, Cout, dtype_size(dt), ks, nl,
                                    ws_ok && !a.glu ? workspace_bytes / sizeof(float) : 0,
-                                   a.scale != nullptr || a.act != SIGE_ACT_NONE, p);
+                                   a.scale != nullptr || a.act != SIGE_ACT_NONE, most, p);
     p->few_rows_alone = few_rows_alone(g, a, ks, nl, planned ? p : nullptr);
     if (!planned && p->few_rows_alone) {
         *pointwise = 2;
@@ -456,7 +461,7 @@ extern "C" size_t sige_conv_workspace_bytes(sige_dtype dt, const sige_geom* g, i
     size_t need = 0;
     for (int nl = 1; nl <= max_blocks; ++nl) {
         ConvPlan p;
-        if (!plan_conv(g, th, tw, Cin, Cout, dtype_size(dt), ks, nl, (size_t)1 << 40, true, &p)) return 0;
+        if (!plan_conv(g, th, tw, Cin, Cout, dtype_size(dt), ks, nl, (size_t)1 << 40, true, LONG_MAX, &p)) return 0;
         if (p.ksplit > 1) need = std::max(need, (size_t)p.ksplit * nl * g->block_h * g->block_w * Cout * sizeof(float));
         else if ((long)p.groups * p.bands * p.slabs > 256) break;   // more blocks only add workgroups
     }
@@ -718,15 +723,24 @@ static int fused_pair(const char* who, const sige_fused_conv_call* first, const 
     // with the same chunk: a 3x3 call first, a 1x1 call second (measured a gain up to the 1440
     // workgroups at which calls still take that shape: 23.3 vs 25.2 us; 11.4 vs 16.3 us at 560), unless the 1x1 call
     // by itself goes to the few-row kernel and the two are the faster way (shared_beats_few_rows)
-    const long wgs_both = nl[0] > 0 && nl[1] > 0 && !pw[0] && !pw[1]
-                              ? (long)p[0].groups * p[0].bands * p[0].slabs + (long)p[1].groups * p[1].bands * p[1].slabs
-                              : 0;
+    const auto wgs = [&](int i) { return (long)p[i].groups * p[i].bands * p[i].slabs; };
     const int pair_knob = knob(SIGE_KNOB_CONV_PAIR_WGS);     // most workgroups for which the calls share a launch
     const long pair_max = pair_knob >= 0 ? pair_knob : (1L << 30);
-    const bool together = nl[0] > 0 && nl[1] > 0 && wgs_both <= pair_max && !pw[0] && !pw[1] && c[0]->dt == c[1]->dt && a[0].k == 3 &&
-                          a[1].k == 1 && p[0].cfg == 3 && p[1].cfg == 3 && p[0].ksplit == 1 && p[1].ksplit == 1 &&
-                          p[0].kc == p[1].kc && (p[0].kc == 8 || p[0].kc == 4) &&
-                          (!p[1].few_rows_alone || shared_beats_few_rows(a[0], p[0], p[1], c[0]->dt == SIGE_F32 ? 8 : 16));
+    const bool fit = nl[0] > 0 && nl[1] > 0 && !pw[0] && !pw[1] && wgs(0) + wgs(1) <= pair_max && c[0]->dt == c[1]->dt && a[0].k == 3 &&
+                     a[1].k == 1 && p[1].cfg == 3 && p[0].ksplit == 1 && p[1].ksplit == 1;
+    // ... or when the 3x3 call takes an eight-wave shape with the whole of 256 channels at once and the 1x1 call chunks of eight K
+    // steps.  A compute unit holds one such workgroup: the 3x3 call's patches are cut only so far that both calls run in one round (the
+    // sums of a patch have the same order in all three shapes).  Two launches -> one, f16, weights from memory: 256 -> 128 + 128 on three
+    // 8x8 blocks 11.6 -> 6.4 us (in chunks of eight K steps beside each other 8.7), 256 -> 256 + 256 on sixteen 12.6 -> 8.4 (9.5),
+    // 256 -> 512 + 512 on one 16x16 block 12.6 -> 7.7 (10.4; not cut for one round: 11.9).
+    const bool whole = fit && p[0].cfg >= 4 && p[0].cfg <= 6 && p[0].kc == 16 && a[0].Cin == 256 && c[0]->dt != SIGE_F32 && p[1].kc == 8 &&
+                       !p[1].few_rows_alone;
+    if (whole && wgs(0) + wgs(1) > 256)
+        if (int rc = prepare_conv(who, c[0]->dt, c[0]->g, th[0], tw[0], c[0]->Cin, c[0]->Cout, c[0]->max_blocks, c[0]->n_blocks, nl[0],
+                                  a[0], c[0]->workspace, c[0]->workspace_bytes, &p[0], &pw[0], 256 - wgs(1)))
+            return rc;
+    const bool together = whole || (fit && p[0].cfg == 3 && p[0].kc == p[1].kc && (p[0].kc == 8 || p[0].kc == 4) &&
+                                    (!p[1].few_rows_alone || shared_beats_few_rows(a[0], p[0], p[1], c[0]->dt == SIGE_F32 ? 8 : 16)));
     bool scan = false;
     if (marks != nullptr) {
         // the one-launch kernel builds the lists itself when a workgroup can scan a whole block grid

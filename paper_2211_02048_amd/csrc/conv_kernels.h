@@ -378,8 +378,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         // Nobody touches the other half during this step, so the call's first workgroup clears it
         // and advances the first phase word: the next marking pass finds a clean half without any
         // workgroup having to wait for the others to finish reading this one.
-        static_assert(NT == 256, "marked mode is built for the four-wave shape");
-        __shared__ int wtot[4];
+        __shared__ int wtot[NT / 64];                         // (up to 1024 flags: the first 256 threads have them all)
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         const uint32_t* words = reinterpret_cast<const uint32_t*>(a.mk_flags);
         const int hw = a.mk_half >> 2;
@@ -404,7 +403,7 @@ __device__ __forceinline__ void conv_body(const ConvArgs& a, const int bx, const
         __syncthreads();
         int off = 0, total = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NT / 64; ++i) {
             const int t = wtot[i];
             if (i < wave) off += t;
             total += t;
@@ -1069,26 +1068,51 @@ __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK > 4 ? 1 : 2)) void
 // MARKED: the launch follows the marking pass directly, without the compaction pass in between (on
 // this part a dependent launch costs more than the compaction's work): every workgroup derives its
 // blocks from the flags (see conv_body).
-template <typename T, int KC, bool MARKED, int MODE>
-__global__ __launch_bounds__(256, 2) void conv_pair_kernel(ConvArgs a, ConvArgs b, int wgs_a, FastDiv xa, FastDiv ya,
-                                                           int ta, FastDiv xb, FastDiv yb, int tb)
+//
+// A one-dimensional grid: the first call's workgroups, then the second's.  Consecutive workgroups go to the eight XCDs in turn and
+// each XCD has its own L2, so the workgroups that read the same input tile (one per slab of output channels) are numbered
+// eight apart: they land on one XCD and the tile leaves HBM once instead of once per slab.
+struct PairGrid { int wgs_a, ta, tb; FastDiv xa, ya, xb, yb; };   // workgroups of the first call; tiles = bands * groups; slabs, bands
+template <int APART>                                              // 8, or 1: in the order of a call by itself
+__device__ __forceinline__ bool pair_place(const PairGrid& g, bool& first, int& bx, int& by, int& bz)
 {
-    // A one-dimensional grid: the first call's workgroups, then the second's.  Consecutive workgroups
-    // go to the eight XCDs in turn and each XCD has its own L2, so the workgroups that read the same
-    // input tile (one per 32-wide slab of output channels) are numbered eight apart: they land on one
-    // XCD and the tile leaves HBM once instead of once per slab.  (ta, tb: tiles = bands * groups.)
     int id = blockIdx.x;
-    const bool first = id < wgs_a;
-    if (!first) id -= wgs_a;
-    const FastDiv nx = first ? xa : xb, ny = first ? ya : yb;
-    const int nt = first ? ta : tb;
-    int jt, bx, bz, by;
-    divmod(id >> 3, nx, jt, bx);
-    const int tile = jt * 8 + (id & 7);
-    if (tile >= nt) return;
+    first = id < g.wgs_a;
+    if (!first) id -= g.wgs_a;
+    const FastDiv nx = first ? g.xa : g.xb, ny = first ? g.ya : g.yb;
+    int jt;
+    divmod(id / APART, nx, jt, bx);
+    const int tile = jt * APART + id % APART;
+    if (tile >= (first ? g.ta : g.tb)) return false;
     divmod(tile, ny, bz, by);
+    return true;
+}
+
+template <typename T, int KC, bool MARKED, int MODE>
+__global__ __launch_bounds__(256, 2) void conv_pair_kernel(ConvArgs a, ConvArgs b, PairGrid g)
+{
+    bool first;
+    int bx, by, bz;
+    if (!pair_place<8>(g, first, bx, by, bz)) return;
     if (first) conv_body<T, 2, 1, 1, 1, 4, KC, 9, MARKED, MODE>(a, bx, by, bz);
     else conv_body<T, 2, 1, 1, 1, 4, KC, 1, MARKED, MODE>(b, bx, by, bz);
+}
+
+// The same where the 3x3 call takes one of the eight-wave shapes with the whole of 256 channels (SHAPE: 4 = 64 x 32, 5 = 32 x 32, 6 = 32 x 16
+// patches): either call sums in the order it has by itself.  A 1x1 workgroup is the four waves it is there; the other four end before its
+// first barrier (waves that ended are not waited for).
+template <typename T, int SHAPE, bool MARKED, int MODE>
+__global__ __launch_bounds__(512, 1) void conv_pair_whole_kernel(ConvArgs a, ConvArgs b, PairGrid g)
+{
+    bool first;
+    int bx, by, bz;
+    if (!pair_place<1>(g, first, bx, by, bz)) return;
+    if (first) {
+        conv_body<T, SHAPE == 5 ? 1 : 2, 1, 1, 1, 8, 16, 9, MARKED, MODE, SHAPE == 6>(a, bx, by, bz);
+    } else {
+        if (threadIdx.x >= 256) return;
+        conv_body<T, 2, 1, 1, 1, 4, 8, 1, MARKED>(b, bx, by, bz);
+    }
 }
 
 // v += the ksplit shares of one run of N channels, B of them in flight at a time (each batch is a
@@ -1686,27 +1710,39 @@ int launch_pair(const ConvArgs& a, const ConvPlan& pa, const ConvArgs& b, const 
 {
     const size_t lds = std::max(pa.lds, pb.lds);
     // tiles in groups of eight (one per XCD), every group times the slabs
-    const int ta = pa.bands * pa.groups, tb = pb.bands * pb.groups;
-    const int wgs_a = (ta + 7) / 8 * 8 * pa.slabs, wgs_b = (tb + 7) / 8 * 8 * pb.slabs;
-    const dim3 grid(wgs_a + wgs_b);
-    auto launch = [&](auto kern) {
+    PairGrid g;
+    g.ta = pa.bands * pa.groups;
+    g.tb = pb.bands * pb.groups;
+    const int apart = pa.cfg == 3 ? 8 : 1;
+    g.wgs_a = (g.ta + apart - 1) / apart * apart * pa.slabs;
+    g.xa = fast_div(pa.slabs); g.ya = fast_div(pa.bands); g.xb = fast_div(pb.slabs); g.yb = fast_div(pb.bands);
+    const dim3 grid(g.wgs_a + (g.tb + apart - 1) / apart * apart * pb.slabs);
+    auto launch = [&](auto kern, int threads = 256) {
         if (lds > 48 * 1024) {
             hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             SIGE_REQUIRE(e == hipSuccess, SIGE_ERR_HIP, "sige_fused_conv_pair: cannot reserve %zu bytes of LDS: %s", lds,
                          hipGetErrorString(e));
         }
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, a, b, wgs_a, fast_div(pa.slabs), fast_div(pa.bands), ta,
-                           fast_div(pb.slabs), fast_div(pb.bands), tb);
+        hipLaunchKernelGGL(kern, grid, dim3(threads), lds, st, a, b, g);
         SIGE_LAUNCH_CHECK("sige_fused_conv_pair");
         return (int)SIGE_OK;
     };
-    const bool once = pa.mode == kOnce && pb.mode == kOnce;   // (both read the same number of channels in practice)
-    if (marked) {
-        if (once) return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, true, kOnce>) : launch(conv_pair_kernel<T, 4, true, kOnce>);
-        return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, true, kPlain>) : launch(conv_pair_kernel<T, 4, true, kPlain>);
-    }
-    if (once) return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, false, kOnce>) : launch(conv_pair_kernel<T, 4, false, kOnce>);
-    return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, false, kPlain>) : launch(conv_pair_kernel<T, 4, false, kPlain>);
+    auto as = [&](auto marked_c) {
+        constexpr bool M = decltype(marked_c)::value;
+        if (pa.cfg != 3) {
+            if constexpr (sizeof(T) == 2) {
+                const bool at_once = pa.mode == kOnce;
+                if (pa.cfg == 4) return at_once ? launch(conv_pair_whole_kernel<T, 4, M, kOnce>, 512) : launch(conv_pair_whole_kernel<T, 4, M, kPlain>, 512);
+                if (pa.cfg == 5) return at_once ? launch(conv_pair_whole_kernel<T, 5, M, kOnce>, 512) : launch(conv_pair_whole_kernel<T, 5, M, kPlain>, 512);
+                if (pa.cfg == 6 && at_once) return launch(conv_pair_whole_kernel<T, 6, M, kOnce>, 512);
+            }
+            return fail(SIGE_ERR_UNSUPPORTED, "sige_fused_conv_pair: internal: shape %d shares no launch", pa.cfg);
+        }
+        const bool once = pa.mode == kOnce && pb.mode == kOnce;   // (both read the same number of channels in practice)
+        if (once) return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, M, kOnce>) : launch(conv_pair_kernel<T, 4, M, kOnce>);
+        return pa.kc == 8 ? launch(conv_pair_kernel<T, 8, M, kPlain>) : launch(conv_pair_kernel<T, 4, M, kPlain>);
+    };
+    return marked ? as(std::true_type{}) : as(std::false_type{});
 }
 
 // Re-lays an OIHW weight into the fragment order the kernels read.

@@ -1113,6 +1113,68 @@ def test_fused_conv_pair_wide_shortcut(oracle, dtype, Cin, C3, C1, b, n, staged,
         assert_close(t1.view(n, b, b, C1)[i, :hh, :ww], want, td, f"1x1, block {i}")
 
 
+@pytest.mark.parametrize("dtype,C3,C1,Cs,res,b,n,shape,launches", [
+    ("f16", 96, 72, 256, 32, 8, 3, 6, 1),       # 32 x 16 patches
+    ("bf16", 512, 40, 256, 18, 16, 1, 6, 1),    # ... too many of them beside the shortcut's: 32 x 32
+    ("bf16", 256, 64, 256, 32, 8, 9, 5, 1),     # 32 x 32: more than 128 workgroups of them
+    ("f16", 320, 256, 256, 32, 16, 2, 5, 1),    # ... too many: 64 x 32
+    ("f16", 64, 64, 256, 60, 28, 4, 5, 1),      # ... whose tile (3 x 30) is more than one batch of requests
+    ("bf16", 40, 64, 256, 27, 6, 9, 4, 1),      # 64 x 32, one block
+    ("f16", 96, 40, 128, 22, 4, 11, 4, 1),      # ... four of them, more than one batch; a shortcut of one chunk
+    ("f16", 256, 64, 64, 32, 8, 3, 6, 2),       # a shortcut in chunks of four: two launches
+])
+def test_fused_conv_pair_whole(oracle, dtype, C3, C1, Cs, res, b, n, shape, launches):
+    """Pairs whose 3x3 call stages the whole of 256 channels in an eight-wave shape share one launch with the shortcut: bit for
+    bit what the two calls write, also on marked lists (the launch builds them), and the 3x3 result against the oracle."""
+    Cin = 256
+    rng = np.random.default_rng(C3 + C1 + res + b)
+    td = DT[dtype]
+    x3, x1 = (torch.from_numpy(rng.standard_normal((res, res, c)).astype(np.float32)).to(td) for c in (Cin, Cs))
+    w3, b3 = inputs.conv_params(rng, C3, Cin, 3, td)
+    w1, b1 = inputs.conv_params(rng, C1, Cs, 1, td)
+    conv3, conv1 = SigeConv(dev(w3), b3, res, res, b, 1, 1), SigeConv(dev(w1), b1, res, res, b, 1, 0)
+    every = BlockList(conv3.g, "cuda").all_active().indices
+    pick = np.sort(np.append(rng.permutation(len(every) - 1)[:n - 1], len(every) - 1))     # the ragged last block among them
+    idx = every[torch.from_numpy(pick).cuda()]
+    lists = [BlockList(c.g, "cuda", max_blocks=n) for c in (conv3, conv1)]
+    for bl in lists:
+        bl.indices.copy_(idx)
+        bl.count.fill_(n)
+        bl.n_host = n
+    ws = Workspace("cuda")
+    d3, d1 = dev(x3), dev(x1)
+    cache3, cache1 = (torch.from_numpy(rng.standard_normal((res, res, c)).astype(np.float32)).to(td) for c in (C3, C1))
+    resid = dev(torch.from_numpy(rng.standard_normal((res, res, C3)).astype(np.float32)).to(td))
+    assert api.sige_conv_plan(td, conv3.g, Cin, C3, n).shape == shape
+    ya, yb = dev(cache3).clone(), dev(cache1).clone()
+    conv3.forward(d3, ya, lists[0], ws, residual=resid, fused=True)
+    conv1.forward(d1, yb, lists[1], ws, fused=True)
+    y3, y1 = dev(cache3).clone(), dev(cache1).clone()
+    c3, _ = conv3.fused_call(d3, y3, lists[0], ws, residual=resid, tag="p3")
+    c1, _ = conv1.fused_call(d1, y1, lists[1], ws, tag="p1")
+    assert kernel_launches(lambda: api.sige_fused_conv_pair(c3, c1)) == launches
+    api.sige_fused_conv_pair(c3, c1)
+    torch.cuda.synchronize()
+    assert torch.equal(y3, ya) and torch.equal(y1, yb), "pair differs from the two calls"
+    mask = torch.zeros((res, res), dtype=torch.uint8, device="cuda")
+    for yy, xx in idx.tolist():
+        mask[min(yy + 2, res - 1), min(xx + 2, res - 1)] = 1
+    got = [BlockList(c.g, "cuda", max_blocks=n) for c in (conv3, conv1)]
+    BlockList.mark_together(got, mask_in=mask)
+    y3, y1 = dev(cache3).clone(), dev(cache1).clone()
+    m3, _ = conv3.fused_call(d3, y3, got[0], ws, residual=resid, tag="p3")
+    m1, _ = conv1.fused_call(d1, y1, got[1], ws, tag="p1")
+    descs = [bl.desc() for bl in got]
+    assert kernel_launches(lambda: api.sige_fused_conv_pair_marked(m3, m1, descs)) == (1 if launches == 1 else 3)
+    api.sige_fused_conv_pair_marked(m3, m1, descs)
+    torch.cuda.synchronize()
+    for bl in got:
+        assert int(bl.count.item()) == n and torch.equal(bl.indices, idx)
+    assert torch.equal(y3, ya) and torch.equal(y1, yb), "marked pair"
+    want = oracle.conv2d(f64(x3), f64(w3), f64(b3), 1, 1) + f64(resid)
+    assert_close(y3, oracle.select_blocks(want, f64(cache3), idx.cpu().numpy(), b, b), td, "3x3 call of the pair")
+
+
 @pytest.mark.parametrize("dtype,Cin,C3,C1,res,b,frac", [
     ("f16", 128, 128, 256, 256, 16, 0.01),   # benchmark configuration 2: the launch builds the lists itself
     ("bf16", 64, 40, 72, 100, 8, 0.03),      # 169 blocks of 8x8 on a ragged grid

@@ -9,8 +9,9 @@
 // l+32, the online softmax needs a single cross-lane exchange, the probabilities
 // feed the second MFMA (O^T = V^T P^T) straight from registers because the
 // contraction index may be permuted freely as long as V^T is read with the same
-// permutation, and the running rescale of O^T is lane-local.  The waves of a workgroup share
-// 32 queries and split the keys; when few queries are active the key range is also split over
+// permutation, and the running rescale of O^T is lane-local.  The waves of a workgroup are groups that split
+// the keys: of one wave each on the same 32 queries (few queries, large heads) or of four waves on 128 queries that fetch their
+// chunks once (attn_kernel); when few queries are active the key range is also split over
 // workgroups and a second small kernel merges the partial (max, sum, O) triples.  Single precision has a kernel of
 // its own further down (attn_f32_kernel).
 #include "common.h"
@@ -75,6 +76,7 @@ struct AttnArgs {
     int q_ld, kv_ld, o_ld;
     int Nq, T, heads, d;
     int splits, chunks_per_split;
+    int groups;      // half types: groups of waves in a workgroup (one where it has one chunk, whatever the kernel is built for)
     float scale_log2e;
     // queries taken from a full tensor by block list (q_blocks != NULL): query i is pixel i % q_tpb of
     // block i / q_tpb, at row (y0 + py) * q_W + x0 + px of q (clamped into the q_H x q_W map)
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) 
     const int k_stride = (FAR ? 32 * DT : d) * 2 + 16;             // bytes per K row in LDS (NQ > 1)
     const int vs0 = wk * (KCH * VROW);             // this group's V rows, then the groups' K rows
     char* const vs = lds + vs0;
-    char* const ks = lds + NK * KCH * VROW + wk * (KCH * k_stride);
+    char* const ks = lds + (NK == 1 ? 1 : a.groups) * (KCH * VROW) + wk * (KCH * k_stride);
     char* const qs = lds + NK * KCH * VROW;        // Q_LDS: [DK][64 lanes], behind the V rows
 
     const int chunks_total = (a.T + KCH - 1) / KCH;
@@ -407,8 +409,9 @@ __global__ __launch_bounds__(64 * NQ * NK, NQ * NK == 8 || (NQ == 4 && DT == 4) 
     } else {
         l_tot = l_run + __shfl_xor(l_run, 32);
     }
-    if constexpr (NK == 1) {                       // no other wave has keys of these queries: straight from the registers
-        if (!q_ok) return;
+    // no other wave has keys of these queries: straight from the registers
+    if (NK == 1 || a.chunks_per_split == 1) {
+        if (!q_ok || wk != 0) return;
         const float inv = 1.0f / l_tot;
         float* const w = a.ws + (((long)blockIdx.z * a.heads + head) * a.Nq + qi) * (d + 4);
         if (a.splits > 1 && half == 0) *(float2*)(w + d) = make_float2(m_run, l_tot);
@@ -789,6 +792,7 @@ static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt, size_t
     double best_us = 1e30;
     for (int form = 0; form < 3; ++form) {
         if (fixed_us[DK][form] == 0.0f) continue;
+        if (form > 0 && chunks == 1 && DT <= 3 && target < 0) continue;      // (one wave works either way: 300 calls, the common form 3 - 35 % faster)
         const AttnForm g = form == 0 ? AttnForm{4, common_groups(DT), 1} : AttnForm{1, form == 1 ? 4 : 8, 1};
         const long base = (long)heads * ((Nq + 32 * g.nq - 1) / (32 * g.nq));
         const int r = DK > 8 ? 1 : held[DK][form];
@@ -809,12 +813,15 @@ static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt, size_t
 }
 
 template <typename T, int DT, int NQ, int NK, bool FAR = false>
-static int launch_attn_dt(const AttnArgs& a, hipStream_t st)
+static int launch_attn_dt(AttnArgs a, hipStream_t st)
 {
     constexpr int KCH = 32 * key_tiles(DT);
-    const size_t lds = std::max((size_t)NK * KCH * (v_row_bytes(DT) + (NQ > 1 ? (FAR ? 32 * DT : a.d) * 2 + 16 : 0)) +
+    // one chunk: the first of several groups of four waves is the workgroup (f16, 5664 queries x 8 heads of 96 on 32 keys 12.5 -> 9.2 us,
+    // 994 x 1 of 64 on 64 5.2 -> 4.4)
+    a.groups = NQ > 1 && a.chunks_per_split == 1 ? 1 : NK;
+    const size_t lds = std::max((size_t)a.groups * KCH * (v_row_bytes(DT) + (NQ > 1 ? (FAR ? 32 * DT : a.d) * 2 + 16 : 0)) +
                                     (q_in_lds(DT, NQ) ? 2 * DT * 1024 : 0),
-                                NK == 1 ? 0 : (size_t)NK * NQ * 32 * (a.d + 4) * sizeof(float));
+                                a.groups == 1 ? 0 : (size_t)NK * NQ * 32 * (a.d + 4) * sizeof(float));
     dim3 grid((a.Nq + 32 * NQ - 1) / (32 * NQ), a.heads, a.splits);
     const bool odd = ((a.d + 15) / 16) & 1;        // d % 32 is 8 or 16
     auto kern = attn_kernel<T, DT, !FAR, NQ, NK, FAR>;
@@ -828,7 +835,7 @@ static int launch_attn_dt(const AttnArgs& a, hipStream_t st)
         SIGE_REQUIRE(e == hipSuccess, SIGE_ERR_HIP, "sige_sparse_attn: cannot reserve %zu bytes of LDS: %s", lds,
                      hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(kern, grid, dim3(64 * NQ * NK), lds, st, a);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * NQ * a.groups), lds, st, a);
     SIGE_LAUNCH_CHECK("sige_sparse_attn");
     if (a.splits > 1) return launch_merge<T>(a, st);
     return SIGE_OK;

@@ -118,6 +118,29 @@ def test_sparse_attention_heads_of_seven_tiles(oracle, T, d, dtype):
 
 
 @pytest.mark.parametrize("T,heads,d,n_q,dtype,wgs", [
+    (64, 2, 32, 130, "f16", None), (40, 3, 40, 300, "bf16", None), (64, 2, 96, 70, "bf16", None), (1, 1, 64, 33, "f16", None),
+    (32, 2, 160, 70, "bf16", None), (30, 2, 256, 70, "f16", None),
+    (200, 2, 48, 130, "f16", 16), (256, 1, 96, 130, "bf16", 8),        # several chunks, four splits of one: partial sums
+    (64, 2, 40, 130, "bf16", 10), (64, 2, 72, 130, "f16", 10),         # one wave per key group
+])
+def test_sparse_attention_one_chunk_per_workgroup(oracle, T, heads, d, n_q, dtype, wgs):
+    """One chunk of keys per workgroup: a single group of waves has it and writes without the others (wgs: the number of workgroups that
+    chooses form and splits); other heads are not numbers."""
+    c = inputs.attention_case(T + d, T, heads, d, n_q, dtype)
+    want = oracle.attention(f64(c["q"]), f64(c["k"]), f64(c["v"]), c["scale"])
+    ws = torch.empty(64 * heads * n_q * (d + 4), dtype=torch.float32, device="cuda")
+    q, o = dev(c["q"]), torch.full_like(dev(c["q"]), 7.0)
+    for only in range(heads):
+        k, v = dev(c["k"]).clone(), dev(c["v"]).clone()
+        for t in (k, v):
+            t[:, :only] = t[:, only + 1:] = float("nan")
+        with api.knobs(ATTN_WGS=wgs):
+            api.sige_sparse_attn(q, k, v, o, c["scale"], workspace=ws)
+        torch.cuda.synchronize()
+        attn_close(o[:, only:only + 1], want[:, only:only + 1], DT[dtype], f"head {only}")
+
+
+@pytest.mark.parametrize("T,heads,d,n_q,dtype,wgs", [
     (1024, 8, 72, 192, "bf16", 128), (512, 8, 88, 24, "bf16", 32), (512, 8, 160, 24, "bf16", 128), (1024, 8, 256, 64, "f16", 128),
     (1024, 1, 128, 24, "f16", 32), (4096, 8, 64, 64, "f16", 256), (9216, 8, 40, 96, "bf16", 232),
     (4096, 8, 128, 1500, "f16", 384), (1024, 4, 96, 800, "bf16", 100),

@@ -752,7 +752,8 @@ static int launch_merge(const AttnArgs& a, hipStream_t st)
 // queries on 77 to 9216 keys, heads of 24 to 256, one to eight of them, each form with every number of splits near its
 // best: 18000 times; the choice takes 1.01 times the best of them in the mean, 1.2 at worst; of the times before waves split the keys it makes 0.83 in the mean and 1.14 at worst, the model of 24 calls made 0.87 and 1.30).  What it trades:
 // four waves on the same chunks fetch them once; waves with chunks of their own have no barriers and no partial sums for a merge kernel
-// (3 us, and 2.75 per million of them) where a call has enough queries to fill the chip, but fetch K in pieces of 32 bytes of a row, which
+// (3 us, and 2.75 per million of them; half a microsecond more is asked of a split, since the sum is right to about that: of 2500 calls 123
+// instead of 146 then take more than 5 % longer than the better of both) where a call has enough queries to fill the chip, but fetch K in pieces of 32 bytes of a row, which
 // costs more where the rows of a head are not side by side.
 struct AttnForm { int nq, nk, splits; };           // waves with the same chunks, key groups, splits over workgroups
 // room: floats of workspace, what the splits' partial sums have to fit into.
@@ -804,7 +805,7 @@ static AttnForm plan_attn(int Nq, int T, int heads, int d, sige_dtype dt, size_t
             // workgroups side by side lengthen each other's chunks; the fixed part of the next ones runs beside the chunks of those before
             const double us = fixed_us[DK][form] * (1.0 + 0.5 * ((on_one + r - 1) / r - 1)) + on_one / r * chunk * (1.0 + 0.4 * (r - 1)) +
                               (on_one % r ? chunk * (1.0 + 0.4 * (on_one % r - 1)) : 0.0);
-            const double merge = real == 1 ? 0.0 : (real > 16 ? 3.3 : 3.0) + 2.75e-6 * real * heads * Nq * (d + 4);
+            const double merge = real == 1 ? 0.0 : (real > 16 ? 3.8 : 3.5) + 2.75e-6 * real * heads * Nq * (d + 4);
             const double cost = target >= 0 ? std::abs(target - (double)base * real) : us + merge;
             if (cost < best_us) { best_us = cost; f = g; f.splits = real; }
         }

@@ -325,7 +325,8 @@ int sige_fused_conv(const void* x, sige_dtype dt, int32_t Cin, int32_t x_ld, int
  * paper's per-layer pipeline run for two layers side by side).  Each struct holds the arguments
  * of one sige_fused_conv call, with the same meaning and the same checks.  When the first is a
  * 3x3 and the second a 1x1 convolution of the same dtype and both would take the few-block kernel
- * shape without a K split over workgroups, they run as ONE kernel launch (on this part a launch
+ * shape without a K split over workgroups (or the 3x3 one, half types, stages the whole of 256
+ * channels at once), they run as ONE kernel launch (on this part a launch
  * of a dependent kernel costs more than the work of such a call), unless the 1x1 call has so many
  * rows and channels that the two are faster by themselves; otherwise one after the other.
  * The outputs are bit-identical to those of the two separate calls.  The two calls must not
